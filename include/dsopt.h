@@ -224,9 +224,9 @@ int ds_esdf_release(ds_plan* plan, int32_t scene_id);
  * no occupied (no free) voxel yields values >= 1e9 * voxel in magnitude.
  * The field becomes scene `scene_id` exactly as with ds_esdf_upload;
  * `out_vals` (device, nx*ny*nz floats, may be NULL) receives a copy of the
- * signed distances.  Temporary space (4 * nx*ny*nz floats) comes from the
- * arena.  Errors: DS_ERR_INVALID (dims < 2 or > 1024, voxel <= 0),
- * DS_ERR_NOMEM. */
+ * signed distances.  Temporary space (nx*ny*nz floats, as many again without
+ * out_vals, and a bit per voxel) comes from the arena.  Errors:
+ * DS_ERR_INVALID (dims < 2 or > 1024, voxel <= 0), DS_ERR_NOMEM. */
 int ds_esdf_from_occupancy(ds_plan* plan, int32_t scene_id, const uint8_t* occ, int nx, int ny,
                            int nz, float voxel, const float origin[3], float* out_vals,
                            void* stream);

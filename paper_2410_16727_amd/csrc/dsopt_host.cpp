@@ -368,6 +368,77 @@ int run_optimize(ds_plan* p, const ds_problem* probs, int n, hipStream_t s, floa
   return DS_OK;
 }
 
+// Check a scene's grid, retire the scene of that id if there is one, and give
+// the new one its place in the arena (rec; nothing is enqueued).
+int open_scene(ds_plan* p, int32_t scene_id, int nx, int ny, int nz, float voxel,
+               const float origin[3], SceneRec& rec) {
+  if (scene_id < 0) return fail(DS_ERR_INVALID, "scene id must be >= 0");
+  if (nx < 2 || ny < 2 || nz < 2) return fail(DS_ERR_INVALID, "grid dims must be >= 2");
+  if (!(voxel > 0) || !std::isfinite(voxel) || !finite_all(origin, 3))
+    return fail(DS_ERR_INVALID, "voxel must be > 0 and origin finite");
+  size_t cells = (size_t)(nx - 1) * (ny - 1) * (nz - 1);
+  size_t rec_bytes = cells * 32;
+  if (rec_bytes > 0x7fffffffull) return fail(DS_ERR_INVALID, "grid too large (> 2^26 cells)");
+  // the kernels form a cell's record index as ix + (nx-1) * ((ny-1) * iz + iy)
+  // with 24-bit multiplies: both factors of each product must stay below 2^24
+  if ((size_t)(ny - 1) * (nz - 1) >= (1u << 24) || (size_t)(nx - 1) >= (1u << 24))
+    return fail(DS_ERR_INVALID, "grid too flat: (ny-1)*(nz-1) must be < 2^24");
+  poll_deferred(p, false);
+  if (p->scenes.count(scene_id)) {
+    if (ds_serve_uses_scene(p, scene_id))
+      return fail(DS_ERR_BUSY, "scene %d is used by a serving request", scene_id);
+    HIP_TRY(hipDeviceSynchronize());
+    p->arena.release(p->scenes[scene_id].off);
+    p->scenes.erase(scene_id);
+  }
+  // coarse block size: the smallest 2^s (s >= 2) cells per axis whose table
+  // fits COARSE_MAX blocks
+  int cshift = 2, cdx, cdy, cdz;
+  for (;; ++cshift) {
+    const int b = 1 << cshift;
+    cdx = (nx - 1 + b - 1) / b;
+    cdy = (ny - 1 + b - 1) / b;
+    cdz = (nz - 1 + b - 1) / b;
+    if ((long long)cdx * cdy * cdz <= COARSE_MAX) break;
+  }
+  const size_t coarse_at = (rec_bytes + 255) / 256 * 256;
+  rec.off = arena_alloc(p, coarse_at + COARSE_BYTES);
+  if (rec.off == SIZE_MAX)
+    return fail(DS_ERR_NOMEM, "arena full (scene %d, %zu B)", scene_id, rec_bytes);
+  // one level of the coarse table: the largest sphere's skip distance
+  // (radius + far) spans 8 levels, so every sphere's test fits in 15
+  float rmax = 0.f;
+  for (int k = 0; k < p->robot.ns; ++k) rmax = std::max(rmax, p->robot.sph[k].w);
+  rec.dev.rec = reinterpret_cast<const float4*>(p->arena.ptr(rec.off));
+  rec.dev.nx = nx; rec.dev.ny = ny; rec.dev.nz = nz;
+  rec.dev.ox = origin[0]; rec.dev.oy = origin[1]; rec.dev.oz = origin[2];
+  rec.dev.inv_h = 1.f / voxel;
+  rec.dev.bytes = (uint32_t)rec_bytes;
+  rec.dev.coarse = p->arena.ptr(rec.off) + coarse_at;
+  rec.dev.cq = (rmax + p->params.far) / 8.f;
+  rec.dev.cshift = cshift;
+  rec.dev.cdx = cdx; rec.dev.cdy = cdy; rec.dev.cdz = cdz;
+  return DS_OK;
+}
+
+// Make the scene resident from its node values (device memory).
+int fill_scene(ds_plan* p, int32_t scene_id, const float* vals, const SceneRec& rec,
+               hipStream_t s) {
+  const SceneDev& d = rec.dev;
+  HIP_TRY(launch_esdf_pack(vals, d.nx, d.ny, d.nz, d.cshift, d.cdx, d.cdy, d.cdz, d.cq,
+                           const_cast<float4*>(d.rec), const_cast<uint8_t*>(d.coarse), s));
+  p->scenes[scene_id] = rec;
+  return DS_OK;
+}
+
+bool on_device(const void* ptr) {
+  hipPointerAttribute_t attr;
+  const bool dev = hipPointerGetAttributes(&attr, ptr) == hipSuccess &&
+                   (attr.type == hipMemoryTypeDevice || attr.type == hipMemoryTypeManaged);
+  (void)hipGetLastError();
+  return dev;
+}
+
 }  // namespace dsh
 
 using namespace dsh;
@@ -497,79 +568,23 @@ void ds_plan_destroy(ds_plan* p) {
 int ds_esdf_upload(ds_plan* p, int32_t scene_id, const float* vals, int nx, int ny, int nz,
                    float voxel, const float origin[3], void* stream) {
   if (!p || !vals || !origin) return fail(DS_ERR_INVALID, "NULL argument");
-  if (scene_id < 0) return fail(DS_ERR_INVALID, "scene id must be >= 0");
-  if (nx < 2 || ny < 2 || nz < 2) return fail(DS_ERR_INVALID, "grid dims must be >= 2");
-  if (!(voxel > 0) || !std::isfinite(voxel) || !finite_all(origin, 3))
-    return fail(DS_ERR_INVALID, "voxel must be > 0 and origin finite");
-  size_t cells = (size_t)(nx - 1) * (ny - 1) * (nz - 1);
-  size_t rec_bytes = cells * 32;
-  if (rec_bytes > 0x7fffffffull) return fail(DS_ERR_INVALID, "grid too large (> 2^26 cells)");
-  // the kernels form a cell's record index as ix + (nx-1) * ((ny-1) * iz + iy)
-  // with 24-bit multiplies: both factors of each product must stay below 2^24
-  if ((size_t)(ny - 1) * (nz - 1) >= (1u << 24) || (size_t)(nx - 1) >= (1u << 24))
-    return fail(DS_ERR_INVALID, "grid too flat: (ny-1)*(nz-1) must be < 2^24");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  poll_deferred(p, false);
-  if (p->scenes.count(scene_id)) {
-    if (ds_serve_uses_scene(p, scene_id))
-      return fail(DS_ERR_BUSY, "scene %d is used by a serving request", scene_id);
-    HIP_TRY(hipDeviceSynchronize());
-    p->arena.release(p->scenes[scene_id].off);
-    p->scenes.erase(scene_id);
-  }
-  // coarse block size: the smallest 2^s (s >= 2) cells per axis whose table
-  // fits COARSE_MAX blocks
-  int cshift = 2, cdx, cdy, cdz;
-  for (;; ++cshift) {
-    const int b = 1 << cshift;
-    cdx = (nx - 1 + b - 1) / b;
-    cdy = (ny - 1 + b - 1) / b;
-    cdz = (nz - 1 + b - 1) / b;
-    if ((long long)cdx * cdy * cdz <= COARSE_MAX) break;
-  }
-  const size_t coarse_at = (rec_bytes + 255) / 256 * 256;
-  size_t off = arena_alloc(p, coarse_at + COARSE_BYTES);
-  if (off == SIZE_MAX) return fail(DS_ERR_NOMEM, "arena full (scene %d, %zu B)", scene_id, rec_bytes);
+  SceneRec rec;
+  if (int rc = open_scene(p, scene_id, nx, ny, nz, voxel, origin, rec)) return rc;
   const float* src = vals;
   size_t tmp_off = SIZE_MAX;
-  hipPointerAttribute_t attr;
-  bool on_device = false;
-  if (hipPointerGetAttributes(&attr, vals) == hipSuccess)
-    on_device = attr.type == hipMemoryTypeDevice || attr.type == hipMemoryTypeManaged;
-  (void)hipGetLastError();
   size_t nbytes = (size_t)nx * ny * nz * sizeof(float);
-  if (!on_device) {
+  if (!on_device(vals)) {
     tmp_off = arena_alloc(p, nbytes);
     if (tmp_off == SIZE_MAX) {
-      p->arena.release(off);
+      p->arena.release(rec.off);
       return fail(DS_ERR_NOMEM, "arena full (scene staging, %zu B)", nbytes);
     }
     HIP_TRY(hipMemcpyAsync(p->arena.ptr(tmp_off), vals, nbytes, hipMemcpyHostToDevice, s));
     src = reinterpret_cast<const float*>(p->arena.ptr(tmp_off));
   }
-  HIP_TRY(launch_esdf_pack(src, nx, ny, nz, reinterpret_cast<float4*>(p->arena.ptr(off)), s));
-  uint8_t* coarse = p->arena.ptr(off) + coarse_at;
-  // one level of the coarse table: the largest sphere's skip distance
-  // (radius + far) spans 8 levels, so every sphere's test fits in 15
-  float rmax = 0.f;
-  for (int k = 0; k < p->robot.ns; ++k) rmax = std::max(rmax, p->robot.sph[k].w);
-  const float cq = (rmax + p->params.far) / 8.f;
-  HIP_TRY(launch_coarse(src, nx, ny, nz, cshift, cdx, cdy, cdz, cq, coarse, s));
-  if (tmp_off != SIZE_MAX)
-    if (int rc = defer_free(p, tmp_off, s)) return rc;
-  SceneRec rec;
-  rec.off = off;
-  rec.dev.rec = reinterpret_cast<const float4*>(p->arena.ptr(off));
-  rec.dev.nx = nx; rec.dev.ny = ny; rec.dev.nz = nz;
-  rec.dev.ox = origin[0]; rec.dev.oy = origin[1]; rec.dev.oz = origin[2];
-  rec.dev.inv_h = 1.f / voxel;
-  rec.dev.bytes = (uint32_t)rec_bytes;
-  rec.dev.coarse = coarse;
-  rec.dev.cq = cq;
-  rec.dev.cshift = cshift;
-  rec.dev.cdx = cdx; rec.dev.cdy = cdy; rec.dev.cdz = cdz;
-  p->scenes[scene_id] = rec;
-  return DS_OK;
+  if (int rc = fill_scene(p, scene_id, src, rec, s)) return rc;
+  return tmp_off != SIZE_MAX ? defer_free(p, tmp_off, s) : DS_OK;
 }
 
 int ds_esdf_from_occupancy(ds_plan* p, int32_t scene_id, const uint8_t* occ, int nx, int ny,
@@ -584,15 +599,15 @@ int ds_esdf_from_occupancy(ds_plan* p, int32_t scene_id, const uint8_t* occ, int
   poll_deferred(p, false);
   const size_t n = (size_t)nx * ny * nz;
   const size_t fb = n * sizeof(float);
-  size_t occ_off = SIZE_MAX, work_off = arena_alloc(p, 5 * fb);
-  if (work_off == SIZE_MAX) return fail(DS_ERR_NOMEM, "arena full (distance transform, %zu B)", 5 * fb);
+  // occupancy bits, the signed squared distances between the passes and,
+  // unless the caller takes them, the distances
+  const size_t bits = (edt_bits_bytes(nx, ny, nz) + 255) / 256 * 256;
+  const size_t work_bytes = bits + (out_vals ? 1 : 2) * fb;
+  size_t occ_off = SIZE_MAX, work_off = arena_alloc(p, work_bytes);
+  if (work_off == SIZE_MAX)
+    return fail(DS_ERR_NOMEM, "arena full (distance transform, %zu B)", work_bytes);
   const uint8_t* occ_dev = occ;
-  hipPointerAttribute_t attr;
-  bool on_device = false;
-  if (hipPointerGetAttributes(&attr, occ) == hipSuccess)
-    on_device = attr.type == hipMemoryTypeDevice || attr.type == hipMemoryTypeManaged;
-  (void)hipGetLastError();
-  if (!on_device) {
+  if (!on_device(occ)) {
     occ_off = arena_alloc(p, n);
     if (occ_off == SIZE_MAX) {
       p->arena.release(work_off);
@@ -601,12 +616,18 @@ int ds_esdf_from_occupancy(ds_plan* p, int32_t scene_id, const uint8_t* occ, int
     HIP_TRY(hipMemcpyAsync(p->arena.ptr(occ_off), occ, n, hipMemcpyHostToDevice, s));
     occ_dev = p->arena.ptr(occ_off);
   }
-  float* w = reinterpret_cast<float*>(p->arena.ptr(work_off));
-  float* dist = w + 4 * n;
-  HIP_TRY(launch_esdf_from_occupancy(occ_dev, nx, ny, nz, voxel, w, w + n, w + 2 * n, w + 3 * n,
-                                     dist, s));
-  if (out_vals) HIP_TRY(hipMemcpyAsync(out_vals, dist, fb, hipMemcpyDeviceToDevice, s));
-  int rc = ds_esdf_upload(p, scene_id, dist, nx, ny, nz, voxel, origin, stream);
+  // the scene's place first: a scene that is replaced waits for the device,
+  // and every launch below then follows the one before it at once
+  SceneRec rec;
+  int rc = open_scene(p, scene_id, nx, ny, nz, voxel, origin, rec);
+  if (!rc) {
+    uint8_t* w = p->arena.ptr(work_off);
+    float* work = reinterpret_cast<float*>(w + bits);
+    float* dist = out_vals ? out_vals : work + n;
+    HIP_TRY(launch_esdf_from_occupancy(occ_dev, nx, ny, nz, voxel,
+                                       reinterpret_cast<unsigned long long*>(w), work, dist, s));
+    rc = fill_scene(p, scene_id, dist, rec, s);
+  }
   if (int r2 = defer_free(p, work_off, s)) return r2;
   if (occ_off != SIZE_MAX)
     if (int r2 = defer_free(p, occ_off, s)) return r2;

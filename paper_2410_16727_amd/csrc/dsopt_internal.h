@@ -123,11 +123,16 @@ bool ds_serve_uses_scene(const ds_plan* plan, int32_t scene_id);
 // with the optional terms (self-collision, swept sub-samples) compiled in.
 namespace dsk {
 inline bool params_ext(const ParamsDev& P) { return P.ws != 0.f || P.nsub > 0; }
-hipError_t launch_esdf_pack(const float* vals, int nx, int ny, int nz, float4* rec,
+// A field's cell records and its coarse table (COARSE_BYTES) (dsopt_scene.hip).
+hipError_t launch_esdf_pack(const float* vals, int nx, int ny, int nz, int shift, int cdx,
+                            int cdy, int cdz, float cq, float4* rec, uint8_t* table,
                             hipStream_t s);
-// The coarse table of a scene into out (COARSE_BYTES, cleared here).
-hipError_t launch_coarse(const float* vals, int nx, int ny, int nz, int shift, int cdx, int cdy,
-                         int cdz, float cq, uint8_t* out, hipStream_t s);
+// The signed distance field of an occupancy grid into dist (work: as many
+// floats again; bits: edt_bits_bytes) (dsopt_scene.hip).
+size_t edt_bits_bytes(int nx, int ny, int nz);
+hipError_t launch_esdf_from_occupancy(const uint8_t* occ, int nx, int ny, int nz, float voxel,
+                                      unsigned long long* bits, float* work, float* dist,
+                                      hipStream_t s);
 // counter: N_XCD ints when xcd_ranges (N_XCD + 1 ints: the per-XCD queues'
 // bounds in the tile table) is given, else one.
 // tile_list (optional): the queue order, a permutation of 0..n_tiles-1.
@@ -156,9 +161,6 @@ hipError_t launch_zero_i32(int* p, int n, hipStream_t s);
 // counters (N_XCD ints; n_tiles >= 1).
 hipError_t launch_tile_reset(const TileDev* tiles, const ProbDev* probs, int n_tiles, int* counter,
                              hipStream_t s);
-hipError_t launch_esdf_from_occupancy(const uint8_t* occ, int nx, int ny, int nz, float voxel,
-                                      float* w0, float* w1, float* w2, float* w3, float* out,
-                                      hipStream_t s);
 hipError_t launch_serve_step(const RobotDev* rb, const ParamsDev* pp, const ProbDev* probs,
                              const TileDev* tiles, const int* tile_list, int* counter,
                              int max_tiles, int grid_blocks, const int* max_iters_dev, int waves,

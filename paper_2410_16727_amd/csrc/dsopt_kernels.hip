@@ -1996,149 +1996,12 @@ __global__ void k_spheres(const RobotDev* __restrict__ rb, const float* __restri
   }
 }
 
-// x-fastest node values -> 8-corner cell records.
-__global__ void k_esdf_pack(const float* __restrict__ v, int nx, int ny, int nz,
-                            float4* __restrict__ rec) {
-  const long long cx = nx - 1, cy = ny - 1, cz = nz - 1;
-  const long long n = cx * cy * cz;
-  for (long long r = blockIdx.x * (long long)blockDim.x + threadIdx.x; r < n;
-       r += (long long)gridDim.x * blockDim.x) {
-    long long i = r % cx, j = (r / cx) % cy, k = r / (cx * cy);
-    auto at = [&](long long a, long long b, long long c) { return v[a + nx * (b + (long long)ny * c)]; };
-    rec[2 * r] = make_float4(at(i, j, k), at(i + 1, j, k), at(i, j + 1, k), at(i + 1, j + 1, k));
-    rec[2 * r + 1] = make_float4(at(i, j, k + 1), at(i + 1, j, k + 1), at(i, j + 1, k + 1),
-                                 at(i + 1, j + 1, k + 1));
-  }
-}
-
-// Coarse table: minimum node value m over each block of 2^shift cells per
-// axis (the nodes of the block's cells, inclusive of the far faces), kept
-// as the 4-bit level L = the largest L <= 15 with L * cq <= m (0 for a
-// negative or NaN m).  One workgroup per block: its threads stride over
-// the block's nodes (x runs contiguous), then a shuffle and LDS minimum;
-// the level lands in its nibble of the cleared table with an atomic or.
-constexpr int COARSE_THREADS = 256;
-
-__global__ void __launch_bounds__(COARSE_THREADS)
-k_coarse(const float* __restrict__ v, int nx, int ny, int nz, int shift, int cdx, int cdy,
-         float cq, unsigned* __restrict__ out) {
-  __shared__ float s_min[COARSE_THREADS / WAVE];
-  const int b = blockIdx.x;
-  const int bx = b % cdx, by = (b / cdx) % cdy, bz = b / (cdx * cdy);
-  const int x0 = bx << shift, x1 = min((bx + 1) << shift, nx - 1);
-  const int y0 = by << shift, y1 = min((by + 1) << shift, ny - 1);
-  const int z0 = bz << shift, z1 = min((bz + 1) << shift, nz - 1);
-  const int lx = x1 - x0 + 1, ly = y1 - y0 + 1, lz = z1 - z0 + 1;
-  const int n = lx * ly * lz;
-  float m = FLT_MAX;
-  for (int e = threadIdx.x; e < n; e += COARSE_THREADS) {
-    const int i = e % lx, j = (e / lx) % ly, k = e / (lx * ly);
-    m = fminf(m, v[(size_t)(x0 + i) + (size_t)nx * ((y0 + j) + (size_t)ny * (z0 + k))]);
-  }
-  for (int off = 1; off < WAVE; off <<= 1) m = fminf(m, __shfl_xor(m, off));
-  if ((threadIdx.x & (WAVE - 1)) == 0) s_min[threadIdx.x / WAVE] = m;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float r = s_min[0];
-    for (int w = 1; w < COARSE_THREADS / WAVE; ++w) r = fminf(r, s_min[w]);
-    // fminf drops NaN node values; a NaN minimum (every node NaN) or a
-    // negative one gives level 0, which never proves a skip
-    unsigned L = 0;
-    if (r >= 0.f) {
-      L = (unsigned)fminf(floorf(r / cq), 15.f);
-      while (L > 0 && (float)L * cq > r) --L;   // the quotient may have rounded up
-    }
-    atomicOr(&out[b >> 3], L << ((b & 7) * 4));
-  }
-}
-
-// ---------------------------------------------- ESDF from an occupancy grid --
-// Exact squared Euclidean distance transform by separable passes: after the
-// pass along x, y and z, f(v) = min over marked voxels w of |v - w|^2 (index
-// units).  Every value is an integer below 2^24 (or the "none" sentinel), so
-// float arithmetic is exact.
-constexpr float EDT_NONE = 1e20f;
-
-__global__ void k_edt_init(const uint8_t* __restrict__ occ, long long n, int target,
-                           float* __restrict__ f) {
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x)
-    f[i] = ((occ[i] != 0) == (target != 0)) ? 0.f : EDT_NONE;
-}
-
-// One pass along `axis` (0 = x, 1 = y, 2 = z): one workgroup per line, the
-// line staged in LDS.  Element p takes min_q (p - q)^2 + f(q) by scanning
-// outward from q = p and stopping once r^2 >= the best value so far (every
-// farther term is at least r^2): the same minimum as a scan of the whole
-// line.  A line with no finite value stays at "none".
-__global__ void __launch_bounds__(256)
-k_edt_pass(const float* __restrict__ fin, float* __restrict__ fout, int nx, int ny, int nz,
-           int axis) {
-  extern __shared__ float line[];
-  __shared__ int s_any;
-  const int n = axis == 0 ? nx : (axis == 1 ? ny : nz);
-  const long long stride = axis == 0 ? 1 : (axis == 1 ? (long long)nx : (long long)nx * ny);
-  // the line's first element
-  long long l = blockIdx.x, base;
-  if (axis == 0) base = l * nx;
-  else if (axis == 1) base = (l / nx) * (long long)nx * ny + (l % nx);
-  else base = l;
-  if (threadIdx.x == 0) s_any = 0;
-  __syncthreads();
-  int any = 0;
-  for (int q = threadIdx.x; q < n; q += blockDim.x) {
-    const float v = fin[base + q * stride];
-    line[q] = v;
-    any |= v < EDT_NONE;
-  }
-  if (any) s_any = 1;
-  __syncthreads();
-  const bool finite = s_any != 0;
-  for (int pidx = threadIdx.x; pidx < n; pidx += blockDim.x) {
-    float best = line[pidx];
-    if (finite) {
-      for (int r = 1; r < n; ++r) {
-        const float r2 = (float)(r * r);
-        if (r2 >= best) break;
-        if (pidx - r >= 0) best = fminf(best, r2 + line[pidx - r]);
-        if (pidx + r < n) best = fminf(best, r2 + line[pidx + r]);
-      }
-    }
-    fout[base + pidx * stride] = best;
-  }
-}
-
-__global__ void k_edt_final(const uint8_t* __restrict__ occ, const float* __restrict__ d_occ,
-                            const float* __restrict__ d_free, long long n, float voxel,
-                            float* __restrict__ out) {
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x)
-    out[i] = occ[i] ? -voxel * sqrtf(d_free[i]) : voxel * sqrtf(d_occ[i]);
-}
-
 __global__ void k_zero_i32(int* p, int n) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0;
 }
 
 }  // namespace
-
-hipError_t launch_esdf_pack(const float* vals, int nx, int ny, int nz, float4* rec,
-                            hipStream_t s) {
-  long long n = (long long)(nx - 1) * (ny - 1) * (nz - 1);
-  int blocks = (int)std::min<long long>((n + 255) / 256, 65536);
-  hipLaunchKernelGGL(k_esdf_pack, dim3(blocks), dim3(256), 0, s, vals, nx, ny, nz, rec);
-  return hipGetLastError();
-}
-
-hipError_t launch_coarse(const float* vals, int nx, int ny, int nz, int shift, int cdx, int cdy,
-                         int cdz, float cq, uint8_t* out, hipStream_t s) {
-  hipError_t e = launch_zero_i32(reinterpret_cast<int*>(out), COARSE_BYTES / 4, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_coarse, dim3(cdx * cdy * cdz), dim3(COARSE_THREADS), 0, s, vals, nx, ny,
-                     nz, shift, cdx, cdy, cq, reinterpret_cast<unsigned*>(out));
-  return hipGetLastError();
-}
 
 int team_block(int W) { return (W > 1 ? W : WAVES_PER_BLOCK) * WAVE; }
 // dynamic LDS of an optimiser workgroup: a team's partial sums (double
@@ -2245,33 +2108,6 @@ hipError_t launch_spheres(const RobotDev* rb, const float* X, int S, int T, floa
                           hipStream_t s) {
   int n = S * T;
   hipLaunchKernelGGL(k_spheres, dim3((n + 255) / 256), dim3(256), 0, s, rb, X, n, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_esdf_from_occupancy(const uint8_t* occ, int nx, int ny, int nz, float voxel,
-                                      float* w0, float* w1, float* w2, float* w3, float* out,
-                                      hipStream_t s) {
-  const long long n = (long long)nx * ny * nz;
-  const int blocks = (int)std::min<long long>((n + 255) / 256, 65536);
-  float* chain[2][2] = {{w0, w1}, {w2, w3}};
-  for (int c = 0; c < 2; ++c) {   // c = 0: distance to occupied, 1: to free
-    hipLaunchKernelGGL(k_edt_init, dim3(blocks), dim3(256), 0, s, occ, n, c == 0 ? 1 : 0,
-                       chain[c][0]);
-    float* a = chain[c][0];
-    float* b = chain[c][1];
-    for (int axis = 0; axis < 3; ++axis) {
-      int len = axis == 0 ? nx : (axis == 1 ? ny : nz);
-      long long lines = n / len;
-      hipLaunchKernelGGL(k_edt_pass, dim3((unsigned)lines), dim3(256), len * sizeof(float), s, a,
-                         b, nx, ny, nz, axis);
-      float* t = a;
-      a = b;
-      b = t;
-    }
-    chain[c][0] = a;   // result of the three passes
-  }
-  hipLaunchKernelGGL(k_edt_final, dim3(blocks), dim3(256), 0, s, occ, chain[0][0], chain[1][0],
-                     n, voxel, out);
   return hipGetLastError();
 }
 

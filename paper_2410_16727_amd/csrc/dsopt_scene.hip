@@ -1,0 +1,449 @@
+// gfx950 kernels that make a scene resident: the distance field from an
+// occupancy grid, and a field's gather layout (8-corner cell records and the
+// coarse table of block minima).
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cfloat>
+#include <cmath>
+
+#include "dsopt_internal.h"
+
+namespace dsk {
+namespace {
+
+// ------------------------------------------------------ records and table --
+// One workgroup makes the records of a row of up to PACK_XB coarse blocks
+// (2^shift cells per axis) and their table entries, so that the field is
+// read once for both.  A thread owns a column of cells along z inside the
+// row: it keeps the plane of four nodes it has and loads the next one (four
+// loads per record instead of eight), writes the 32-byte record, and adds
+// the column's minimum to its block's in LDS.
+//
+// Table entry: the minimum node value m over the block's cells (the far
+// faces included: a cell's corners), kept as the 4-bit level L = the largest
+// L <= 15 with L * cq <= m (0 for a negative m), two blocks per byte, the
+// even block (linear index bx + cdx (by + cdy bz)) in the low nibble.  The
+// workgroup that owns a byte's even block writes the byte; where the odd one
+// is not in its row it forms that block's minimum from the nodes as well, so
+// no byte has two writers and the table needs no clearing.
+//
+// Bound: HBM, 36 bytes a cell (4 read, 32 written).  200^3: 57 us, 4.9 TB/s
+// of the 5.2 a large copy reaches here (one thread per record and a second
+// kernel that read the field again for the table: 54 + 35 us, and 5 us to
+// clear it).  Workgroups of 256 threads: 60 us; stores past the caches: 146.
+constexpr int PACK_XB = 32;
+constexpr int PACK_THREADS = 512;
+constexpr int PACK_Z = 4;
+
+// Order-preserving integer key of a float (for a minimum by LDS atomics).
+__device__ __forceinline__ int min_key(float v) {
+  const int i = __float_as_int(v);
+  return i < 0 ? i ^ 0x7FFFFFFF : i;
+}
+__device__ __forceinline__ float key_value(int k) {
+  return __int_as_float(k < 0 ? k ^ 0x7FFFFFFF : k);
+}
+
+__device__ __forceinline__ unsigned level_of(float m, float cq) {
+  if (!(m >= 0.f)) return 0;
+  unsigned L = (unsigned)fminf(floorf(m / cq), 15.f);
+  while (L > 0 && (float)L * cq > m) --L;   // the quotient may have rounded up
+  return L;
+}
+
+__global__ void __launch_bounds__(PACK_THREADS)
+k_esdf_pack(const float* __restrict__ v, int nx, int ny, int nz, int shift, int cdx, int cdy,
+            int cdz, float cq, float4* __restrict__ rec, uint8_t* __restrict__ table) {
+  __shared__ int s_min[PACK_XB + 1];   // the row's blocks and the one after them
+  const int cx = nx - 1, cy = ny - 1, cz = nz - 1;
+  // this workgroup's blocks: bx in [bx0, bx1) of the row (by, bz)
+  const int by = blockIdx.y % cdy, bz = blockIdx.y / cdy;
+  const int bx0 = blockIdx.x * PACK_XB, bx1 = min(bx0 + PACK_XB, cdx);
+  const int x0 = bx0 << shift, xn = min(bx1 << shift, cx) - x0;
+  const int y0 = by << shift, yn = min((by + 1) << shift, cy) - y0;
+  const int z0 = bz << shift, z1 = min((bz + 1) << shift, cz);
+  for (int i = threadIdx.x; i < PACK_XB + 1; i += PACK_THREADS) s_min[i] = min_key(FLT_MAX);
+  __syncthreads();
+  const size_t row = nx, plane = (size_t)nx * ny;
+  for (int c = threadIdx.x; c < xn * yn; c += PACK_THREADS) {
+    const int yi = c / xn, x = x0 + (c - yi * xn), y = y0 + yi;
+    const float* p = v + x + row * y + plane * z0;
+    float a0 = p[0], a1 = p[1], a2 = p[row], a3 = p[row + 1];
+    float m = fminf(FLT_MAX, fminf(fminf(a0, a1), fminf(a2, a3)));   // drops NaN nodes
+    float4* r = rec + 2 * ((size_t)x + (size_t)cx * ((size_t)y + (size_t)cy * z0));
+    const size_t step = 2 * (size_t)cx * cy;
+    for (int z = z0; z < z1; z += PACK_Z) {
+      // PACK_Z planes' loads in flight together
+      float b[PACK_Z][4];
+#pragma unroll
+      for (int k = 0; k < PACK_Z; ++k) {
+        const float* q = p + plane * min(z + k + 1 - z0, z1 - z0);
+        b[k][0] = q[0]; b[k][1] = q[1]; b[k][2] = q[row]; b[k][3] = q[row + 1];
+      }
+#pragma unroll
+      for (int k = 0; k < PACK_Z; ++k, r += step) {
+        if (z + k < z1) {
+          r[0] = make_float4(a0, a1, a2, a3);
+          r[1] = make_float4(b[k][0], b[k][1], b[k][2], b[k][3]);
+        }
+        a0 = b[k][0]; a1 = b[k][1]; a2 = b[k][2]; a3 = b[k][3];
+        m = fminf(m, fminf(fminf(a0, a1), fminf(a2, a3)));
+      }
+    }
+    atomicMin(&s_min[(x - x0) >> shift], min_key(m));
+  }
+  // the odd block after this workgroup's last one, if that byte is its own
+  const int first = bx0 + cdx * (by + cdy * bz), last = first + (bx1 - bx0);
+  if ((last & 1) && last < cdx * cdy * cdz) {
+    const int ex = last % cdx, ey = (last / cdx) % cdy, ez = last / (cdx * cdy);
+    const int ex0 = ex << shift, ey0 = ey << shift, ez0 = ez << shift;
+    const int lx = min((ex + 1) << shift, cx) - ex0 + 1, ly = min((ey + 1) << shift, cy) - ey0 + 1,
+              lz = min((ez + 1) << shift, cz) - ez0 + 1;
+    float m = FLT_MAX;
+    for (int e = threadIdx.x; e < lx * ly * lz; e += PACK_THREADS) {
+      const int i = e % lx, j = (e / lx) % ly, k = e / (lx * ly);
+      m = fminf(m, v[(size_t)(ex0 + i) + row * (ey0 + j) + plane * (ez0 + k)]);
+    }
+    for (int off = 1; off < WAVE; off <<= 1) m = fminf(m, __shfl_xor(m, off));
+    if ((threadIdx.x & (WAVE - 1)) == 0) atomicMin(&s_min[last - first], min_key(m));
+  }
+  __syncthreads();
+  // bytes whose even block is one of this workgroup's
+  for (int b = (first + 1) / 2 + threadIdx.x; 2 * b < last; b += PACK_THREADS) {
+    const int e = 2 * b - first;
+    const unsigned lo = level_of(key_value(s_min[e]), cq);
+    const unsigned hi = 2 * b + 1 < cdx * cdy * cdz ? level_of(key_value(s_min[e + 1]), cq) : 0u;
+    table[b] = (uint8_t)(lo | (hi << 4));
+  }
+}
+
+// ---------------------------------------------- ESDF from an occupancy grid --
+// Exact squared Euclidean distance transform by separable passes (along x,
+// y and z), f'(p) = min over q on the line of f(q) + (p - q)^2 in voxels.
+// Every value is an integer below 2^24 (or the "none" sentinel), so float
+// arithmetic is exact.
+//
+// Both signs in one field: a free voxel needs the distance to the occupied
+// ones and an occupied voxel that to the free ones, and its other distance
+// is zero.  One signed float per voxel therefore holds both fields --
+// positive the squared distance of a free voxel, negative that of an
+// occupied one -- and max(+-f, 0) is either field.
+//
+// Along y and z a line is done by divide and conquer: the position q that
+// minimises f(q) + (p - q)^2 does not decrease with p, so once the
+// minimisers of every (4 S)-th position are known, the positions between
+// two of them need only the range between theirs.  Strides 64, 16, 4, 1 make
+// about 14 candidates per voxel for a line of 200, whatever the distances
+// are (a scan outward from p takes twice the distance, the whole line where
+// the line holds no obstacle).  The positions of one gap are scanned
+// together, so one LDS read serves three or four of them, and a block of
+// candidates whose smallest value cannot win is passed over: a wavefront
+// takes as long as its widest range, and wide ranges lie where the nearest
+// surface changes, with little between.
+//
+// Bound: VALU of the candidates (half of the issue slots; the rest is the
+// latency of one round of workgroups, five per CU).  200^3 shelf scene: bits
+// 6 us, x and y 54 us, z 48 us; before, with a field for each sign and a scan
+// outward from every voxel, six passes of 27 to 428 us (829 together) and
+// 50 us of kernels around them.
+constexpr float EDT_NONE = 1e20f;
+constexpr int EDT_X = 32;          // lines of a workgroup, side by side along x
+constexpr int EDT_THREADS = 256;
+constexpr int EDT_ROWS = EDT_THREADS / EDT_X;
+
+// Candidates per block: the block minima fit into LDS beside a line of 1024.
+__host__ __device__ inline int edt_block_shift(int n) { return n <= 512 ? 3 : 4; }
+
+// In LDS, element [i * EDT_X + column]: the candidates s[q], q < n; the
+// minimum of each block of 2^bs of them, signed like them (0 where the block
+// holds both kinds: a zero of either field); the minimisers of the positions
+// that are multiples of four.
+struct EdtLines {
+  float *s, *blk;
+  unsigned short* opt;
+  int n, bs, col;
+  __device__ __forceinline__ EdtLines(float* lds, int n_)
+      : s(lds), n(n_), bs(edt_block_shift(n_)), col((int)threadIdx.x % EDT_X) {
+    blk = s + n * EDT_X;
+    opt = reinterpret_cast<unsigned short*>(blk + (((n - 1) >> bs) + 1) * EDT_X);
+  }
+  __device__ __forceinline__ float at(int q) const { return s[q * EDT_X + col]; }
+};
+
+size_t edt_lds(int n) {
+  return (size_t)EDT_X * ((n + ((n - 1) >> edt_block_shift(n)) + 1) * sizeof(float) +
+                          (n + 3) / 4 * sizeof(unsigned short));
+}
+
+// N positions p0 + i step of one field (sg > 0: that of the free voxels):
+// the smallest sum of each so far and, with ARG, where.  With d = q - p0 a
+// sum is f(q) + d^2 - 2 i step d + (i step)^2; the last part is added at the
+// end, so a candidate costs a multiply-add and a minimum for each position.
+template <int N, bool ARG>
+struct EdtBest {
+  float p0, step, sg, best[N];
+  int arg[N];
+  __device__ __forceinline__ EdtBest(int p0_, int step_, float sg_)
+      : p0((float)p0_), step((float)step_), sg(sg_) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      best[i] = FLT_MAX;
+      arg[i] = 0;
+    }
+  }
+  __device__ __forceinline__ void take(const EdtLines& L, int q) {
+    const float d = (float)q - p0, c0 = fmaf(d, d, fmaxf(sg * L.at(q), 0.f));
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const float c = i ? fmaf(-2.f * i * step, d, c0) : c0;
+      if (ARG) arg[i] = c < best[i] ? q : arg[i];
+      best[i] = fminf(best[i], c);
+    }
+  }
+  __device__ __forceinline__ float sum(int i) const {
+    return fmaf(i * step, i * step, best[i]);
+  }
+  // The candidates of block b, unless its smallest value at its nearest
+  // place to the positions is no less than the largest sum so far.  All of
+  // them, eight reads in flight, also where only some were asked for: more
+  // candidates never change a minimum.
+  __device__ __forceinline__ void block(const EdtLines& L, int b) {
+    const float q0 = (float)(b << L.bs), q1 = q0 + (float)((1 << L.bs) - 1);
+    const float d = fmaxf(fmaxf(q0 - (p0 + (N - 1) * step), p0 - q1), 0.f);
+    float most = best[0];
+#pragma unroll
+    for (int i = 1; i < N; ++i) most = fmaxf(most, sum(i));
+    if (fmaf(d, d, fmaxf(sg * L.blk[b * EDT_X + L.col], 0.f)) >= most) return;
+    for (int q = b << L.bs; q < (b + 1) << L.bs; q += 8) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) take(L, min(q + k, L.n - 1));
+    }
+  }
+};
+
+// The N positions p0, p0 + step, ... (those before n): put(i, sum, minimiser)
+// of each in the field its own kind needs, over the candidates between the
+// minimisers of a and b (b past the end: the end of the line).  An a or b of
+// the other kind is a zero of that field, and so its own minimiser.
+template <int N, bool ARG, class Put>
+__device__ __forceinline__ void edt_gap(const EdtLines& L, int a, int b, int p0, int step,
+                                        Put put) {
+  const bool past = b >= L.n;
+  const int be = past ? L.n - 1 : b;
+  const bool fa = L.at(a) > 0.f, fb = past || L.at(be) > 0.f;
+  const int oa = L.opt[(a >> 2) * EDT_X + L.col];
+  const int ob = past ? be : L.opt[(be >> 2) * EDT_X + L.col];
+  bool fr[N], some = false, other = false;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int p = p0 + i * step;
+    fr[i] = L.at(min(p, L.n - 1)) > 0.f;
+    some |= p < L.n && fr[i];
+    other |= p < L.n && !fr[i];
+  }
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const bool field = t == 0;
+    if (!(field ? some : other)) continue;
+    const int lo = fa == field ? oa : a, hi = fb == field ? ob : be;
+    EdtBest<N, ARG> r(p0, step, field ? 1.f : -1.f);
+    r.take(L, lo);
+    r.take(L, hi);
+    if (lo + 1 < hi)
+      for (int k = (lo + 1) >> L.bs; k <= (hi - 1) >> L.bs; ++k) r.block(L, k);
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if (fr[i] == field && p0 + i * step < L.n) put(i, field ? r.sum(i) : -r.sum(i), r.arg[i]);
+  }
+}
+
+// All lines of the workgroup: put(p, signed minimum) for every position.
+// Every thread must call it, after s is filled.
+template <class Put>
+__device__ __forceinline__ void edt_lines(const EdtLines& L, Put put) {
+  const int n = L.n, g0 = threadIdx.x / EDT_X, nb = ((n - 1) >> L.bs) + 1;
+  __syncthreads();
+  for (int b = g0; b < nb; b += EDT_ROWS) {
+    const int q1 = min(n, (b + 1) << L.bs);
+    float mo = EDT_NONE, mf = EDT_NONE;   // minima of the two fields
+    for (int q = b << L.bs; q < q1; ++q) {
+      const float v = L.at(q);
+      mo = fminf(mo, fmaxf(v, 0.f));
+      mf = fminf(mf, fmaxf(-v, 0.f));
+    }
+    L.blk[b * EDT_X + L.col] = mo - mf;   // one of them is zero
+  }
+  __syncthreads();
+  // every 64th position: its block, then outward while a block is near enough
+  for (int p = g0 * 64; p < n; p += EDT_ROWS * 64) {
+    const float v = L.at(p);
+    EdtBest<1, true> r(p, 0, v > 0.f ? 1.f : -1.f);
+    r.best[0] = fabsf(v);
+    r.arg[0] = p;
+    const int b0 = p >> L.bs;
+    r.block(L, b0);
+    for (int k = 1; k < nb; ++k) {
+      const float d = (float)(((k - 1) << L.bs) + 1);   // the nearest voxel of block b0 +- k
+      if (d * d >= r.best[0]) break;
+      if (b0 - k >= 0) r.block(L, b0 - k);
+      if (b0 + k < nb) r.block(L, b0 + k);
+    }
+    L.opt[(p >> 2) * EDT_X + L.col] = (unsigned short)r.arg[0];
+  }
+  __syncthreads();
+  for (int S = 16; S >= 4; S >>= 2) {
+    for (int a = g0 * 4 * S; a + S < n; a += EDT_ROWS * 4 * S) {
+      edt_gap<3, true>(L, a, a + 4 * S, a + S, S, [&](int i, float, int arg) {
+        L.opt[((a + (i + 1) * S) >> 2) * EDT_X + L.col] = (unsigned short)arg;
+      });
+    }
+    __syncthreads();
+  }
+  for (int a = g0 * 4; a < n; a += EDT_ROWS * 4) {
+    edt_gap<4, false>(L, a, a + 4, a, 1, [&](int i, float f, int) { put(a + i, f); });
+  }
+}
+
+// Occupancy as bits: 2 * ceil(nx / 64) words of 32 voxels per row.  A lane
+// reads four voxels (rows start at any byte, so these are unaligned words;
+// only a row's last, partial one is read byte by byte) and eight lanes join
+// their four bits each to a word.  BITS_ROWS rows' loads are in flight
+// together: the kernel is a round or two of memory latency for the grid.
+constexpr int BITS_ROWS = 4;
+__global__ void __launch_bounds__(EDT_THREADS)
+k_edt_bits(const uint8_t* __restrict__ occ, int nx, int rows, unsigned* __restrict__ bits) {
+  const int lane = threadIdx.x & (WAVE - 1), words = 2 * ((nx + WAVE - 1) / WAVE);
+  const int r0 = (blockIdx.x * (EDT_THREADS / WAVE) +
+                  __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE))) * BITS_ROWS;
+  for (int x = 4 * lane; x < 32 * words; x += 4 * WAVE) {
+    unsigned v[BITS_ROWS];
+#pragma unroll
+    for (int r = 0; r < BITS_ROWS; ++r) {
+      v[r] = 0;
+      if (r0 + r >= rows) continue;
+      const uint8_t* p = occ + (size_t)(r0 + r) * nx + x;
+      if (x + 4 <= nx) {
+        __builtin_memcpy(&v[r], p, 4);
+      } else {
+        for (int k = 0; x + k < nx; ++k) v[r] |= (unsigned)p[k] << (8 * k);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < BITS_ROWS; ++r) {
+      unsigned b = 0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) b |= (v[r] >> (8 * k) & 255u) ? 1u << k : 0u;
+      b <<= 4 * (lane & 7);
+      b |= __shfl_xor(b, 1);
+      b |= __shfl_xor(b, 2);
+      b |= __shfl_xor(b, 4);
+      if ((lane & 7) == 0 && r0 + r < rows) bits[(size_t)(r0 + r) * words + x / 32] = b;
+    }
+  }
+}
+
+// Passes along x and y: one workgroup per tile of EDT_X columns of one z
+// plane.  The tile is one word of each row's bits, so the nearest opposite
+// voxel on the row is in that word or is one of four positions that the
+// whole row of the tile shares (the nearest occupied and free one before
+// and after it), found by one thread per row.
+__global__ void __launch_bounds__(EDT_THREADS)
+k_edt_xy(const unsigned* __restrict__ bits, int nx, int ny, float* __restrict__ out) {
+  extern __shared__ float s_line[];
+  const EdtLines L(s_line, ny);
+  const int x0 = blockIdx.x * EDT_X, w0 = blockIdx.x;
+  const int words = 2 * ((nx + WAVE - 1) / WAVE);
+  // the tile's word and the four positions of each row, where the block
+  // minima and minimisers will be (16 bytes a row: as many as the minimisers)
+  struct Row {
+    unsigned own;
+    short po, pf, no, nf;
+  };
+  Row* rows = reinterpret_cast<Row*>(L.blk);
+  for (int y = threadIdx.x; y < ny; y += EDT_THREADS) {
+    const unsigned* w = bits + ((size_t)blockIdx.y * ny + y) * words;
+    Row r = {w[w0], -2048, -2048, 4096, 4096};
+    for (int k = 0; k < w0; ++k) {
+      const unsigned o = w[k], f = ~o;
+      if (o) r.po = (short)(k * 32 + 31 - __builtin_clz(o));
+      if (f) r.pf = (short)(k * 32 + 31 - __builtin_clz(f));
+    }
+    for (int k = (nx - 1) / 32; k > w0; --k) {
+      const unsigned o = w[k], f = ~o & (0xFFFFFFFFu >> max(0, (k + 1) * 32 - nx));
+      if (o) r.no = (short)(k * 32 + __builtin_ctz(o));
+      if (f) r.nf = (short)(k * 32 + __builtin_ctz(f));
+    }
+    rows[y] = r;
+  }
+  __syncthreads();
+  const int x = x0 + L.col;
+  const unsigned valid = 0xFFFFFFFFu >> max(0, x0 + 32 - nx), below = (1u << L.col) - 1u;
+  for (int y = threadIdx.x / EDT_X; y < ny; y += EDT_ROWS) {
+    const Row r = rows[y];
+    const bool is_occ = (r.own >> L.col) & 1;
+    const unsigned opp = is_occ ? valid & ~r.own : r.own;
+    const unsigned lo = opp & below, hi = opp & ~below;
+    const int before = lo ? x0 + 31 - __builtin_clz(lo) : (is_occ ? r.pf : r.po);
+    const int after = hi ? x0 + __builtin_ctz(hi) : (is_occ ? r.nf : r.no);
+    const int d = min(x - before, after - x);
+    // (columns past the row's end get a value that is not used)
+    const float v = d < 1024 ? (float)(d * d) : EDT_NONE;
+    L.s[y * EDT_X + L.col] = is_occ ? -v : v;
+  }
+  float* o = out + ((size_t)blockIdx.y * ny) * nx + x;
+  edt_lines(L, [&](int p, float f) {
+    if (x < nx) o[(size_t)p * nx] = f;
+  });
+}
+
+// Pass along z over EDT_X neighbouring lines, and the distance itself: the
+// root of the squared distance in metres, negative inside.
+__global__ void __launch_bounds__(EDT_THREADS)
+k_edt_z(const float* __restrict__ f, long long plane, int nz, float voxel,
+        float* __restrict__ dist) {
+  extern __shared__ float s_line[];
+  const EdtLines L(s_line, nz);
+  const long long l = (long long)blockIdx.x * EDT_X + L.col;
+  const bool in = l < plane;
+  for (int z = threadIdx.x / EDT_X; z < nz; z += EDT_ROWS)
+    L.s[z * EDT_X + L.col] = in ? f[l + z * plane] : 1.f;
+  edt_lines(L, [&](int p, float s) {
+    if (in) dist[l + p * plane] = s < 0.f ? -voxel * sqrtf(-s) : voxel * sqrtf(s);
+  });
+}
+
+}  // namespace
+
+hipError_t launch_esdf_pack(const float* vals, int nx, int ny, int nz, int shift, int cdx,
+                            int cdy, int cdz, float cq, float4* rec, uint8_t* table,
+                            hipStream_t s) {
+  hipLaunchKernelGGL(k_esdf_pack, dim3((cdx + PACK_XB - 1) / PACK_XB, cdy * cdz),
+                     dim3(PACK_THREADS), 0, s, vals, nx, ny, nz, shift, cdx, cdy, cdz, cq, rec,
+                     table);
+  return hipGetLastError();
+}
+
+size_t edt_bits_bytes(int nx, int ny, int nz) {
+  return (size_t)((nx + WAVE - 1) / WAVE) * ny * nz * sizeof(unsigned long long);
+}
+
+hipError_t launch_esdf_from_occupancy(const uint8_t* occ, int nx, int ny, int nz, float voxel,
+                                      unsigned long long* bits, float* work, float* dist,
+                                      hipStream_t s) {
+  const long long plane = (long long)nx * ny;
+  const int per = EDT_THREADS / WAVE * BITS_ROWS;
+  hipLaunchKernelGGL(k_edt_bits, dim3((ny * nz + per - 1) / per), dim3(EDT_THREADS), 0, s, occ, nx,
+                     ny * nz, reinterpret_cast<unsigned*>(bits));
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_edt_xy, dim3((nx + EDT_X - 1) / EDT_X, nz), dim3(EDT_THREADS),
+                     edt_lds(ny), s, reinterpret_cast<const unsigned*>(bits), nx, ny, work);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_edt_z, dim3((unsigned)((plane + EDT_X - 1) / EDT_X)), dim3(EDT_THREADS),
+                     edt_lds(nz), s, work, plane, nz, voxel, dist);
+  return hipGetLastError();
+}
+
+}  // namespace dsk
