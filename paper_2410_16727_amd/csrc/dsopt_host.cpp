@@ -708,16 +708,12 @@ static int cost_common(ds_plan* p, const ds_problem* prob, const float* X, int S
   if (int rc = validate_problem(p, *prob, false)) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
   poll_deferred(p, false);
-  size_t off = arena_alloc(p, sizeof(ProbDev));
-  if (off == SIZE_MAX) return fail(DS_ERR_NOMEM, "arena full");
   ProbDev pd = make_probdev(p, *prob);
   pd.S = S;
   pd.T = T;
-  ProbDev* dev = reinterpret_cast<ProbDev*>(p->arena.ptr(off));
-  if (int rc = upload(p, dev, &pd, sizeof pd, s)) return rc;
-  HIP_TRY(launch_cost(p->robot_dev, p->params_dev, dev, X, S, T, dJ, J_out, dX, with_grad,
+  HIP_TRY(launch_cost(p->robot_dev, p->params_dev, pd, X, S, T, dJ, J_out, dX, with_grad,
                       params_ext(p->params), p->cu_count, s));
-  return defer_free(p, off, s);
+  return DS_OK;
 }
 
 int ds_cost(ds_plan* p, const ds_problem* prob, const float* X, int S, int T, float* J_out,
@@ -738,16 +734,12 @@ int ds_guide(ds_plan* p, const ds_problem* prob, float* X, int S, int T, float a
   if (int rc = validate_problem(p, *prob, false)) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
   poll_deferred(p, false);
-  size_t off = arena_alloc(p, sizeof(ProbDev));
-  if (off == SIZE_MAX) return fail(DS_ERR_NOMEM, "arena full");
   ProbDev pd = make_probdev(p, *prob);
   pd.S = S;
   pd.T = T;
-  ProbDev* dev = reinterpret_cast<ProbDev*>(p->arena.ptr(off));
-  if (int rc = upload(p, dev, &pd, sizeof pd, s)) return rc;
-  HIP_TRY(launch_guide(p->robot_dev, p->params_dev, dev, X, S, T, alpha, n_steps, J_out,
+  HIP_TRY(launch_guide(p->robot_dev, p->params_dev, pd, X, S, T, alpha, n_steps, J_out,
                        params_ext(p->params), p->cu_count, s));
-  return defer_free(p, off, s);
+  return DS_OK;
 }
 
 int ds_kernel_timing(ds_plan* p, int enable) {

@@ -1874,32 +1874,41 @@ __device__ __forceinline__ int seed_of(int W, float* team_lds, Team& tm) {
   return (blockIdx.x * BLOCK + threadIdx.x) / WAVE;
 }
 
+// Waypoint t of a trajectory (zeros past the horizon or the last seed).
+// Called ahead of the staging, so its memory round trip overlaps theirs.
+__device__ __forceinline__ void load_waypoint(const float* __restrict__ X, int seed, int S, int T,
+                                              int t, float* x) {
+  const bool in = seed < S && t < T;
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) x[j] = in ? X[((size_t)seed * T + t) * NJ + j] : 0.f;
+}
+
+// The problem is a kernel argument of k_cost and k_guide: a table in device
+// memory costs a copy ahead of the kernel and an event behind it.
 // Objective (and gradient) of arbitrary trajectories: one wavefront (or a
 // team) per seed group of G lanes (G = smallest of 16/32/64 holding T).
 template <bool EXT>
 __global__ void __launch_bounds__(MAX_TEAM * WAVE)
-k_cost(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp,
-       const ProbDev* __restrict__ pb, const float* __restrict__ X, int S, int T, int G,
-       const float* __restrict__ dJ, float* __restrict__ J_out, float* __restrict__ dX,
-       int with_grad, int W) {
+k_cost(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp, const ProbDev pb,
+       const float* __restrict__ X, int S, int T, int G, const float* __restrict__ dJ,
+       float* __restrict__ J_out, float* __restrict__ dX, int with_grad, int W) {
   extern __shared__ float s_team[];
   __shared__ __attribute__((aligned(16))) uint8_t s_cm[COARSE_BYTES];
-  if (pp->skip) stage_coarse(pb->sc, lds(s_cm), threadIdx.x, blockDim.x);
-  stage_spheres(rb);
   const int lane = threadIdx.x & (WAVE - 1);
   Team tm;
   const int seed = seed_of(W, s_team, tm);
-  if (seed >= S) return;   // whole wavefront (team: whole workgroup) past the end
   const int t = lane & (G - 1);
   const bool owner = tm.w == 0 && lane < G;
   const bool active = t < T;
-  ParamsDev P = *pp;
-  Sampler Sm = make_sampler(pb->sc);
-  Sm.cm = lds(s_cm);
-  Goal goal = make_goal(*pb);
   float x[NJ];
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) x[j] = active ? X[((size_t)seed * T + t) * NJ + j] : 0.f;
+  load_waypoint(X, seed, S, T, t, x);
+  if (pp->skip) stage_coarse(pb.sc, lds(s_cm), threadIdx.x, blockDim.x);
+  stage_spheres(rb);
+  if (seed >= S) return;   // whole wavefront (team: whole workgroup) past the end
+  ParamsDev P = *pp;
+  Sampler Sm = make_sampler(pb.sc);
+  Sm.cm = lds(s_cm);
+  Goal goal = make_goal(pb);
   float J;
   if (with_grad) {
     EvalOut e = eval_any<EV_GRAD, EXT>(use_pipe(rb, tm, G), rb, P, Sm, goal, x, t, T, G, active, tm);
@@ -1920,28 +1929,27 @@ k_cost(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp,
 // wavefront (or a team) per seed (same evaluation as the optimiser).
 template <bool EXT>
 __global__ void __launch_bounds__(MAX_TEAM * WAVE)
-k_guide(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp,
-        const ProbDev* __restrict__ pb, float* __restrict__ X, int S, int T, int G, float alpha,
-        int n_steps, float* __restrict__ J_out, int W) {
+k_guide(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp, const ProbDev pb,
+        float* __restrict__ X, int S, int T, int G, float alpha, int n_steps,
+        float* __restrict__ J_out, int W) {
   extern __shared__ float s_team[];
   __shared__ __attribute__((aligned(16))) uint8_t s_cm[COARSE_BYTES];
-  if (pp->skip) stage_coarse(pb->sc, lds(s_cm), threadIdx.x, blockDim.x);
-  stage_spheres(rb);
   const int lane = threadIdx.x & (WAVE - 1);
   Team tm;
   const int seed = seed_of(W, s_team, tm);
-  if (seed >= S) return;   // whole wavefront (team: whole workgroup) past the end
   const int t = lane & (G - 1);
   const bool owner = tm.w == 0 && lane < G;
   const bool active = t < T;
-  ParamsDev P = *pp;
-  Sampler Sm = make_sampler(pb->sc);
-  Sm.cm = lds(s_cm);
-  Goal goal = make_goal(*pb);
-  const bool pipe = use_pipe(rb, tm, G);
   float x[NJ];
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) x[j] = active ? X[((size_t)seed * T + t) * NJ + j] : 0.f;
+  load_waypoint(X, seed, S, T, t, x);
+  if (pp->skip) stage_coarse(pb.sc, lds(s_cm), threadIdx.x, blockDim.x);
+  stage_spheres(rb);
+  if (seed >= S) return;   // whole wavefront (team: whole workgroup) past the end
+  ParamsDev P = *pp;
+  Sampler Sm = make_sampler(pb.sc);
+  Sm.cm = lds(s_cm);
+  Goal goal = make_goal(pb);
+  const bool pipe = use_pipe(rb, tm, G);
   for (int k = 0; k < n_steps; ++k) {
     EvalOut e = eval_any<EV_GRAD, EXT>(pipe, rb, P, Sm, goal, x, t, T, G, active, tm);
 #pragma unroll
@@ -2080,7 +2088,7 @@ static int cost_team(int S, int cu_count) {
   return W;
 }
 
-hipError_t launch_cost(const RobotDev* rb, const ParamsDev* pp, const ProbDev* prob,
+hipError_t launch_cost(const RobotDev* rb, const ParamsDev* pp, const ProbDev& prob,
                        const float* X, int S, int T, const float* dJ, float* J_out, float* dX,
                        int with_grad, bool ext, int cu_count, hipStream_t s) {
   const int G = T <= 16 ? 16 : (T <= 32 ? 32 : 64);
@@ -2092,7 +2100,7 @@ hipError_t launch_cost(const RobotDev* rb, const ParamsDev* pp, const ProbDev* p
   return hipGetLastError();
 }
 
-hipError_t launch_guide(const RobotDev* rb, const ParamsDev* pp, const ProbDev* prob, float* X,
+hipError_t launch_guide(const RobotDev* rb, const ParamsDev* pp, const ProbDev& prob, float* X,
                         int S, int T, float alpha, int n_steps, float* J_out, bool ext,
                         int cu_count, hipStream_t s) {
   const int G = T <= 16 ? 16 : (T <= 32 ? 32 : 64);
