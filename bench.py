@@ -49,7 +49,9 @@ def ops_per_eval(n_spheres, grad):
     return 2 * fwd + 30 * n_spheres if grad else fwd
 
 
-KERNEL_SOURCES = ["paper_2410_16727_amd/csrc/dsopt_kernels.hip",
+KERNEL_SOURCES = ["paper_2410_16727_amd/csrc/dsopt_eval.h",
+                  "paper_2410_16727_amd/csrc/dsopt_optimize.h",
+                  "paper_2410_16727_amd/csrc/dsopt_kernels.hip",
                   "paper_2410_16727_amd/csrc/dsopt_internal.h"]
 PMC_SUMMARY = "profiles/k_optimize_pmc_batched.json"
 COPY_BYTES = 256 << 20

@@ -1,0 +1,976 @@
+// Device code of the objective: one evaluation of a trajectory by a wavefront
+// or a team (included by the translation units with kernels that evaluate).
+//
+// Mapping: one wavefront (or a team of W wavefronts) owns one tile = one
+// seed of one problem; lane t of each lane group holds waypoint t (group
+// size G = 64, 32 or 16 >= T) and the 64 / G groups of a wavefront are
+// copies of the seed that split its spheres.  Per lane the kernel runs the whole per-waypoint chain of the
+// objective (App. A.6): forward kinematics (sincos + 3x4 compositions with
+// the robot table read through the scalar cache), sphere centres, an ESDF
+// gather of one 32-byte corner record per sphere (two 16-byte buffer
+// loads), the smooth hinge, and -- for the gradient -- the joint-axis
+// adjoint: sphere forces f = w_c phi'(D) grad d accumulated per link into
+// a wrench and projected on every preceding joint twist, recomputing the
+// kinematics instead of storing transforms.  Finite differences of the
+// trajectory (smoothness) move between lanes with cross-lane shuffles;
+// per-seed sums (cost, L-BFGS dot products, Armijo tests) are butterfly
+// reductions inside the lane group, so every lane ends with bitwise the same
+// value and the reduction order depends only on G.  Nothing here is a dense
+// contraction: no MFMA.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cfloat>
+#include <cmath>
+#include <type_traits>
+
+#include "dsopt_internal.h"
+
+namespace dsk {
+namespace {
+
+constexpr unsigned RSRC_DWORD3 = 0x00020000u;   // raw buffer, gfx9 family
+
+// Pointers read from tables are generic to the compiler; these casts state
+// that they address global memory, so accesses use global (not flat)
+// instructions.
+#define DS_GLOBAL __attribute__((address_space(1)))
+template <class T>
+__device__ __forceinline__ DS_GLOBAL T* glb(T* p) {
+  return (DS_GLOBAL T*)p;
+}
+template <class T>
+__device__ __forceinline__ const DS_GLOBAL T* glb(const T* p) {
+  return (const DS_GLOBAL T*)p;
+}
+// ... and that a pointer into a __shared__ array addresses LDS (ds_read /
+// ds_write rather than flat accesses).
+#define DS_LDS __attribute__((address_space(3)))
+template <class T>
+__device__ __forceinline__ DS_LDS T* lds(T* p) {
+  return (DS_LDS T*)p;
+}
+#ifndef DSOPT_CH
+#define DSOPT_CH 4
+#endif
+constexpr int CH = DSOPT_CH;                     // sphere gathers in flight per lane
+// s_waitcnt operand: vector memory count 0, the export and LDS/scalar
+// counts at their maxima (not waited on)
+constexpr int WAIT_VMEM_ALL = 0x0F70;
+
+// Butterfly reductions over a lane group of G = 16, 32 or 64 lanes.  The
+// first four stages pair lanes inside a 16-lane row with DPP (quad
+// permutations 1<->0 / 2<->0, then the half-row and row mirrors), the
+// remaining ones exchange rows (lane ^ 16) and halves (lane ^ 32) with the
+// permlane swaps -- VALU instructions, no LDS round trip.  Every pairing is
+// an involution, so both partners add the same two numbers and every lane of
+// the group ends with bitwise the same result.
+constexpr int DPP_QUAD_XOR1 = 0xB1;   // quad_perm [1,0,3,2]
+constexpr int DPP_QUAD_XOR2 = 0x4E;   // quad_perm [2,3,0,1]
+constexpr int DPP_HALF_MIRROR = 0x141;
+constexpr int DPP_MIRROR = 0x140;
+
+constexpr int DPP_WAVE_SHL1 = 0x130;   // lane i reads lane i + 1
+constexpr int DPP_WAVE_SHR1 = 0x138;   // lane i reads lane i - 1
+
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+
+// The value of lane i + 1 / lane i - 1 (one DPP move; the lane past either
+// end of the wavefront reads 0).  Callers only use lanes whose neighbour is
+// in the same lane group.
+__device__ __forceinline__ float from_next(float v) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(0, __float_as_int(v), DPP_WAVE_SHL1, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float from_prev(float v) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(0, __float_as_int(v), DPP_WAVE_SHR1, 0xF, 0xF, true));
+}
+
+struct OpSum { __device__ static float f(float a, float b) { return a + b; } };
+struct OpMax { __device__ static float f(float a, float b) { return fmaxf(a, b); } };
+struct OpMin { __device__ static float f(float a, float b) { return fminf(a, b); } };
+
+// v combined with lane ^ 16's v (v_permlane16_swap with v as both operands
+// exchanges the odd rows of the first with the even rows of the second: in
+// every lane one result is its own value and the other its partner's) and
+// with lane ^ 32's (v_permlane32_swap: the upper half of the first operand
+// with the lower half of the second).  The operations are commutative, so
+// combining the two results needs no per-lane select.
+template <class Op>
+__device__ __forceinline__ float xor16_reduce(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), true,
+                                                  false);
+  return Op::f(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+template <class Op>
+__device__ __forceinline__ float xor32_reduce(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), true,
+                                                  false);
+  return Op::f(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+template <class Op>
+__device__ __forceinline__ float xor_reduce(float v, int off) {
+  return off == 16 ? xor16_reduce<Op>(v) : xor32_reduce<Op>(v);
+}
+
+template <class Op>
+__device__ __forceinline__ float grp_reduce(float v, int G) {
+  v = Op::f(v, dpp<DPP_QUAD_XOR1>(v));
+  v = Op::f(v, dpp<DPP_QUAD_XOR2>(v));
+  v = Op::f(v, dpp<DPP_HALF_MIRROR>(v));
+  v = Op::f(v, dpp<DPP_MIRROR>(v));
+  if (G > 16) v = xor16_reduce<Op>(v);
+  if (G > 32) v = xor32_reduce<Op>(v);
+  return v;
+}
+
+__device__ __forceinline__ float grp_sum(float v, int G) { return grp_reduce<OpSum>(v, G); }
+__device__ __forceinline__ float grp_max(float v, int G) { return grp_reduce<OpMax>(v, G); }
+__device__ __forceinline__ float grp_min(float v, int G) { return grp_reduce<OpMin>(v, G); }
+__device__ __forceinline__ float dot7(const float* a, const float* b) {
+  float s = a[0] * b[0];
+#pragma unroll
+  for (int j = 1; j < NJ; ++j) s += a[j] * b[j];
+  return s;
+}
+
+struct Goal {
+  float pd[3];
+  float Rd[9];
+};
+
+// Unit goal quaternion (w, x, y, z) -> rotation matrix (uniform per tile).
+__device__ __forceinline__ Goal make_goal(const ProbDev& pb) {
+  Goal g;
+  float w = pb.quat[0], x = pb.quat[1], y = pb.quat[2], z = pb.quat[3];
+  float n = sqrtf(w * w + x * x + y * y + z * z);
+  w /= n; x /= n; y /= n; z /= n;
+  g.Rd[0] = 1.f - 2.f * (y * y + z * z); g.Rd[1] = 2.f * (x * y - w * z); g.Rd[2] = 2.f * (x * z + w * y);
+  g.Rd[3] = 2.f * (x * y + w * z); g.Rd[4] = 1.f - 2.f * (x * x + z * z); g.Rd[5] = 2.f * (y * z - w * x);
+  g.Rd[6] = 2.f * (x * z - w * y); g.Rd[7] = 2.f * (y * z + w * x); g.Rd[8] = 1.f - 2.f * (x * x + y * y);
+  g.pd[0] = pb.pd[0]; g.pd[1] = pb.pd[1]; g.pd[2] = pb.pd[2];
+  return g;
+}
+
+struct Sampler {
+  __amdgpu_buffer_rsrc_t rsrc;
+  float ox, oy, oz, inv_h, h, nxm1, nym1, nzm1;
+  float fxm2, fym2, fzm2;          // last cell index per axis, as floats
+  int nxm2, nym2, nzm2, cx, cy;    // cells along x and y
+  const DS_LDS uint8_t* cm;        // the scene's coarse table (4-bit levels), staged in LDS
+  float cq;                        // distance of one level
+  int cshift, cdx, cdy;
+};
+
+__device__ __forceinline__ Sampler make_sampler(const SceneDev& sc) {
+  Sampler s;
+  s.rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)sc.rec, (short)0, (int)sc.bytes, RSRC_DWORD3);
+  s.ox = sc.ox; s.oy = sc.oy; s.oz = sc.oz; s.inv_h = sc.inv_h; s.h = 1.f / sc.inv_h;
+  s.nxm1 = (float)(sc.nx - 1); s.nym1 = (float)(sc.ny - 1); s.nzm1 = (float)(sc.nz - 1);
+  s.nxm2 = sc.nx - 2; s.nym2 = sc.ny - 2; s.nzm2 = sc.nz - 2;
+  s.fxm2 = (float)s.nxm2; s.fym2 = (float)s.nym2; s.fzm2 = (float)s.nzm2;
+  s.cx = sc.nx - 1;
+  s.cy = sc.ny - 1;
+  s.cm = nullptr;
+  s.cq = sc.cq;
+  s.cshift = sc.cshift;
+  s.cdx = sc.cdx;
+  s.cdy = sc.cdy;
+  return s;
+}
+
+// Copy the scene's coarse table into LDS (threads tid = 0..nth-1 of the
+// group that shares it; the caller synchronises them afterwards) in
+// 16-byte pieces, STAGE_UNROLL loads in flight per thread before their LDS
+// stores (one load at a time made every piece a memory round trip).  The
+// table's allocation and both ends are 16-byte aligned.
+constexpr int STAGE_UNROLL = 4;
+__device__ __forceinline__ void stage_coarse(const SceneDev& sc, DS_LDS uint8_t* dst, int tid,
+                                             int nth) {
+  const int n = (sc.cdx * sc.cdy * sc.cdz + 31) / 32;   // 32 levels per piece
+  const DS_GLOBAL uint32_t* src = glb(reinterpret_cast<const uint32_t*>(sc.coarse));
+  DS_LDS uint32_t* d = (DS_LDS uint32_t*)dst;
+  for (int i0 = tid; i0 < n; i0 += STAGE_UNROLL * nth) {
+    uint32_t v[STAGE_UNROLL][4];
+#pragma unroll
+    for (int u = 0; u < STAGE_UNROLL; ++u) {
+      const int i = i0 + u * nth;
+      if (i < n) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[u][q] = src[4 * i + q];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < STAGE_UNROLL; ++u) {
+      const int i = i0 + u * nth;
+      if (i < n) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) d[4 * i + q] = v[u][q];
+      }
+    }
+  }
+}
+
+// A coarse-table entry as a distance: level * cq, at most the block's
+// minimum node distance.
+__device__ __forceinline__ float coarse_at(const Sampler& S, int idx) {
+  const unsigned b = S.cm[idx >> 1];
+  return (float)((b >> ((idx & 1) << 2)) & 15u) * S.cq;
+}
+
+// A sample's place in the grid.  u = (c - origin) / voxel is the sphere
+// centre c in grid units; the sample's cell is trunc(clamp(u, 0, n-2)) per
+// axis (the cell whose corners bracket the clamped point), its fractional
+// position clamp(u, 0, n-1) - cell, and the gradient is zero along axes
+// where u was clamped.
+//
+// A link frame (R, p) maps a sphere offset o to c = p + R o.  For a link
+// whose spheres all lie on its z axis (o = (0, 0, oz)) the link's part is
+// formed once -- u = u0 + oz az with u0 = (p - origin) / voxel and
+// az = R e_z / voxel -- so a sphere costs one FMA per axis.
+struct LinkGrid {
+  float u0[3], az[3];
+};
+
+__device__ __forceinline__ LinkGrid link_grid(const Sampler& S, const float* R, const float* p) {
+  LinkGrid g;
+  g.u0[0] = (p[0] - S.ox) * S.inv_h;
+  g.u0[1] = (p[1] - S.oy) * S.inv_h;
+  g.u0[2] = (p[2] - S.oz) * S.inv_h;
+  g.az[0] = R[2] * S.inv_h;
+  g.az[1] = R[5] * S.inv_h;
+  g.az[2] = R[8] * S.inv_h;
+  return g;
+}
+
+// Grid position of the sphere with offset/radius sp on the link (R, p);
+// `axis` (wave-uniform) says the link's spheres sit on its z axis.
+__device__ __forceinline__ void grid_pos(const Sampler& S, const LinkGrid& g, bool axis,
+                                         const float* R, const float* p, float4 sp, float* u) {
+  if (axis) {
+#pragma unroll
+    for (int r = 0; r < 3; ++r) u[r] = fmaf(sp.z, g.az[r], g.u0[r]);
+  } else {
+    const float cx = R[0] * sp.x + R[1] * sp.y + R[2] * sp.z + p[0];
+    const float cy = R[3] * sp.x + R[4] * sp.y + R[5] * sp.z + p[1];
+    const float cz = R[6] * sp.x + R[7] * sp.y + R[8] * sp.z + p[2];
+    u[0] = (cx - S.ox) * S.inv_h;
+    u[1] = (cy - S.oy) * S.inv_h;
+    u[2] = (cz - S.oz) * S.inv_h;
+  }
+}
+
+// The sample's cell: trunc(clamp(u, 0, n-2)) per axis (for u >= 0,
+// min(trunc(min(u, n-1)), n-2) == trunc(min(u, n-2)): one v_med3 and one
+// conversion per axis).
+__device__ __forceinline__ void cell_of(const Sampler& S, const float* u, int* i) {
+  i[0] = (int)__builtin_amdgcn_fmed3f(u[0], 0.f, S.fxm2);
+  i[1] = (int)__builtin_amdgcn_fmed3f(u[1], 0.f, S.fym2);
+  i[2] = (int)__builtin_amdgcn_fmed3f(u[2], 0.f, S.fzm2);
+}
+
+// The cell's block in the coarse table and its record's byte offset.
+// Every product fits 24 bits: the upload keeps (ny-1)(nz-1) below 2^24,
+// and the coarse table has at most COARSE_MAX blocks (stating the bounds
+// keeps both products 24-bit multiply-adds).
+__device__ __forceinline__ int block_index(const Sampler& S, const int* i) {
+  const unsigned crow =
+      __umul24((unsigned)S.cdy, (unsigned)(i[2] >> S.cshift)) + (unsigned)(i[1] >> S.cshift);
+  __builtin_assume(crow < (1u << 24));
+  return (int)(__umul24((unsigned)S.cdx, crow) + (unsigned)(i[0] >> S.cshift));
+}
+
+__device__ __forceinline__ int record_offset(const Sampler& S, const int* i) {
+  const unsigned row = __umul24((unsigned)S.cy, (unsigned)i[2]) + (unsigned)i[1];
+  __builtin_assume(row < (1u << 24));
+  return (int)((__umul24((unsigned)S.cx, row) + (unsigned)i[0]) << 5);
+}
+
+// Trilinear blend of a cell record (a: z0 corners, b: z1 corners) at the
+// fractional position (fx, fy, fz): the value, and the differences its
+// spatial gradient is formed from.
+struct Blend {
+  float d;                          // interpolated distance
+  float dx00, dx10, dx01, dx11;     // x differences of the four x edges
+  float dy0, dy1, dz;               // y differences at z0/z1, z difference
+};
+
+__device__ __forceinline__ Blend blend_value(float fx, float fy, float fz, float4 a, float4 b) {
+  Blend r;
+  r.dx00 = a.y - a.x; r.dx10 = a.w - a.z; r.dx01 = b.y - b.x; r.dx11 = b.w - b.z;
+  float c00 = a.x + fx * r.dx00;
+  float c10 = a.z + fx * r.dx10;
+  float c01 = b.x + fx * r.dx01;
+  float c11 = b.z + fx * r.dx11;
+  r.dy0 = c10 - c00;
+  r.dy1 = c11 - c01;
+  float c0 = c00 + fy * r.dy0;
+  float c1 = c01 + fy * r.dy1;
+  r.dz = c1 - c0;
+  r.d = c0 + fz * r.dz;
+  return r;
+}
+
+// Its spatial gradient in grid units (times 1/voxel by the caller).
+__device__ __forceinline__ void blend_grad(float fy, float fz, const Blend& r, float& gx,
+                                           float& gy, float& gz) {
+  float e0 = r.dx00 + fy * (r.dx10 - r.dx00);
+  float e1 = r.dx01 + fy * (r.dx11 - r.dx01);
+  gx = e0 + fz * (e1 - e0);
+  gy = r.dy0 + fz * (r.dy1 - r.dy0);
+  gz = r.dz;
+}
+
+__device__ __forceinline__ float4 load_rec(const Sampler& S, int off) {
+  auto v = __builtin_amdgcn_raw_buffer_load_b128(S.rsrc, off, 0, 0);
+  return *reinterpret_cast<float4*>(&v);
+}
+
+enum { EV_COST = 0, EV_GRAD = 1, EV_RESULT = 2 };
+
+// The robot's sphere table (offset, radius; sorted by link) staged in LDS
+// by every kernel that evaluates the objective: the sphere a lane takes
+// depends on its copy index, so the reads are per-lane and would otherwise
+// be vector memory round trips ahead of every record gather.
+__shared__ float4 s_sph[DS_MAX_SPHERES];
+
+// Fill s_sph; every thread of the workgroup must call it.
+__device__ __forceinline__ void stage_spheres(const RobotDev* __restrict__ rb) {
+  for (int i = threadIdx.x; i < rb->ns; i += blockDim.x) s_sph[i] = rb->sph[i];
+  __syncthreads();
+}
+
+// Joint twists (axis z_i, origin o_i) of the swept joints, kept for the
+// wrench projections of the adjoint.
+struct Twists {
+  float z[NJ][3], o[NJ][3];
+  __device__ __forceinline__ void put(int i, const float* R, const float* p) {
+    z[i][0] = R[2]; z[i][1] = R[5]; z[i][2] = R[8];
+    o[i][0] = p[0]; o[i][1] = p[1]; o[i][2] = p[2];
+  }
+  __device__ __forceinline__ void get(int i, float* zi, float* oi) const {
+    zi[0] = z[i][0]; zi[1] = z[i][1]; zi[2] = z[i][2];
+    oi[0] = o[i][0]; oi[1] = o[i][1]; oi[2] = o[i][2];
+  }
+};
+
+struct EvalOut {
+  float cost;        // this lane's share of the seed objective (0 when inactive)
+  float g[NJ];       // gradient row (EV_GRAD; zero at t = 0 and inactive lanes)
+  float clr;         // min (distance - radius) at this waypoint (EV_RESULT)
+  float perr, rerr;  // goal errors at this lane's waypoint (EV_RESULT)
+  int ng;            // cell records this lane gathered
+};
+
+// Smoothness on the lane group: v_t = q_{t+1} - q_t (t <= T-2),
+// a_t = v_t - v_{t-1} (t < T), j_t = a_{t+1} - a_t (t < T) plus
+// j_{-1} = a_0 at t = 0 -- the first/second/third differences of the
+// sequence padded with two copies of q_0 and of q_{T-1}.  The gradient
+// applies the transposed stencils with the same lane shifts (DPP moves; the
+// masks keep every read inside the lane group).
+template <bool GRAD>
+__device__ __forceinline__ float smoothness(const ParamsDev& P, const float* q, int t, int T,
+                                            float* g) {
+  float c = 0.f;
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    float qn = from_next(q[j]);
+    float v = (t <= T - 2) ? qn - q[j] : 0.f;
+    float vp = from_prev(v);
+    float a = (t < T) ? v - (t >= 1 ? vp : 0.f) : 0.f;
+    float an = from_next(a);
+    float jk = (t < T) ? ((t + 1 < T ? an : 0.f) - a) : 0.f;
+    float jm = (t == 0) ? a : 0.f;   // j_{-1}
+    c += P.lv * (v * v) + P.la * (a * a) + P.lj * (jk * jk) + P.lj * (jm * jm);
+    if (GRAD) {
+      float jb = 2.f * P.lj * jk;
+      float jbp = from_prev(jb);
+      float ab = (t < T) ? 2.f * P.la * a + ((t == 0) ? 2.f * P.lj * jm : jbp) - jb : 0.f;
+      float abn = from_next(ab);
+      float vb = (t <= T - 2) ? 2.f * P.lv * v + ab - abn : 0.f;
+      float vbp = from_prev(vb);
+      g[j] += ((t >= 1) ? vbp : 0.f) - vb;
+    }
+  }
+  return c;
+}
+
+// A team of W wavefronts (one workgroup) optimises one seed: every
+// wavefront holds the whole trajectory (one waypoint per lane group) and
+// takes every (W*L)-th sphere of each link; the partial sums meet in
+// double-buffered LDS with one barrier per evaluation.  W = 1: independent
+// wavefronts, no barrier.
+constexpr int MAX_TEAM = 8;
+constexpr int PART = NJ + 2;   // partial sums per lane: hinge sum, gradient row, clearance
+
+struct Team {
+  int W, w;       // team size, this wavefront's index
+  float* lds;     // [2][W][PART][64]
+  int buf;
+  __device__ __forceinline__ void sync() const {
+    if (W > 1) __syncthreads();
+  }
+};
+
+// Hinge cost of one sphere sample (grid position u, cell ci, cell record
+// ra/rz, radius r) and, with GRAD, its force accumulated into the link
+// wrench (F, M about the world origin).  Returns whether the force terms
+// ran (some lane of the wavefront inside the hinge band).
+template <int MODE>
+__device__ __forceinline__ bool sphere_term(const ParamsDev& P, const Sampler& S, const float* u,
+                                            const int* ci, float4 ra, float4 rz, float r,
+                                            float& phisum, float& clr, float* FM) {
+  constexpr bool GRAD = (MODE == EV_GRAD);
+  const float cx = __builtin_amdgcn_fmed3f(u[0], 0.f, S.nxm1);
+  const float cy = __builtin_amdgcn_fmed3f(u[1], 0.f, S.nym1);
+  const float cz = __builtin_amdgcn_fmed3f(u[2], 0.f, S.nzm1);
+  const float fy = cy - (float)ci[1], fz = cz - (float)ci[2];
+  const Blend bl = blend_value(cx - (float)ci[0], fy, fz, ra, rz);
+  float D = bl.d - r;
+  float De = D - P.eps;
+  float phi = (D < P.eps) ? De * De * P.half_inv_eps : 0.f;
+  phi = (D < 0.f) ? 0.5f * P.eps - D : phi;
+  phisum += phi;
+  if (MODE == EV_RESULT) clr = fminf(clr, D);
+  // the force is zero outside the hinge band: when no lane of the
+  // wavefront has a sample inside it, the gradient and the wrench terms
+  // (which would add zeros) are skipped
+  const bool band = GRAD && __any(D < P.eps);
+  if (band) {
+    float gx, gy, gz;
+    blend_grad(fy, fz, bl, gx, gy, gz);
+    // world units; zero along axes where the point was clamped
+    gx *= (cx == u[0]) ? S.inv_h : 0.f;
+    gy *= (cy == u[1]) ? S.inv_h : 0.f;
+    gz *= (cz == u[2]) ? S.inv_h : 0.f;
+    float dphi = (D < P.eps) ? De * P.inv_eps : 0.f;
+    dphi = (D < 0.f) ? -1.f : dphi;
+    float w = P.wc * dphi;
+    float fx = w * gx, fyy = w * gy, fzz = w * gz;
+    // the sphere centre (the moment arm) back from its grid position
+    const float px = fmaf(u[0], S.h, S.ox);
+    const float py = fmaf(u[1], S.h, S.oy);
+    const float pz = fmaf(u[2], S.h, S.oz);
+    FM[0] += fx; FM[1] += fyy; FM[2] += fzz;
+    FM[3] += py * fzz - pz * fyy;
+    FM[4] += pz * fx - px * fzz;
+    FM[5] += px * fyy - py * fx;
+  }
+  return band;
+}
+
+// Project a link wrench on the joints 0..l: g_i += z_i . (M - o_i x F).
+__device__ __forceinline__ void project(const Twists& tw, int l, const float* FM, float* g) {
+#pragma unroll
+  for (int i = 0; i < NJ; ++i) {
+    if (i > l) break;
+    float zi[3], oi[3];
+    tw.get(i, zi, oi);
+    float tx = FM[3] - (oi[1] * FM[2] - oi[2] * FM[1]);
+    float ty = FM[4] - (oi[2] * FM[0] - oi[0] * FM[2]);
+    float tz = FM[5] - (oi[0] * FM[1] - oi[1] * FM[0]);
+    g[i] += zi[0] * tx + zi[1] * ty + zi[2] * tz;
+  }
+}
+
+// Self-collision share of this lane (App. A.6 C_self): every pair of spheres
+// on links at least two apart, hinge on D = |c_a - c_b| - r_a - r_b; the
+// pairs of each link pair are split over the W*L copies.  The sweep keeps
+// the seven link frames; forces go into per-link wrenches that are projected
+// on the joint axes at the end.
+template <int MODE>
+__device__ __attribute__((noinline)) void self_collision(const RobotDev* __restrict__ rb,
+                                                         const ParamsDev& P, const float* q,
+                                                         int cp, int LW, float& selfsum,
+                                                         float& clr, float* g) {
+  constexpr bool GRAD = (MODE == EV_GRAD);
+  float Rf[NJ][9], pf[NJ][3];
+  float R[9] = {1.f, 0.f, 0.f, 0.f, 1.f, 0.f, 0.f, 0.f, 1.f};
+  float p[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+  for (int l = 0; l < NJ; ++l) {
+    const float* F = rb->F[l];
+    float A[9], pa[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        A[3 * r + c] = R[3 * r] * F[c] + R[3 * r + 1] * F[4 + c] + R[3 * r + 2] * F[8 + c];
+      pa[r] = R[3 * r] * F[3] + R[3 * r + 1] * F[7] + R[3 * r + 2] * F[11] + p[r];
+    }
+    float sn, cs;
+    sincosf(q[l], &sn, &cs);
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      float a0 = A[3 * r], a1 = A[3 * r + 1];
+      R[3 * r] = cs * a0 + sn * a1;
+      R[3 * r + 1] = cs * a1 - sn * a0;
+      R[3 * r + 2] = A[3 * r + 2];
+      p[r] = pa[r];
+    }
+#pragma unroll
+    for (int k = 0; k < 9; ++k) Rf[l][k] = R[k];
+    pf[l][0] = p[0]; pf[l][1] = p[1]; pf[l][2] = p[2];
+  }
+  float FM[NJ][6];
+#pragma unroll
+  for (int l = 0; l < NJ; ++l)
+#pragma unroll
+    for (int k = 0; k < 6; ++k) FM[l][k] = 0.f;
+#pragma unroll
+  for (int la = 0; la < NJ; ++la) {
+#pragma unroll
+    for (int lb = la + 2; lb < NJ; ++lb) {
+      const int a0 = rb->link_begin[la], na = rb->link_begin[la + 1] - a0;
+      const int b0 = rb->link_begin[lb], nb = rb->link_begin[lb + 1] - b0;
+      for (int k = cp; k < na * nb; k += LW) {
+        const int ia = k / nb, ib = k - ia * nb;
+        const float4 sa = s_sph[a0 + ia], sb = s_sph[b0 + ib];
+        float ca[3], cb[3];
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+          ca[r] = Rf[la][3 * r] * sa.x + Rf[la][3 * r + 1] * sa.y + Rf[la][3 * r + 2] * sa.z + pf[la][r];
+          cb[r] = Rf[lb][3 * r] * sb.x + Rf[lb][3 * r + 1] * sb.y + Rf[lb][3 * r + 2] * sb.z + pf[lb][r];
+        }
+        float dx = ca[0] - cb[0], dy = ca[1] - cb[1], dz = ca[2] - cb[2];
+        float dist = sqrtf(dx * dx + dy * dy + dz * dz);
+        float D = dist - sa.w - sb.w;
+        float De = D - P.eps;
+        float phi = (D < P.eps) ? De * De * P.half_inv_eps : 0.f;
+        phi = (D < 0.f) ? 0.5f * P.eps - D : phi;
+        selfsum += phi;
+        if (MODE == EV_RESULT) clr = fminf(clr, D);
+        if (GRAD) {
+          float dphi = (D < P.eps) ? De * P.inv_eps : 0.f;
+          dphi = (D < 0.f) ? -1.f : dphi;
+          float w = (dist > 0.f) ? P.ws * dphi / dist : 0.f;
+          float fx = w * dx, fy = w * dy, fz = w * dz;
+          FM[la][0] += fx; FM[la][1] += fy; FM[la][2] += fz;
+          FM[la][3] += ca[1] * fz - ca[2] * fy;
+          FM[la][4] += ca[2] * fx - ca[0] * fz;
+          FM[la][5] += ca[0] * fy - ca[1] * fx;
+          FM[lb][0] -= fx; FM[lb][1] -= fy; FM[lb][2] -= fz;
+          FM[lb][3] -= cb[1] * fz - cb[2] * fy;
+          FM[lb][4] -= cb[2] * fx - cb[0] * fz;
+          FM[lb][5] -= cb[0] * fy - cb[1] * fx;
+        }
+      }
+    }
+  }
+  if (GRAD) {
+#pragma unroll
+    for (int l = 0; l < NJ; ++l) {
+#pragma unroll
+      for (int i = 0; i <= l; ++i) {
+        const float zi[3] = {Rf[i][2], Rf[i][5], Rf[i][8]};
+        const float* oi = pf[i];
+        float tx = FM[l][3] - (oi[1] * FM[l][2] - oi[2] * FM[l][1]);
+        float ty = FM[l][4] - (oi[2] * FM[l][0] - oi[0] * FM[l][2]);
+        float tz = FM[l][5] - (oi[0] * FM[l][1] - oi[1] * FM[l][0]);
+        g[i] += zi[0] * tx + zi[1] * ty + zi[2] * tz;
+      }
+    }
+  }
+}
+
+// The sweep over the chain for one configuration q: FK, this lane's share
+// of the sphere samples (hinge sum into phisum, min clearance into clr) and,
+// with GRAD, the link wrenches projected on the joint axes into g.  On
+// return R, p hold the frame of link 7 and tw the joint twists.
+// PIPE (every lane holds at most one sphere of each link, W*L >= spheres
+// per link): the sweep issues each link's record load as soon as its frame
+// exists and consumes the samples afterwards, so one memory round trip
+// covers the whole configuration.  Otherwise each link is processed in
+// chunks of CH gathers right after its frame.
+template <int MODE, bool PIPE>
+__device__ __forceinline__ void sweep(const RobotDev* __restrict__ rb, const ParamsDev& P,
+                                      const Sampler& S, const float* q, int cp, int LW,
+                                      Twists& tw, float* R, float* p, float& phisum, float& clr,
+                                      float* g, int& ng, bool active) {
+  constexpr bool GRAD = (MODE == EV_GRAD);
+  // the result pass gathers every sample: the clearance is a minimum over
+  // all of them
+  const bool SKIP = MODE != EV_RESULT && P.skip;
+  R[0] = 1.f; R[1] = 0.f; R[2] = 0.f; R[3] = 0.f; R[4] = 1.f; R[5] = 0.f;
+  R[6] = 0.f; R[7] = 0.f; R[8] = 1.f;
+  p[0] = p[1] = p[2] = 0.f;
+  // PIPE: the lane's sample of every link (grid position, radius, coarse
+  // minimum, record)
+  float4 pa_[PIPE ? NJ : 1], pz_[PIPE ? NJ : 1];
+  float pu_[PIPE ? NJ : 1][3], pr_[PIPE ? NJ : 1], pcm_[PIPE ? NJ : 1];
+  bool pv_[PIPE ? NJ : 1];
+#pragma unroll
+  for (int l = 0; l < NJ; ++l) {
+    const float* F = rb->F[l];
+    float A[9], pa[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        A[3 * r + c] = R[3 * r] * F[c] + R[3 * r + 1] * F[4 + c] + R[3 * r + 2] * F[8 + c];
+      pa[r] = R[3 * r] * F[3] + R[3 * r + 1] * F[7] + R[3 * r + 2] * F[11] + p[r];
+    }
+    float sn, cs;
+    sincosf(q[l], &sn, &cs);
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      float a0 = A[3 * r], a1 = A[3 * r + 1];
+      R[3 * r] = cs * a0 + sn * a1;
+      R[3 * r + 1] = cs * a1 - sn * a0;
+      R[3 * r + 2] = A[3 * r + 2];
+      p[r] = pa[r];
+    }
+    if (GRAD) tw.put(l, R, p);
+    const int s0 = rb->link_begin[l], s1 = rb->link_begin[l + 1];
+    const bool axis = (rb->axis_links >> l) & 1;   // wave-uniform
+    const LinkGrid lg = link_grid(S, R, p);
+    if (PIPE) {
+      // copy cp takes sphere (cp - rot) mod LW of the link, rot advancing by
+      // the longest link's sphere count from link to link: when there are
+      // more copies than spheres, consecutive links land on different
+      // copies and the samples spread evenly over the wavefronts
+      int idx = cp - (l * rb->max_per_link) % LW;
+      if (idx < 0) idx += LW;
+      const int sk = s0 + idx;
+      pv_[l] = active && sk < s1;   // lanes past the horizon gather nothing
+      if (pv_[l]) {
+        const float4 sp = s_sph[sk];
+        grid_pos(S, lg, axis, R, p, sp, pu_[l]);
+        pr_[l] = sp.w;
+        // the coarse minimum is read here and tested after the chain, so
+        // no link waits for its lookup before the next frame
+        if (SKIP) {
+          int ci[3];
+          cell_of(S, pu_[l], ci);
+          pcm_[l] = coarse_at(S, block_index(S, ci));
+        }
+      }
+      continue;
+    }
+    float FM[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    bool forced = false;   // some sample of this link added a force
+    // chunks of CH spheres per lane (this lane takes every (W*L)-th sphere
+    // of the link): issue every record load of the chunk, then consume them
+    // in sphere order -- CH gathers in flight per lane.  A sample whose
+    // coarse block holds no node nearer than radius + eps (+ margin) has a
+    // zero hinge (a trilinear blend stays within its corners' range): it
+    // loads nothing.
+    for (int s = s0; s < s1; s += LW * CH) {
+      float u[CH][3], rr[CH];
+      int ci[CH][3];
+      float4 ra[CH], rz[CH];
+      bool use[CH];
+#pragma unroll
+      for (int k = 0; k < CH; ++k) {
+        const int sk = s + k * LW + cp;
+        use[k] = active && sk < s1;
+        if (use[k]) {
+          const float4 sp = s_sph[sk];
+          grid_pos(S, lg, axis, R, p, sp, u[k]);
+          cell_of(S, u[k], ci[k]);
+          rr[k] = sp.w;
+          if (SKIP && coarse_at(S, block_index(S, ci[k])) >= sp.w + P.far) {
+            use[k] = false;   // zero hinge, zero gradient
+          } else {
+            const int off = record_offset(S, ci[k]);
+            ra[k] = load_rec(S, off);
+            rz[k] = load_rec(S, off + 16);
+            ++ng;
+          }
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < CH; ++k) {
+        if (use[k])
+          forced |= sphere_term<MODE>(P, S, u[k], ci[k], ra[k], rz[k], rr[k], phisum, clr, FM);
+      }
+      // every load of the chunk has been consumed: saying so keeps the
+      // next chunk's loads in flight together.  (The loads and their uses
+      // sit in separate wavefront-uniform branches, so without it the
+      // compiler cannot tell which of them are outstanding at the loop's
+      // back edge and drains them all before each sphere's loads.)
+      __builtin_amdgcn_s_waitcnt(WAIT_VMEM_ALL);
+    }
+    // a link with no force in this wavefront has a zero wrench everywhere:
+    // its projection would add zeros
+    if (GRAD && __any(forced)) project(tw, l, FM, g);
+  }
+  if (PIPE) {
+    // issue the record loads of the samples that can reach the hinge
+#pragma unroll
+    for (int l = 0; l < NJ; ++l) {
+      if (pv_[l]) {
+        if (SKIP && pcm_[l] >= pr_[l] + P.far) {
+          pv_[l] = false;   // zero hinge, zero gradient: nothing to add
+        } else {
+          int ci[3];
+          cell_of(S, pu_[l], ci);
+          const int off = record_offset(S, ci);
+          pa_[l] = load_rec(S, off);
+          pz_[l] = load_rec(S, off + 16);
+          ++ng;
+        }
+      }
+    }
+#pragma unroll
+    for (int l = 0; l < NJ; ++l) {
+      float FM[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      bool forced = false;
+      if (pv_[l]) {
+        int ci[3];
+        cell_of(S, pu_[l], ci);
+        forced = sphere_term<MODE>(P, S, pu_[l], ci, pa_[l], pz_[l], pr_[l], phisum, clr, FM);
+      }
+      // a link with no force in this wavefront has a zero wrench
+      // everywhere: its projection would add zeros
+      if (GRAD && __any(forced)) project(tw, l, FM, g);
+    }
+  }
+}
+
+// One evaluation of the objective at this lane's configuration q (its
+// waypoint) and, with swept sub-samples, at the configurations interpolated
+// towards the next waypoint.
+template <int MODE, bool PIPE, bool EXT>
+__device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
+                                            const ParamsDev& P, const Sampler& S, const Goal& goal,
+                                            const float* q, int t, int T, int G, bool active,
+                                            Team& tm) {
+  constexpr bool GRAD = (MODE == EV_GRAD);
+  // the L = 64/G lanes holding the same waypoint in each of the W
+  // wavefronts split its spheres: copy index and stride
+  const int L = WAVE / G;
+  const int lane = threadIdx.x & (WAVE - 1);
+  const int cp = tm.w * L + lane / G;
+  const int LW = tm.W * L;
+  EvalOut o;
+  o.ng = 0;
+  o.perr = o.rerr = 0.f;
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) o.g[j] = 0.f;
+  float phisum = 0.f, clr = FLT_MAX;
+  if (EXT && P.nsub > 0) {
+    // swept collision: q + tau (q_next - q), tau = i / (nsub + 1); the
+    // gradient splits (1 - tau) here and tau onto the next waypoint
+    float qn[NJ], gsh[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      qn[j] = __shfl_down(q[j], 1);
+      gsh[j] = 0.f;
+    }
+    const bool seg = active && t <= T - 2;
+    for (int i = 1; i <= P.nsub; ++i) {
+      const float tau = (float)i / (float)(P.nsub + 1);
+      float qi[NJ], gi[NJ], Rs[9], ps[3];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        qi[j] = q[j] + tau * (qn[j] - q[j]);
+        gi[j] = 0.f;
+      }
+      Twists tws;
+      float ph = 0.f, cl = FLT_MAX;
+      sweep<MODE, PIPE>(rb, P, S, qi, cp, LW, tws, Rs, ps, ph, cl, gi, o.ng, seg);
+      if (seg) {
+        phisum += ph;
+        clr = fminf(clr, cl);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          o.g[j] += (1.f - tau) * gi[j];
+          gsh[j] += tau * gi[j];
+        }
+      }
+    }
+    if (GRAD) {
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        float up = __shfl_up(gsh[j], 1);
+        o.g[j] += (t >= 1) ? up : 0.f;
+      }
+    }
+  }
+  float R[9], p[3];
+  Twists tw;
+  sweep<MODE, PIPE>(rb, P, S, q, cp, LW, tw, R, p, phisum, clr, o.g, o.ng, active);
+  // collision cost share: world hinge sum, plus the self-collision pairs
+  // when that term is on
+  float coll = P.wc * phisum;
+  if (EXT && P.ws != 0.f) {
+    float selfsum = 0.f;
+    self_collision<MODE>(rb, P, q, cp, LW, selfsum, clr, o.g);
+    coll += P.ws * selfsum;
+  }
+  // goal pose, joint limits and smoothness: the same for every copy of the
+  // waypoint, so one wavefront of the team computes each and only its first
+  // copy adds them to its share before the sums below -- the goal on the
+  // second wavefront, the limits on the third and the smoothness on the
+  // fourth (off the first one's path; smaller teams fold them onto fewer
+  // wavefronts), except in the result pass, whose goal errors the first
+  // one writes
+  const int xg = (MODE == EV_RESULT || tm.W == 1) ? 0 : 1;
+  const int xl = (MODE == EV_RESULT || tm.W < 3) ? xg : 2;
+  const int xs = (MODE == EV_RESULT || tm.W < 4) ? xl : 3;
+  if (tm.w == xg || tm.w == xl || tm.w == xs) {
+    const bool first = lane < G;
+    const bool last = (t == T - 1);
+    float ge[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) ge[j] = 0.f;
+    float extra_g = 0.f, extra_l = 0.f;
+    if (tm.w == xg) {
+    // end effector and goal pose
+    const float* E = rb->Fee;
+    float Re[9], pe[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        Re[3 * r + c] = R[3 * r] * E[c] + R[3 * r + 1] * E[4 + c] + R[3 * r + 2] * E[8 + c];
+      pe[r] = R[3 * r] * E[3] + R[3 * r + 1] * E[7] + R[3 * r + 2] * E[11] + p[r];
+    }
+    float ex = pe[0] - goal.pd[0], ey = pe[1] - goal.pd[1], ez = pe[2] - goal.pd[2];
+    float tr = 0.f;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) tr += goal.Rd[k] * Re[k];
+    const float goal_cost = P.wp * (ex * ex + ey * ey + ez * ez) + P.wr * (3.f - tr) * 0.25f;
+    extra_g = last ? goal_cost : 0.f;
+    if (GRAD && last) {
+      // force 2 w_p e at p_ee and torque -(w_r/4) w, w = vee(M - M^T), M = R_ee R_d^T
+      float M[9];
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int b = 0; b < 3; ++b)
+          M[3 * a + b] = Re[3 * a] * goal.Rd[3 * b] + Re[3 * a + 1] * goal.Rd[3 * b + 1] +
+                         Re[3 * a + 2] * goal.Rd[3 * b + 2];
+      float wx = M[5] - M[7], wy = M[6] - M[2], wz = M[1] - M[3];
+      float k2 = 2.f * P.wp, k4 = -0.25f * P.wr;
+      float fx = k2 * ex, fy = k2 * ey, fz = k2 * ez;
+#pragma unroll
+      for (int i = 0; i < NJ; ++i) {
+        float zi[3], oi[3];
+        tw.get(i, zi, oi);
+        float rx = pe[0] - oi[0], ry = pe[1] - oi[1], rz = pe[2] - oi[2];
+        float tx = ry * fz - rz * fy + k4 * wx;
+        float ty = rz * fx - rx * fz + k4 * wy;
+        float tz = rx * fy - ry * fx + k4 * wz;
+        ge[i] += zi[0] * tx + zi[1] * ty + zi[2] * tz;
+      }
+    }
+    if (MODE == EV_RESULT) {
+      o.perr = sqrtf(ex * ex + ey * ey + ez * ez);
+      // angle of R_d^T R_ee: cos = (tr - 1) / 2, sin = |vee(R_ee R_d^T)| / 2
+      float M5, M7, M6, M2, M1, M3;
+      M5 = Re[3] * goal.Rd[6] + Re[4] * goal.Rd[7] + Re[5] * goal.Rd[8];
+      M7 = Re[6] * goal.Rd[3] + Re[7] * goal.Rd[4] + Re[8] * goal.Rd[5];
+      M6 = Re[6] * goal.Rd[0] + Re[7] * goal.Rd[1] + Re[8] * goal.Rd[2];
+      M2 = Re[0] * goal.Rd[6] + Re[1] * goal.Rd[7] + Re[2] * goal.Rd[8];
+      M1 = Re[0] * goal.Rd[3] + Re[1] * goal.Rd[4] + Re[2] * goal.Rd[5];
+      M3 = Re[3] * goal.Rd[0] + Re[4] * goal.Rd[1] + Re[5] * goal.Rd[2];
+      float wx = M5 - M7, wy = M6 - M2, wz = M1 - M3;
+      o.rerr = atan2f(0.5f * sqrtf(wx * wx + wy * wy + wz * wz), 0.5f * (tr - 1.f));
+    }
+    }
+    if (tm.w == xl) {
+    // joint limits
+    float lim = 0.f;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      float hi = q[j] - rb->qhi[j], lo = rb->qlo[j] - q[j];
+      float hp = fmaxf(hi, 0.f), lp = fmaxf(lo, 0.f);
+      lim += hp * hp + lp * lp;
+      if (GRAD) ge[j] += 2.f * P.wl * (hp - lp);
+    }
+    extra_l = P.wl * lim;
+    }
+    if (tm.w == xs) extra_l += smoothness<GRAD>(P, q, t, T, ge);
+    coll += first ? extra_l + extra_g : 0.f;
+    if (GRAD) {
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) o.g[j] += first ? ge[j] : 0.f;
+    }
+  }
+  phisum = coll;
+  // a team's gradient pass sums the copies inside its reduce-scatter below
+  const bool scatter = GRAD && tm.W > 1;
+  // sum the shares of the L lanes of this waypoint (butterfly: every copy
+  // ends with the same value)
+  if (!scatter)
+  for (int off = G; off < WAVE; off <<= 1) {
+    phisum = xor_reduce<OpSum>(phisum, off);
+    if (MODE == EV_RESULT) clr = xor_reduce<OpMin>(clr, off);
+    if (GRAD) {
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) o.g[j] = xor_reduce<OpSum>(o.g[j], off);
+    }
+  }
+  if (scatter) {
+    // ... and of the W wavefronts, summed in wavefront order: wavefront w
+    // sums the components c = w mod W of the team (into wavefront 0's row)
+    // -- each copy's lanes separately, then the copies by the butterfly --
+    // and every wavefront takes the sums
+    constexpr int NC = NJ + 1;
+    float* base = tm.lds + (tm.buf * tm.W * PART) * WAVE + lane;
+    float* mine = base + tm.w * PART * WAVE;
+    mine[0] = phisum;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) mine[(1 + j) * WAVE] = o.g[j];
+    tm.sync();
+    for (int cc = tm.w; cc < NC; cc += tm.W) {
+      float v = base[cc * WAVE];
+      for (int u = 1; u < tm.W; ++u) v += base[(u * PART + cc) * WAVE];
+      for (int off = G; off < WAVE; off <<= 1) v = xor_reduce<OpSum>(v, off);
+      base[cc * WAVE] = v;
+    }
+    tm.sync();
+    phisum = base[0];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) o.g[j] = base[(1 + j) * WAVE];
+    tm.buf ^= 1;
+  } else if (tm.W > 1) {
+    // (cost and result passes: every wavefront sums all shares)
+    float* mine = tm.lds + ((tm.buf * tm.W + tm.w) * PART) * WAVE + lane;
+    mine[0] = phisum;
+    if (MODE == EV_RESULT) mine[(1 + NJ) * WAVE] = clr;
+    tm.sync();
+    const float* all = tm.lds + (tm.buf * tm.W * PART) * WAVE + lane;
+    phisum = all[0];
+    if (MODE == EV_RESULT) clr = all[(1 + NJ) * WAVE];
+    for (int v = 1; v < tm.W; ++v) {
+      const float* pv = all + v * PART * WAVE;
+      phisum += pv[0];
+      if (MODE == EV_RESULT) clr = fminf(clr, pv[(1 + NJ) * WAVE]);
+    }
+    tm.buf ^= 1;
+  }
+  if (MODE == EV_RESULT) o.clr = clr;
+  o.cost = active ? phisum : 0.f;
+  if (GRAD) {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) o.g[j] = (active && t > 0) ? o.g[j] : 0.f;
+  }
+  return o;
+}
+
+// The evaluation form for this team: PIPE when every lane holds at most one
+// sphere per link.
+template <int MODE, bool EXT>
+__device__ __forceinline__ EvalOut eval_any(bool pipe, const RobotDev* __restrict__ rb,
+                                            const ParamsDev& P, const Sampler& S, const Goal& goal,
+                                            const float* q, int t, int T, int G, bool active,
+                                            Team& tm) {
+  if (pipe) return evaluate<MODE, true, EXT>(rb, P, S, goal, q, t, T, G, active, tm);
+  return evaluate<MODE, false, EXT>(rb, P, S, goal, q, t, T, G, active, tm);
+}
+
+__device__ __forceinline__ bool use_pipe(const RobotDev* __restrict__ rb, const Team& tm, int G) {
+  return tm.W * (WAVE / G) >= rb->max_per_link;
+}
+
+}  // namespace
+}  // namespace dsk
