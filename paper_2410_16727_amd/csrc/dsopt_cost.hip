@@ -16,11 +16,13 @@ __device__ __forceinline__ int seed_of(int W, float* team_lds, Team& tm) {
     tm.W = W;
     tm.w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
     tm.lds = team_lds;
+    tm.kin = W == MAX_TEAM ? team_lds + 2 * W * PART * WAVE : nullptr;
     return blockIdx.x;
   }
   tm.W = 1;
   tm.w = 0;
   tm.lds = nullptr;
+  tm.kin = nullptr;
   return (blockIdx.x * BLOCK + threadIdx.x) / WAVE;
 }
 
@@ -53,15 +55,15 @@ k_cost(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp, const 
   float x[NJ];
   load_waypoint(X, seed, S, T, t, x);
   if (pp->skip) stage_coarse(pb.sc, lds(s_cm), threadIdx.x, blockDim.x);
-  stage_spheres(rb);
+  stage_robot(rb);
   if (seed >= S) return;   // whole wavefront (team: whole workgroup) past the end
   ParamsDev P = *pp;
-  Sampler Sm = make_sampler(pb.sc);
+  Sampler Sm = make_sampler(pb.sc, rb);
   Sm.cm = lds(s_cm);
-  Goal goal = make_goal(pb);
+  put_goal(pb);
   float J;
   if (with_grad) {
-    EvalOut e = eval_any<EV_GRAD, EXT>(use_pipe(rb, tm, G), rb, P, Sm, goal, x, t, T, G, active, tm);
+    EvalOut e = eval_any<EV_GRAD, EXT>(use_pipe(rb, tm, G), rb, P, Sm, x, t, T, G, active, tm);
     J = grp_sum(e.cost, G);
     float w = dJ ? dJ[seed] : 1.f;
     if (active && owner) {
@@ -69,7 +71,7 @@ k_cost(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp, const 
       for (int j = 0; j < NJ; ++j) dX[((size_t)seed * T + t) * NJ + j] = w * e.g[j];
     }
   } else {
-    EvalOut e = eval_any<EV_COST, EXT>(use_pipe(rb, tm, G), rb, P, Sm, goal, x, t, T, G, active, tm);
+    EvalOut e = eval_any<EV_COST, EXT>(use_pipe(rb, tm, G), rb, P, Sm, x, t, T, G, active, tm);
     J = grp_sum(e.cost, G);
   }
   if (J_out && tm.w == 0 && lane == 0) J_out[seed] = J;
@@ -93,20 +95,20 @@ k_guide(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp, const
   float x[NJ];
   load_waypoint(X, seed, S, T, t, x);
   if (pp->skip) stage_coarse(pb.sc, lds(s_cm), threadIdx.x, blockDim.x);
-  stage_spheres(rb);
+  stage_robot(rb);
   if (seed >= S) return;   // whole wavefront (team: whole workgroup) past the end
   ParamsDev P = *pp;
-  Sampler Sm = make_sampler(pb.sc);
+  Sampler Sm = make_sampler(pb.sc, rb);
   Sm.cm = lds(s_cm);
-  Goal goal = make_goal(pb);
+  put_goal(pb);
   const bool pipe = use_pipe(rb, tm, G);
   for (int k = 0; k < n_steps; ++k) {
-    EvalOut e = eval_any<EV_GRAD, EXT>(pipe, rb, P, Sm, goal, x, t, T, G, active, tm);
+    EvalOut e = eval_any<EV_GRAD, EXT>(pipe, rb, P, Sm, x, t, T, G, active, tm);
 #pragma unroll
     for (int j = 0; j < NJ; ++j) x[j] -= alpha * e.g[j];
   }
   if (J_out) {
-    EvalOut e = eval_any<EV_COST, EXT>(pipe, rb, P, Sm, goal, x, t, T, G, active, tm);
+    EvalOut e = eval_any<EV_COST, EXT>(pipe, rb, P, Sm, x, t, T, G, active, tm);
     float J = grp_sum(e.cost, G);
     if (tm.w == 0 && lane == 0) J_out[seed] = J;
   }
@@ -173,7 +175,7 @@ hipError_t launch_cost(const RobotDev* rb, const ParamsDev* pp, const ProbDev& p
   const int G = T <= 16 ? 16 : (T <= 32 ? 32 : 64);
   const int W = cost_team(S, cu_count);
   const int blocks = W > 1 ? S : (S + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK;
-  const size_t lds_bytes = W > 1 ? (size_t)2 * W * PART * WAVE * sizeof(float) : 0;
+  const size_t lds_bytes = eval_lds(W);
   hipLaunchKernelGGL(ext ? k_cost<true> : k_cost<false>, dim3(blocks), dim3(W > 1 ? W * WAVE : BLOCK),
                      lds_bytes, s, rb, pp, prob, X, S, T, G, dJ, J_out, dX, with_grad, W);
   return hipGetLastError();
@@ -185,7 +187,7 @@ hipError_t launch_guide(const RobotDev* rb, const ParamsDev* pp, const ProbDev& 
   const int G = T <= 16 ? 16 : (T <= 32 ? 32 : 64);
   const int W = cost_team(S, cu_count);
   const int blocks = W > 1 ? S : (S + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK;
-  const size_t lds_bytes = W > 1 ? (size_t)2 * W * PART * WAVE * sizeof(float) : 0;
+  const size_t lds_bytes = eval_lds(W);
   hipLaunchKernelGGL(ext ? k_guide<true> : k_guide<false>, dim3(blocks), dim3(W > 1 ? W * WAVE : BLOCK),
                      lds_bytes, s, rb, pp, prob, X, S, T, G, alpha, n_steps, J_out, W);
   return hipGetLastError();

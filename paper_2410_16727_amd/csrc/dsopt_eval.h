@@ -23,6 +23,7 @@
 
 #include <cfloat>
 #include <cmath>
+#include <cstddef>
 #include <type_traits>
 
 #include "dsopt_internal.h"
@@ -140,13 +141,18 @@ __device__ __forceinline__ float dot7(const float* a, const float* b) {
   return s;
 }
 
+// The goal pose of a wavefront's tile lives in LDS: twelve values that one
+// section of the evaluation reads (in registers they were live across all of
+// it).
 struct Goal {
   float pd[3];
   float Rd[9];
 };
+constexpr int MAX_WAVES = 8;   // wavefronts of a workgroup
+__shared__ Goal s_goal[MAX_WAVES];
 
 // Unit goal quaternion (w, x, y, z) -> rotation matrix (uniform per tile).
-__device__ __forceinline__ Goal make_goal(const ProbDev& pb) {
+__device__ __forceinline__ void put_goal(const ProbDev& pb) {
   Goal g;
   float w = pb.quat[0], x = pb.quat[1], y = pb.quat[2], z = pb.quat[3];
   float n = sqrtf(w * w + x * x + y * y + z * z);
@@ -155,10 +161,48 @@ __device__ __forceinline__ Goal make_goal(const ProbDev& pb) {
   g.Rd[3] = 2.f * (x * y + w * z); g.Rd[4] = 1.f - 2.f * (x * x + z * z); g.Rd[5] = 2.f * (y * z - w * x);
   g.Rd[6] = 2.f * (x * z - w * y); g.Rd[7] = 2.f * (y * z + w * x); g.Rd[8] = 1.f - 2.f * (x * x + y * y);
   g.pd[0] = pb.pd[0]; g.pd[1] = pb.pd[1]; g.pd[2] = pb.pd[2];
-  return g;
+  // (a wavefront's LDS accesses complete in order: no barrier)
+  if ((threadIdx.x & (WAVE - 1)) == 0) s_goal[threadIdx.x / WAVE] = g;
+  __builtin_amdgcn_wave_barrier();
+}
+__device__ __forceinline__ Goal get_goal() {
+  return s_goal[__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE))];
+}
+
+// The robot's sphere ranges, packed into three scalar registers: read from
+// the table at every use they were a scalar memory round trip per link and
+// evaluation (the compiler repeats invariant loads when it is short of
+// scalar registers, unless their value is opaque to it).
+struct Links {
+  unsigned lo, hi, misc;
+  // spheres of link l (0..6): [begin(l), begin(l + 1))
+  __device__ __forceinline__ int begin(int l) const {
+    return (int)((l < 4 ? lo >> (8 * l) : hi >> (8 * (l - 4))) & 255u);
+  }
+  __device__ __forceinline__ int last() const { return begin(NJ) - 1; }
+  // whether every sphere of link l sits on its z axis
+  __device__ __forceinline__ bool axis(int l) const { return (misc >> l) & 1u; }
+  __device__ __forceinline__ bool all_axis() const { return (misc & 0x7Fu) == 0x7Fu; }
+  __device__ __forceinline__ int most() const { return (int)(misc >> 8); }   // on one link
+};
+static_assert(DS_MAX_SPHERES <= 255, "sphere positions are bytes");
+
+__device__ __forceinline__ Links make_links(const RobotDev* __restrict__ rb) {
+  Links k{0, 0, (unsigned)rb->axis_links | ((unsigned)rb->max_per_link << 8)};
+#pragma unroll
+  for (int l = 0; l < 4; ++l) {
+    k.lo |= (unsigned)rb->link_begin[l] << (8 * l);
+    k.hi |= (unsigned)rb->link_begin[l + 4] << (8 * l);
+  }
+  k.lo = __builtin_amdgcn_readfirstlane(k.lo);
+  k.hi = __builtin_amdgcn_readfirstlane(k.hi);
+  k.misc = __builtin_amdgcn_readfirstlane(k.misc);
+  asm("" : "+s"(k.lo), "+s"(k.hi), "+s"(k.misc));
+  return k;
 }
 
 struct Sampler {
+  Links ln;
   __amdgpu_buffer_rsrc_t rsrc;
   float ox, oy, oz, inv_h, h, nxm1, nym1, nzm1;
   float fxm2, fym2, fzm2;          // last cell index per axis, as floats
@@ -168,8 +212,9 @@ struct Sampler {
   int cshift, cdx, cdy;
 };
 
-__device__ __forceinline__ Sampler make_sampler(const SceneDev& sc) {
+__device__ __forceinline__ Sampler make_sampler(const SceneDev& sc, const RobotDev* __restrict__ rb) {
   Sampler s;
+  s.ln = make_links(rb);
   s.rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)sc.rec, (short)0, (int)sc.bytes, RSRC_DWORD3);
   s.ox = sc.ox; s.oy = sc.oy; s.oz = sc.oz; s.inv_h = sc.inv_h; s.h = 1.f / sc.inv_h;
   s.nxm1 = (float)(sc.nx - 1); s.nym1 = (float)(sc.ny - 1); s.nzm1 = (float)(sc.nz - 1);
@@ -238,32 +283,32 @@ struct LinkGrid {
   float u0[3], az[3];
 };
 
-__device__ __forceinline__ LinkGrid link_grid(const Sampler& S, const float* R, const float* p) {
+// (z: the third column of R)
+__device__ __forceinline__ LinkGrid link_grid(const Sampler& S, const float* z, const float* p) {
   LinkGrid g;
   g.u0[0] = (p[0] - S.ox) * S.inv_h;
   g.u0[1] = (p[1] - S.oy) * S.inv_h;
   g.u0[2] = (p[2] - S.oz) * S.inv_h;
-  g.az[0] = R[2] * S.inv_h;
-  g.az[1] = R[5] * S.inv_h;
-  g.az[2] = R[8] * S.inv_h;
+  g.az[0] = z[0] * S.inv_h;
+  g.az[1] = z[1] * S.inv_h;
+  g.az[2] = z[2] * S.inv_h;
   return g;
 }
 
-// Grid position of the sphere with offset/radius sp on the link (R, p);
-// `axis` (wave-uniform) says the link's spheres sit on its z axis.
-__device__ __forceinline__ void grid_pos(const Sampler& S, const LinkGrid& g, bool axis,
-                                         const float* R, const float* p, float4 sp, float* u) {
-  if (axis) {
+// Grid position of a sphere at oz on its link's z axis ...
+__device__ __forceinline__ void axis_pos(const LinkGrid& g, float oz, float* u) {
 #pragma unroll
-    for (int r = 0; r < 3; ++r) u[r] = fmaf(sp.z, g.az[r], g.u0[r]);
-  } else {
-    const float cx = R[0] * sp.x + R[1] * sp.y + R[2] * sp.z + p[0];
-    const float cy = R[3] * sp.x + R[4] * sp.y + R[5] * sp.z + p[1];
-    const float cz = R[6] * sp.x + R[7] * sp.y + R[8] * sp.z + p[2];
-    u[0] = (cx - S.ox) * S.inv_h;
-    u[1] = (cy - S.oy) * S.inv_h;
-    u[2] = (cz - S.oz) * S.inv_h;
-  }
+  for (int r = 0; r < 3; ++r) u[r] = fmaf(oz, g.az[r], g.u0[r]);
+}
+// ... and of any sphere on the link (R, p).
+__device__ __forceinline__ void frame_pos(const Sampler& S, const float* R, const float* p,
+                                          float4 sp, float* u) {
+  const float cx = R[0] * sp.x + R[1] * sp.y + R[2] * sp.z + p[0];
+  const float cy = R[3] * sp.x + R[4] * sp.y + R[5] * sp.z + p[1];
+  const float cz = R[6] * sp.x + R[7] * sp.y + R[8] * sp.z + p[2];
+  u[0] = (cx - S.ox) * S.inv_h;
+  u[1] = (cy - S.oy) * S.inv_h;
+  u[2] = (cz - S.oz) * S.inv_h;
 }
 
 // The sample's cell: trunc(clamp(u, 0, n-2)) per axis (for u >= 0,
@@ -340,9 +385,19 @@ enum { EV_COST = 0, EV_GRAD = 1, EV_RESULT = 2 };
 // be vector memory round trips ahead of every record gather.
 __shared__ float4 s_sph[DS_MAX_SPHERES];
 
-// Fill s_sph; every thread of the workgroup must call it.
-__device__ __forceinline__ void stage_spheres(const RobotDev* __restrict__ rb) {
+// The fixed transforms before the joints, rows of 3x4: read by the wavefronts
+// that form a team's frames (scalar loads would be five round trips along
+// the chain).
+__shared__ float4 s_frame[3 * NJ + 3];   // and the end effector's
+
+// Fill s_sph and s_frame; every thread of the workgroup must call it.
+__device__ __forceinline__ void stage_robot(const RobotDev* __restrict__ rb) {
   for (int i = threadIdx.x; i < rb->ns; i += blockDim.x) s_sph[i] = rb->sph[i];
+  static_assert(offsetof(RobotDev, Fee) == sizeof(RobotDev::F), "the frames are one array");
+  if (threadIdx.x < 3 * NJ + 3) {
+    const float* f = &rb->F[0][0] + 4 * threadIdx.x;
+    s_frame[threadIdx.x] = make_float4(f[0], f[1], f[2], f[3]);
+  }
   __syncthreads();
 }
 
@@ -401,6 +456,21 @@ __device__ __forceinline__ float smoothness(const ParamsDev& P, const float* q, 
   return c;
 }
 
+// Joint-limit penalty (its gradient into g).
+template <bool GRAD>
+__device__ __forceinline__ float limits(const RobotDev* __restrict__ rb, const ParamsDev& P,
+                                        const float* q, float* g) {
+  float lim = 0.f;
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    float hi = q[j] - rb->qhi[j], lo = rb->qlo[j] - q[j];
+    float hp = fmaxf(hi, 0.f), lp = fmaxf(lo, 0.f);
+    lim += hp * hp + lp * lp;
+    if (GRAD) g[j] += 2.f * P.wl * (hp - lp);
+  }
+  return P.wl * lim;
+}
+
 // A team of W wavefronts (one workgroup) optimises one seed: every
 // wavefront holds the whole trajectory (one waypoint per lane group) and
 // takes every (W*L)-th sphere of each link; the partial sums meet in
@@ -412,26 +482,44 @@ constexpr int PART = NJ + 2;   // partial sums per lane: hinge sum, gradient row
 struct Team {
   int W, w;       // team size, this wavefront's index
   float* lds;     // [2][W][PART][64]
+  float* kin;     // [KIN_ROWS][64] of a full team, else null
   int buf;
   __device__ __forceinline__ void sync() const {
     if (W > 1) __syncthreads();
   }
 };
 
-// Hinge cost of one sphere sample (grid position u, cell ci, cell record
-// ra/rz, radius r) and, with GRAD, its force accumulated into the link
+// Kinematics of a full team (MAX_TEAM wavefronts), shared through LDS.  With
+// every wavefront forming the whole chain (about 530 VALU instructions of
+// 1270 per evaluation, two wavefronts on each SIMD) the SIMDs issued in 80 %
+// of the cycles; here three wavefronts form a row of every frame each (the
+// rows of R and the components of p follow the chain independently of each
+// other) and all of them read what they need.  One more barrier, the same
+// arithmetic per element: the results are those of the whole chain.
+// Rows of 64 lanes: per link the joint axis (third column of R) and the
+// origin; per link the first two columns of R; the goal's part of the sums.
+// Smaller teams keep the whole chain: there are fewer copies of it to save,
+// and the rows would halve the workgroups that fit a CU.
+constexpr int KIN_ZO = 0, KIN_XY = KIN_ZO + 6 * NJ, KIN_GOAL = KIN_XY + 6 * NJ,
+              KIN_ROWS = KIN_GOAL + 1;
+
+// Hinge cost of one sphere sample (grid position u, cell record ra/rz,
+// radius r) and, with GRAD, its force accumulated into the link
 // wrench (F, M about the world origin).  Returns whether the force terms
 // ran (some lane of the wavefront inside the hinge band).
 template <int MODE>
 __device__ __forceinline__ bool sphere_term(const ParamsDev& P, const Sampler& S, const float* u,
-                                            const int* ci, float4 ra, float4 rz, float r,
+                                            float4 ra, float4 rz, float r,
                                             float& phisum, float& clr, float* FM) {
   constexpr bool GRAD = (MODE == EV_GRAD);
   const float cx = __builtin_amdgcn_fmed3f(u[0], 0.f, S.nxm1);
   const float cy = __builtin_amdgcn_fmed3f(u[1], 0.f, S.nym1);
   const float cz = __builtin_amdgcn_fmed3f(u[2], 0.f, S.nzm1);
-  const float fy = cy - (float)ci[1], fz = cz - (float)ci[2];
-  const Blend bl = blend_value(cx - (float)ci[0], fy, fz, ra, rz);
+  // the cell, as cell_of gives it
+  const float fx0 = cx - truncf(__builtin_amdgcn_fmed3f(u[0], 0.f, S.fxm2));
+  const float fy = cy - truncf(__builtin_amdgcn_fmed3f(u[1], 0.f, S.fym2));
+  const float fz = cz - truncf(__builtin_amdgcn_fmed3f(u[2], 0.f, S.fzm2));
+  const Blend bl = blend_value(fx0, fy, fz, ra, rz);
   float D = bl.d - r;
   float De = D - P.eps;
   float phi = (D < P.eps) ? De * De * P.half_inv_eps : 0.f;
@@ -579,156 +667,303 @@ __device__ __attribute__((noinline)) void self_collision(const RobotDev* __restr
   }
 }
 
+// Sines and cosines of N joint angles.  Below 2^17 the library's sincosf is a
+// short straight line; above it reduces the argument by a long one, and with
+// both in the code every call is two branches around it, which cost about as
+// much as the line itself.  Angles that large only come from a caller's
+// seeds: one test for the wavefront takes the short form for all of them
+// (the same instructions, hence the same results), or the whole one for all.
+template <int N>
+__device__ __forceinline__ void sincos_n(const float* q, float* sn, float* cs) {
+  constexpr float SHORT = 0x1p17f;
+  unsigned most = 0;   // as bits, so that a NaN counts as large
+#pragma unroll
+  for (int j = 0; j < N; ++j) most = max(most, __float_as_uint(q[j]) & 0x7FFFFFFFu);
+  if (__any(most >= __float_as_uint(SHORT))) {
+    // (one copy of the long form: the angles pass through it in turn)
+    float x[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      x[j] = q[j];
+      sn[j] = cs[j] = 0.f;
+    }
+#pragma unroll 1
+    for (int k = 0; k < N; ++k) {
+      float s, c;
+      sincosf(x[0], &s, &c);
+#pragma unroll
+      for (int j = 0; j + 1 < N; ++j) {
+        x[j] = x[j + 1];
+        sn[j] = sn[j + 1];
+        cs[j] = cs[j + 1];
+      }
+      sn[N - 1] = s;
+      cs[N - 1] = c;
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const bool is_short = __builtin_fabsf(q[j]) < SHORT;
+      __builtin_assume(is_short);
+      sincosf(q[j], &sn[j], &cs[j]);
+    }
+  }
+}
+
+// The next frame of the chain: (R, p) of a link from its predecessor's and the
+// link's fixed transform F, turned by the joint (sine sn, cosine cs).  One
+// row of it (row r of R, component r of p):
+__device__ __forceinline__ void frame_row(const float* F, float sn, float cs, float* R, float& p) {
+  float A[3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) A[c] = R[0] * F[c] + R[1] * F[4 + c] + R[2] * F[8 + c];
+  p = R[0] * F[3] + R[1] * F[7] + R[2] * F[11] + p;
+  R[0] = cs * A[0] + sn * A[1];
+  R[1] = cs * A[1] - sn * A[0];
+  R[2] = A[2];
+}
+
+// The kinematics of q by a full team: the twists of every joint on return,
+// the frames' rows in tm.kin.  `between` runs while three wavefronts form the
+// frames (work of the others that needs no frame).  Every wavefront calls it.
+template <class Between>
+__device__ __forceinline__ void team_kinematics(const RobotDev* __restrict__ rb, const Team& tm,
+                                                const float* q, Twists& tw, Between between) {
+  const int lane = threadIdx.x & (WAVE - 1);
+  DS_LDS float* kin = lds(tm.kin) + lane;
+  // rows on wavefronts 4..6: three different SIMDs, beside wavefronts that
+  // wait, and not that of the smoothness (3)
+  constexpr int ROW0 = 4;
+  const int r = tm.w - ROW0;
+  if (r >= 0 && r < 3) {
+    float4 F[NJ][3];
+#pragma unroll
+    for (int l = 0; l < NJ; ++l)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) F[l][k] = s_frame[3 * l + k];
+    float sn[NJ], cs[NJ];
+    sincos_n<NJ>(q, sn, cs);
+    float R[3] = {r == 0 ? 1.f : 0.f, r == 1 ? 1.f : 0.f, r == 2 ? 1.f : 0.f}, p = 0.f;
+#pragma unroll
+    for (int l = 0; l < NJ; ++l) {
+      frame_row(&F[l][0].x, sn[l], cs[l], R, p);
+      kin[(KIN_ZO + 6 * l + r) * WAVE] = R[2];
+      kin[(KIN_ZO + 6 * l + 3 + r) * WAVE] = p;
+      kin[(KIN_XY + 6 * l + 2 * r) * WAVE] = R[0];
+      kin[(KIN_XY + 6 * l + 2 * r + 1) * WAVE] = R[1];
+    }
+  } else {
+    between();
+  }
+  tm.sync();
+#pragma unroll
+  for (int l = 0; l < NJ; ++l)
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      tw.z[l][r] = kin[(KIN_ZO + 6 * l + r) * WAVE];
+      tw.o[l][r] = kin[(KIN_ZO + 6 * l + 3 + r) * WAVE];
+    }
+}
+
+// A link's frame from the team's rows (R whole).
+__device__ __forceinline__ void team_frame(const Team& tm, const Twists& tw, int l, float* R,
+                                           float* p) {
+  const DS_LDS float* kin = lds(tm.kin) + (threadIdx.x & (WAVE - 1));
+#pragma unroll
+  for (int r = 0; r < 3; ++r) {
+    R[3 * r] = kin[(KIN_XY + 6 * l + 2 * r) * WAVE];
+    R[3 * r + 1] = kin[(KIN_XY + 6 * l + 2 * r + 1) * WAVE];
+    R[3 * r + 2] = tw.z[l][r];
+    p[r] = tw.o[l][r];
+  }
+}
+
+// A sample's coarse minimum.
+__device__ __forceinline__ float coarse_min(const Sampler& S, const float* u) {
+  int ci[3];
+  cell_of(S, u, ci);
+  return coarse_at(S, block_index(S, ci));
+}
+
 // The sweep over the chain for one configuration q: FK, this lane's share
 // of the sphere samples (hinge sum into phisum, min clearance into clr) and,
 // with GRAD, the link wrenches projected on the joint axes into g.  On
 // return R, p hold the frame of link 7 and tw the joint twists.
+// KIN: the twists are there already (a full team's shared kinematics), and
+// R, p are left alone.
+// A sample whose coarse block holds no node nearer than radius + eps (+
+// margin) has a zero hinge (a trilinear blend stays within its corners'
+// range): it loads no record.
 // PIPE (every lane holds at most one sphere of each link, W*L >= spheres
-// per link): the sweep issues each link's record load as soon as its frame
-// exists and consumes the samples afterwards, so one memory round trip
-// covers the whole configuration.  Otherwise each link is processed in
-// chunks of CH gathers right after its frame.
-template <int MODE, bool PIPE>
-__device__ __forceinline__ void sweep(const RobotDev* __restrict__ rb, const ParamsDev& P,
-                                      const Sampler& S, const float* q, int cp, int LW,
-                                      Twists& tw, float* R, float* p, float& phisum, float& clr,
-                                      float* g, int& ng, bool active) {
+// per link): the tests of all links, then their record loads, then the
+// hinges, so one memory round trip covers the whole configuration.
+// Otherwise each link is processed in chunks of CH spheres per lane, with
+// the next link's frame formed while the last chunk's records are on their
+// way.  The tests are straight lines: their table and coarse reads from LDS
+// are in flight together, where a branch per sample made each of them wait
+// for its own two (lanes without a sample go through the motions with the
+// last sphere of the table at the most).
+template <int MODE, bool PIPE, bool KIN>
+__device__ __forceinline__ void sweep(const ParamsDev& P, const Sampler& S, const float* q, int cp,
+                                      int LW, const Team& tm, Twists& tw, float* R, float* p,
+                                      float& phisum, float& clr, float* g, int& ng, bool active) {
   constexpr bool GRAD = (MODE == EV_GRAD);
   // the result pass gathers every sample: the clearance is a minimum over
   // all of them
   const bool SKIP = MODE != EV_RESULT && P.skip;
-  R[0] = 1.f; R[1] = 0.f; R[2] = 0.f; R[3] = 0.f; R[4] = 1.f; R[5] = 0.f;
-  R[6] = 0.f; R[7] = 0.f; R[8] = 1.f;
-  p[0] = p[1] = p[2] = 0.f;
-  // PIPE: the lane's sample of every link (grid position, radius, coarse
-  // minimum, record)
-  float4 pa_[PIPE ? NJ : 1], pz_[PIPE ? NJ : 1];
-  float pu_[PIPE ? NJ : 1][3], pr_[PIPE ? NJ : 1], pcm_[PIPE ? NJ : 1];
-  bool pv_[PIPE ? NJ : 1];
+  const Links ln = S.ln;
+  float sn[NJ], cs[NJ];
+  // the frame of link l from that of its predecessor
+  auto advance = [&](int l) {
+    float F[12];
 #pragma unroll
-  for (int l = 0; l < NJ; ++l) {
-    const float* F = rb->F[l];
-    float A[9], pa[3];
+    for (int r = 0; r < 3; ++r) *reinterpret_cast<float4*>(F + 4 * r) = s_frame[3 * l + r];
 #pragma unroll
-    for (int r = 0; r < 3; ++r) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c)
-        A[3 * r + c] = R[3 * r] * F[c] + R[3 * r + 1] * F[4 + c] + R[3 * r + 2] * F[8 + c];
-      pa[r] = R[3 * r] * F[3] + R[3 * r + 1] * F[7] + R[3 * r + 2] * F[11] + p[r];
-    }
-    float sn, cs;
-    sincosf(q[l], &sn, &cs);
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-      float a0 = A[3 * r], a1 = A[3 * r + 1];
-      R[3 * r] = cs * a0 + sn * a1;
-      R[3 * r + 1] = cs * a1 - sn * a0;
-      R[3 * r + 2] = A[3 * r + 2];
-      p[r] = pa[r];
-    }
-    if (GRAD) tw.put(l, R, p);
-    const int s0 = rb->link_begin[l], s1 = rb->link_begin[l + 1];
-    const bool axis = (rb->axis_links >> l) & 1;   // wave-uniform
-    const LinkGrid lg = link_grid(S, R, p);
-    if (PIPE) {
-      // copy cp takes sphere (cp - rot) mod LW of the link, rot advancing by
-      // the longest link's sphere count from link to link: when there are
-      // more copies than spheres, consecutive links land on different
-      // copies and the samples spread evenly over the wavefronts
-      int idx = cp - (l * rb->max_per_link) % LW;
-      if (idx < 0) idx += LW;
-      const int sk = s0 + idx;
-      pv_[l] = active && sk < s1;   // lanes past the horizon gather nothing
-      if (pv_[l]) {
-        const float4 sp = s_sph[sk];
-        grid_pos(S, lg, axis, R, p, sp, pu_[l]);
-        pr_[l] = sp.w;
-        // the coarse minimum is read here and tested after the chain, so
-        // no link waits for its lookup before the next frame
-        if (SKIP) {
-          int ci[3];
-          cell_of(S, pu_[l], ci);
-          pcm_[l] = coarse_at(S, block_index(S, ci));
-        }
-      }
-      continue;
-    }
-    float FM[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    bool forced = false;   // some sample of this link added a force
-    // chunks of CH spheres per lane (this lane takes every (W*L)-th sphere
-    // of the link): issue every record load of the chunk, then consume them
-    // in sphere order -- CH gathers in flight per lane.  A sample whose
-    // coarse block holds no node nearer than radius + eps (+ margin) has a
-    // zero hinge (a trilinear blend stays within its corners' range): it
-    // loads nothing.
-    for (int s = s0; s < s1; s += LW * CH) {
-      float u[CH][3], rr[CH];
-      int ci[CH][3];
-      float4 ra[CH], rz[CH];
-      bool use[CH];
-#pragma unroll
-      for (int k = 0; k < CH; ++k) {
-        const int sk = s + k * LW + cp;
-        use[k] = active && sk < s1;
-        if (use[k]) {
-          const float4 sp = s_sph[sk];
-          grid_pos(S, lg, axis, R, p, sp, u[k]);
-          cell_of(S, u[k], ci[k]);
-          rr[k] = sp.w;
-          if (SKIP && coarse_at(S, block_index(S, ci[k])) >= sp.w + P.far) {
-            use[k] = false;   // zero hinge, zero gradient
-          } else {
-            const int off = record_offset(S, ci[k]);
-            ra[k] = load_rec(S, off);
-            rz[k] = load_rec(S, off + 16);
-            ++ng;
-          }
-        }
-      }
-#pragma unroll
-      for (int k = 0; k < CH; ++k) {
-        if (use[k])
-          forced |= sphere_term<MODE>(P, S, u[k], ci[k], ra[k], rz[k], rr[k], phisum, clr, FM);
-      }
-      // every load of the chunk has been consumed: saying so keeps the
-      // next chunk's loads in flight together.  (The loads and their uses
-      // sit in separate wavefront-uniform branches, so without it the
-      // compiler cannot tell which of them are outstanding at the loop's
-      // back edge and drains them all before each sphere's loads.)
-      __builtin_amdgcn_s_waitcnt(WAIT_VMEM_ALL);
-    }
-    // a link with no force in this wavefront has a zero wrench everywhere:
-    // its projection would add zeros
-    if (GRAD && __any(forced)) project(tw, l, FM, g);
+    for (int r = 0; r < 3; ++r) frame_row(F, sn[l], cs[l], R + 3 * r, p[r]);
+    tw.put(l, R, p);
+  };
+  if constexpr (!KIN) {
+    sincos_n<NJ>(q, sn, cs);
+    R[0] = 1.f; R[1] = 0.f; R[2] = 0.f; R[3] = 0.f; R[4] = 1.f; R[5] = 0.f;
+    R[6] = 0.f; R[7] = 0.f; R[8] = 1.f;
+    p[0] = p[1] = p[2] = 0.f;
   }
-  if (PIPE) {
-    // issue the record loads of the samples that can reach the hinge
+  if constexpr (PIPE) {
+    // the lane's sample of every link: sphere, grid position, coarse minimum,
+    // record
+    int sk[NJ];
+    float oz[NJ], r[NJ], u[NJ][3], cm[NJ];
+    bool use[NJ];
 #pragma unroll
     for (int l = 0; l < NJ; ++l) {
-      if (pv_[l]) {
-        if (SKIP && pcm_[l] >= pr_[l] + P.far) {
-          pv_[l] = false;   // zero hinge, zero gradient: nothing to add
-        } else {
-          int ci[3];
-          cell_of(S, pu_[l], ci);
-          const int off = record_offset(S, ci);
-          pa_[l] = load_rec(S, off);
-          pz_[l] = load_rec(S, off + 16);
-          ++ng;
-        }
+      // copy cp takes sphere (cp - rot) mod LW of the link (LW: a power of
+      // two), rot advancing by the longest link's sphere count from link to
+      // link: when there are more copies than spheres, consecutive links
+      // land on different copies and the samples spread evenly over the
+      // wavefronts
+      sk[l] = ln.begin(l) + ((cp - l * ln.most()) & (LW - 1));
+      use[l] = active & (sk[l] < ln.begin(l + 1));   // lanes past the horizon gather nothing
+      sk[l] = min(sk[l], ln.last());
+      oz[l] = s_sph[sk[l]].z;
+      r[l] = s_sph[sk[l]].w;
+    }
+#pragma unroll
+    for (int l = 0; l < NJ; ++l) {
+      if constexpr (!KIN) advance(l);
+      axis_pos(link_grid(S, tw.z[l], tw.o[l]), oz[l], u[l]);
+      if (!KIN && !ln.axis(l)) frame_pos(S, R, p, s_sph[sk[l]], u[l]);
+    }
+    if (KIN && !ln.all_axis()) {
+#pragma unroll
+      for (int l = 0; l < NJ; ++l) {
+        if (ln.axis(l)) continue;
+        float Rl[9], pl[3];
+        team_frame(tm, tw, l, Rl, pl);
+        frame_pos(S, Rl, pl, s_sph[sk[l]], u[l]);
+      }
+    }
+#pragma unroll
+    for (int l = 0; l < NJ; ++l) cm[l] = coarse_min(S, u[l]);
+#pragma unroll
+    for (int l = 0; l < NJ; ++l) use[l] &= !(SKIP & (cm[l] >= r[l] + P.far));
+    // issue the record loads of the samples that can reach the hinge
+    float4 ra[NJ], rz[NJ];
+#pragma unroll
+    for (int l = 0; l < NJ; ++l) {
+      if (use[l]) {
+        int ci[3];
+        cell_of(S, u[l], ci);
+        const int off = record_offset(S, ci);
+        ra[l] = load_rec(S, off);
+        rz[l] = load_rec(S, off + 16);
+        ++ng;
       }
     }
 #pragma unroll
     for (int l = 0; l < NJ; ++l) {
       float FM[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
       bool forced = false;
-      if (pv_[l]) {
-        int ci[3];
-        cell_of(S, pu_[l], ci);
-        forced = sphere_term<MODE>(P, S, pu_[l], ci, pa_[l], pz_[l], pr_[l], phisum, clr, FM);
-      }
+      if (use[l])
+        forced = sphere_term<MODE>(P, S, u[l], ra[l], rz[l], r[l], phisum, clr, FM);
       // a link with no force in this wavefront has a zero wrench
       // everywhere: its projection would add zeros
+      if (GRAD && __any(forced)) project(tw, l, FM, g);
+    }
+  } else {
+    constexpr int C = KIN ? 2 : CH;   // (a full team has eight copies at least)
+    if constexpr (!KIN) advance(0);
+#pragma unroll
+    for (int l = 0; l < NJ; ++l) {
+      const int s1 = ln.begin(l + 1);
+      const LinkGrid lg = link_grid(S, tw.z[l], tw.o[l]);
+      if (KIN && !ln.axis(l)) team_frame(tm, tw, l, R, p);
+      float FM[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      bool forced = false;   // some sample of this link added a force
+      // this lane takes every (W*L)-th sphere of the link
+      int s = ln.begin(l);
+      do {
+        int sk[C];
+        float oz[C], r[C], u[C][3], cm[C];
+        bool use[C], some = false;
+        float4 ra[C], rz[C];
+        auto test = [&](auto count) {
+          constexpr int N = decltype(count)::value;
+#pragma unroll
+          for (int k = 0; k < N; ++k) {
+            sk[k] = s + k * LW + cp;
+            use[k] = active & (sk[k] < s1);
+            sk[k] = min(sk[k], ln.last());
+            oz[k] = s_sph[sk[k]].z;
+            r[k] = s_sph[sk[k]].w;
+          }
+#pragma unroll
+          for (int k = 0; k < N; ++k) axis_pos(lg, oz[k], u[k]);
+          if (!ln.axis(l)) {
+#pragma unroll
+            for (int k = 0; k < N; ++k) frame_pos(S, R, p, s_sph[sk[k]], u[k]);
+          }
+#pragma unroll
+          for (int k = 0; k < N; ++k) cm[k] = coarse_min(S, u[k]);
+#pragma unroll
+          for (int k = 0; k < N; ++k) use[k] &= !(SKIP & (cm[k] >= r[k] + P.far));
+        };
+        if (C == 2 || s + 2 * LW < s1) {
+          test(std::integral_constant<int, C>());
+        } else {   // at most two spheres per lane are left
+#pragma unroll
+          for (int k = 2; k < C; ++k) use[k] = false;
+          test(std::integral_constant<int, 2>());
+        }
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+          some |= use[k];
+          if (use[k]) {
+            int ci[3];
+            cell_of(S, u[k], ci);
+            const int off = record_offset(S, ci);
+            ra[k] = load_rec(S, off);
+            rz[k] = load_rec(S, off + 16);
+            ++ng;
+          }
+        }
+        s += LW * C;
+        if constexpr (!KIN)
+          if (l + 1 < NJ && s >= s1) advance(l + 1);
+        if (__any(some)) {
+#pragma unroll
+          for (int k = 0; k < C; ++k)
+            if (use[k])
+              forced |= sphere_term<MODE>(P, S, u[k], ra[k], rz[k], r[k], phisum, clr, FM);
+          // every load of the chunk has been consumed: saying so keeps the
+          // next chunk's loads in flight together.  (The loads and their uses
+          // sit in separate wavefront-uniform branches, so without it the
+          // compiler cannot tell which of them are outstanding at the loop's
+          // back edge and drains them all before each sphere's loads.)
+          __builtin_amdgcn_s_waitcnt(WAIT_VMEM_ALL);
+        }
+      } while (s < s1);
+      // a link with no force in this wavefront has a zero wrench everywhere:
+      // its projection would add zeros
       if (GRAD && __any(forced)) project(tw, l, FM, g);
     }
   }
@@ -737,10 +972,10 @@ __device__ __forceinline__ void sweep(const RobotDev* __restrict__ rb, const Par
 // One evaluation of the objective at this lane's configuration q (its
 // waypoint) and, with swept sub-samples, at the configurations interpolated
 // towards the next waypoint.
-template <int MODE, bool PIPE, bool EXT>
+template <int MODE, bool PIPE, bool EXT, bool KIN>
 __device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
-                                            const ParamsDev& P, const Sampler& S, const Goal& goal,
-                                            const float* q, int t, int T, int G, bool active,
+                                            const ParamsDev& P, const Sampler& S, const float* q,
+                                            int t, int T, int G, bool active,
                                             Team& tm) {
   constexpr bool GRAD = (MODE == EV_GRAD);
   // the L = 64/G lanes holding the same waypoint in each of the W
@@ -775,7 +1010,9 @@ __device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
       }
       Twists tws;
       float ph = 0.f, cl = FLT_MAX;
-      sweep<MODE, PIPE>(rb, P, S, qi, cp, LW, tws, Rs, ps, ph, cl, gi, o.ng, seg);
+      if constexpr (KIN) team_kinematics(rb, tm, qi, tws, []() {});
+      sweep<MODE, PIPE, KIN>(P, S, qi, cp, LW, tm, tws, Rs, ps, ph, cl, gi, o.ng, seg);
+      if constexpr (KIN) tm.sync();   // the frames are read before the next ones are formed
       if (seg) {
         phisum += ph;
         clr = fminf(clr, cl);
@@ -794,17 +1031,6 @@ __device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
       }
     }
   }
-  float R[9], p[3];
-  Twists tw;
-  sweep<MODE, PIPE>(rb, P, S, q, cp, LW, tw, R, p, phisum, clr, o.g, o.ng, active);
-  // collision cost share: world hinge sum, plus the self-collision pairs
-  // when that term is on
-  float coll = P.wc * phisum;
-  if (EXT && P.ws != 0.f) {
-    float selfsum = 0.f;
-    self_collision<MODE>(rb, P, q, cp, LW, selfsum, clr, o.g);
-    coll += P.ws * selfsum;
-  }
   // goal pose, joint limits and smoothness: the same for every copy of the
   // waypoint, so one wavefront of the team computes each and only its first
   // copy adds them to its share before the sums below -- the goal on the
@@ -815,16 +1041,59 @@ __device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
   const int xg = (MODE == EV_RESULT || tm.W == 1) ? 0 : 1;
   const int xl = (MODE == EV_RESULT || tm.W < 3) ? xg : 2;
   const int xs = (MODE == EV_RESULT || tm.W < 4) ? xl : 3;
-  if (tm.w == xg || tm.w == xl || tm.w == xs) {
+  // a full team's gradient pass forms the goal on the last wavefront, which
+  // leaves it in LDS for the sums to add to the second wavefront's share
+  constexpr bool FAR_GOAL = KIN && GRAD;
+  const int wg = FAR_GOAL ? MAX_TEAM - 1 : xg;
+  float ge[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) ge[j] = 0.f;
+  float extra_g = 0.f, extra_l = 0.f;
+  float R[9], p[3];
+  Twists tw;
+  if constexpr (KIN) {
+    static_assert(MODE != EV_RESULT, "the result pass keeps its terms on one wavefront");
+    // the limits and the smoothness on their own wavefronts while the frames
+    // are formed
+    team_kinematics(rb, tm, q, tw, [&]() {
+      if (tm.w == xl) extra_l = limits<GRAD>(rb, P, q, ge);
+      if (tm.w == xs) extra_l += smoothness<GRAD>(P, q, t, T, ge);
+    });
+  }
+  sweep<MODE, PIPE, KIN>(P, S, q, cp, LW, tm, tw, R, p, phisum, clr, o.g, o.ng, active);
+  // collision cost share: world hinge sum, plus the self-collision pairs
+  // when that term is on
+  float coll = P.wc * phisum;
+  if (EXT && P.ws != 0.f) {
+    float selfsum = 0.f;
+    self_collision<MODE>(rb, P, q, cp, LW, selfsum, clr, o.g);
+    coll += P.ws * selfsum;
+  }
+  if (tm.w == wg || tm.w == xl || tm.w == xs) {
     const bool first = lane < G;
     const bool last = (t == T - 1);
-    float ge[NJ];
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) ge[j] = 0.f;
-    float extra_g = 0.f, extra_l = 0.f;
-    if (tm.w == xg) {
+    if (tm.w == wg) {
     // end effector and goal pose
-    const float* E = rb->Fee;
+    // (a full team: the last waypoint's frame in every lane, and joint i's
+    // part of the gradient on lane i)
+    float zl[3], ol[3];
+    if constexpr (KIN) {
+      const DS_LDS float* kin = lds(tm.kin) + (T - 1);
+      const int i = min(lane, NJ - 1);
+#pragma unroll
+      for (int r = 0; r < 3; ++r) {
+        R[3 * r] = kin[(KIN_XY + 6 * (NJ - 1) + 2 * r) * WAVE];
+        R[3 * r + 1] = kin[(KIN_XY + 6 * (NJ - 1) + 2 * r + 1) * WAVE];
+        R[3 * r + 2] = kin[(KIN_ZO + 6 * (NJ - 1) + r) * WAVE];
+        p[r] = kin[(KIN_ZO + 6 * (NJ - 1) + 3 + r) * WAVE];
+        zl[r] = kin[(KIN_ZO + 6 * i + r) * WAVE];
+        ol[r] = kin[(KIN_ZO + 6 * i + 3 + r) * WAVE];
+      }
+    }
+    const Goal goal = get_goal();
+    float E[12];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) *reinterpret_cast<float4*>(E + 4 * r) = s_frame[3 * NJ + r];
     float Re[9], pe[3];
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
@@ -838,8 +1107,8 @@ __device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
 #pragma unroll
     for (int k = 0; k < 9; ++k) tr += goal.Rd[k] * Re[k];
     const float goal_cost = P.wp * (ex * ex + ey * ey + ez * ez) + P.wr * (3.f - tr) * 0.25f;
-    extra_g = last ? goal_cost : 0.f;
-    if (GRAD && last) {
+    extra_g = !FAR_GOAL && last ? goal_cost : 0.f;
+    if (GRAD && (KIN || last)) {
       // force 2 w_p e at p_ee and torque -(w_r/4) w, w = vee(M - M^T), M = R_ee R_d^T
       float M[9];
 #pragma unroll
@@ -851,15 +1120,24 @@ __device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
       float wx = M[5] - M[7], wy = M[6] - M[2], wz = M[1] - M[3];
       float k2 = 2.f * P.wp, k4 = -0.25f * P.wr;
       float fx = k2 * ex, fy = k2 * ey, fz = k2 * ez;
-#pragma unroll
-      for (int i = 0; i < NJ; ++i) {
-        float zi[3], oi[3];
-        tw.get(i, zi, oi);
+      auto part = [&](const float* zi, const float* oi) {
         float rx = pe[0] - oi[0], ry = pe[1] - oi[1], rz = pe[2] - oi[2];
         float tx = ry * fz - rz * fy + k4 * wx;
         float ty = rz * fx - rx * fz + k4 * wy;
         float tz = rx * fy - ry * fx + k4 * wz;
-        ge[i] += zi[0] * tx + zi[1] * ty + zi[2] * tz;
+        return zi[0] * tx + zi[1] * ty + zi[2] * tz;
+      };
+      if constexpr (KIN) {
+        DS_LDS float* out = lds(tm.kin) + KIN_GOAL * WAVE;
+        if (lane < NJ) out[1 + lane] = part(zl, ol);
+        if (lane == NJ) out[0] = goal_cost;
+      } else {
+#pragma unroll
+        for (int i = 0; i < NJ; ++i) {
+          float zi[3], oi[3];
+          tw.get(i, zi, oi);
+          ge[i] += part(zi, oi);
+        }
       }
     }
     if (MODE == EV_RESULT) {
@@ -876,19 +1154,10 @@ __device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
       o.rerr = atan2f(0.5f * sqrtf(wx * wx + wy * wy + wz * wz), 0.5f * (tr - 1.f));
     }
     }
-    if (tm.w == xl) {
-    // joint limits
-    float lim = 0.f;
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      float hi = q[j] - rb->qhi[j], lo = rb->qlo[j] - q[j];
-      float hp = fmaxf(hi, 0.f), lp = fmaxf(lo, 0.f);
-      lim += hp * hp + lp * lp;
-      if (GRAD) ge[j] += 2.f * P.wl * (hp - lp);
+    if constexpr (!KIN) {
+      if (tm.w == xl) extra_l = limits<GRAD>(rb, P, q, ge);
+      if (tm.w == xs) extra_l += smoothness<GRAD>(P, q, t, T, ge);
     }
-    extra_l = P.wl * lim;
-    }
-    if (tm.w == xs) extra_l += smoothness<GRAD>(P, q, t, T, ge);
     coll += first ? extra_l + extra_g : 0.f;
     if (GRAD) {
 #pragma unroll
@@ -921,11 +1190,26 @@ __device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
 #pragma unroll
     for (int j = 0; j < NJ; ++j) mine[(1 + j) * WAVE] = o.g[j];
     tm.sync();
-    for (int cc = tm.w; cc < NC; cc += tm.W) {
-      float v = base[cc * WAVE];
-      for (int u = 1; u < tm.W; ++u) v += base[(u * PART + cc) * WAVE];
+    if constexpr (KIN) {
+      // a full team: one component per wavefront, its shares read together
+      static_assert(NC == MAX_TEAM, "one component per wavefront");
+      float sh[MAX_TEAM];
+#pragma unroll
+      for (int u = 0; u < MAX_TEAM; ++u) sh[u] = base[(u * PART + tm.w) * WAVE];
+      const float goal_part = lds(tm.kin)[KIN_GOAL * WAVE + tm.w];
+      sh[1] += lane == T - 1 ? goal_part : 0.f;
+      float v = sh[0];
+#pragma unroll
+      for (int u = 1; u < MAX_TEAM; ++u) v += sh[u];
       for (int off = G; off < WAVE; off <<= 1) v = xor_reduce<OpSum>(v, off);
-      base[cc * WAVE] = v;
+      base[tm.w * WAVE] = v;
+    } else {
+      for (int cc = tm.w; cc < NC; cc += tm.W) {
+        float v = base[cc * WAVE];
+        for (int u = 1; u < tm.W; ++u) v += base[(u * PART + cc) * WAVE];
+        for (int off = G; off < WAVE; off <<= 1) v = xor_reduce<OpSum>(v, off);
+        base[cc * WAVE] = v;
+      }
     }
     tm.sync();
     phisum = base[0];
@@ -939,12 +1223,21 @@ __device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
     if (MODE == EV_RESULT) mine[(1 + NJ) * WAVE] = clr;
     tm.sync();
     const float* all = tm.lds + (tm.buf * tm.W * PART) * WAVE + lane;
-    phisum = all[0];
-    if (MODE == EV_RESULT) clr = all[(1 + NJ) * WAVE];
-    for (int v = 1; v < tm.W; ++v) {
-      const float* pv = all + v * PART * WAVE;
-      phisum += pv[0];
-      if (MODE == EV_RESULT) clr = fminf(clr, pv[(1 + NJ) * WAVE]);
+    if constexpr (KIN) {
+      float sh[MAX_TEAM];
+#pragma unroll
+      for (int u = 0; u < MAX_TEAM; ++u) sh[u] = all[u * PART * WAVE];
+      phisum = sh[0];
+#pragma unroll
+      for (int u = 1; u < MAX_TEAM; ++u) phisum += sh[u];
+    } else {
+      phisum = all[0];
+      if (MODE == EV_RESULT) clr = all[(1 + NJ) * WAVE];
+      for (int v = 1; v < tm.W; ++v) {
+        const float* pv = all + v * PART * WAVE;
+        phisum += pv[0];
+        if (MODE == EV_RESULT) clr = fminf(clr, pv[(1 + NJ) * WAVE]);
+      }
     }
     tm.buf ^= 1;
   }
@@ -958,19 +1251,30 @@ __device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
 }
 
 // The evaluation form for this team: PIPE when every lane holds at most one
-// sphere per link.
+// sphere per link; shared kinematics for a full team.
 template <int MODE, bool EXT>
 __device__ __forceinline__ EvalOut eval_any(bool pipe, const RobotDev* __restrict__ rb,
-                                            const ParamsDev& P, const Sampler& S, const Goal& goal,
-                                            const float* q, int t, int T, int G, bool active,
+                                            const ParamsDev& P, const Sampler& S, const float* q,
+                                            int t, int T, int G, bool active,
                                             Team& tm) {
-  if (pipe) return evaluate<MODE, true, EXT>(rb, P, S, goal, q, t, T, G, active, tm);
-  return evaluate<MODE, false, EXT>(rb, P, S, goal, q, t, T, G, active, tm);
+  if constexpr (MODE != EV_RESULT) {
+    if (tm.kin) {
+      if (pipe) return evaluate<MODE, true, EXT, true>(rb, P, S, q, t, T, G, active, tm);
+      return evaluate<MODE, false, EXT, true>(rb, P, S, q, t, T, G, active, tm);
+    }
+  }
+  if (pipe) return evaluate<MODE, true, EXT, false>(rb, P, S, q, t, T, G, active, tm);
+  return evaluate<MODE, false, EXT, false>(rb, P, S, q, t, T, G, active, tm);
 }
 
 __device__ __forceinline__ bool use_pipe(const RobotDev* __restrict__ rb, const Team& tm, int G) {
   return tm.W * (WAVE / G) >= rb->max_per_link;
 }
 
+// dynamic LDS of a team's evaluation: its partial sums (double buffered) and,
+// for a full team, the shared kinematics
+inline size_t eval_lds(int W) {
+  return W > 1 ? ((size_t)2 * W * PART + (W == MAX_TEAM ? KIN_ROWS : 0)) * WAVE * sizeof(float) : 0;
+}
 }  // namespace
 }  // namespace dsk

@@ -154,12 +154,11 @@ __global__ void k_zero_i32(int* p, int n) {
 }  // namespace
 
 int team_block(int W) { return (W > 1 ? W : WAVES_PER_BLOCK) * WAVE; }
-// dynamic LDS of an optimiser workgroup: a team's partial sums (double
-// buffered), history ring, coarse table and direction broadcast; single
-// wavefronts: one coarse table each
+// dynamic LDS of an optimiser workgroup: a team's evaluation, history ring,
+// coarse table and direction broadcast; single wavefronts: one coarse table
+// each
 size_t team_lds(int W) {
-  return W > 1 ? ((size_t)2 * W * PART * WAVE + H_FLOATS + COARSE_FLOATS + DL_FLOATS) *
-                     sizeof(float)
+  return W > 1 ? eval_lds(W) + (H_FLOATS + COARSE_FLOATS + DL_FLOATS) * sizeof(float)
                : (size_t)WAVES_PER_BLOCK * COARSE_FLOATS * sizeof(float);
 }
 

@@ -12,7 +12,6 @@ struct TileCtx {
   ParamsDev P;
   const ProbDev* pb;
   Sampler S;
-  Goal goal;
   DS_GLOBAL float* st;
   int lane, G, t, T, seed;
   bool owner;    // first copy of the waypoint: writes outputs and traces
@@ -372,7 +371,7 @@ __device__ __forceinline__ void trace_scalar(float* buf, const TileCtx& c, int k
 // Final per-seed results and output trajectory.
 template <bool EXT>
 __device__ __forceinline__ int finalize(const TileCtx& c, const float* x, Team& tm) {
-  EvalOut r = eval_any<EV_RESULT, EXT>(c.pipe, c.rb, c.P, c.S, c.goal, x, c.t, c.T, c.G, c.active, tm);
+  EvalOut r = eval_any<EV_RESULT, EXT>(c.pipe, c.rb, c.P, c.S, x, c.t, c.T, c.G, c.active, tm);
   float Jr = grp_sum(r.cost, c.G);
   float clr = grp_min(c.active ? r.clr : FLT_MAX, c.G);
   float perr = grp_sum((c.t == c.T - 1) ? r.perr : 0.f, c.G);
@@ -460,8 +459,8 @@ __device__ __forceinline__ void run_tile(const RobotDev* __restrict__ rb, const 
   c.rb = rb;
   c.P = *pp;
   c.pb = probs + td.prob;
-  c.S = make_sampler(c.pb->sc);
-  c.goal = make_goal(*c.pb);
+  c.S = make_sampler(c.pb->sc, rb);
+  put_goal(*c.pb);
   c.st = glb(td.state);
   c.lane = threadIdx.x & (WAVE - 1);
   c.G = td.G;
@@ -557,7 +556,7 @@ __device__ __forceinline__ void run_tile(const RobotDev* __restrict__ rb, const 
       phase = PH_TRIAL;
     }
     // the one cost+gradient evaluation of this pass
-    EvalOut e = eval_any<EV_GRAD, EXT>(c.pipe, rb, c.P, c.S, c.goal, xe, c.t, c.T, c.G, c.active, tm);
+    EvalOut e = eval_any<EV_GRAD, EXT>(c.pipe, rb, c.P, c.S, xe, c.t, c.T, c.G, c.active, tm);
     ++evg;
     ngath += e.ng;
     const float Je = grp_sum(e.cost, c.G);
@@ -583,7 +582,7 @@ __device__ __forceinline__ void run_tile(const RobotDev* __restrict__ rb, const 
         float xk[NJ];
 #pragma unroll
         for (int j = 0; j < NJ; ++j) xk[j] = x[j] + al * d[j];
-        EvalOut ek = eval_any<EV_COST, EXT>(c.pipe, rb, c.P, c.S, c.goal, xk, c.t, c.T, c.G, c.active,
+        EvalOut ek = eval_any<EV_COST, EXT>(c.pipe, rb, c.P, c.S, xk, c.t, c.T, c.G, c.active,
                                        tm);
         ++evc;
         ngath += ek.ng;
@@ -713,7 +712,7 @@ k_optimize(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp,
            const int* __restrict__ xcd_ranges) {
   extern __shared__ float s_dyn[];
   __shared__ int s_tile;
-  stage_spheres(rb);
+  stage_robot(rb);
   const int lane = threadIdx.x & (WAVE - 1);
   const int nt = n_tiles_dev ? *n_tiles_dev : n_tiles;
   if (max_iters_dev) max_iters = *max_iters_dev;   // serving: set per replay
@@ -722,6 +721,9 @@ k_optimize(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp,
   // wave-uniform (scalar) index, so loops over a wavefront's share stay scalar
   tm.w = TEAM ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE)) : 0;
   tm.lds = s_dyn;
+  tm.kin = TEAM && tm.W == MAX_TEAM
+               ? s_dyn + 2 * tm.W * PART * WAVE + H_FLOATS + COARSE_FLOATS + DL_FLOATS
+               : nullptr;
   tm.buf = 0;
   for (;;) {
     int mine = 0;
