@@ -295,6 +295,14 @@ __device__ __forceinline__ LinkGrid link_grid(const Sampler& S, const float* z, 
   return g;
 }
 
+// World centre of a sphere at oz on its link's z axis, per component, as the
+// full product gives it with zeros in x and y (rounded before p is added).
+__device__ __forceinline__ float axis_centre(float z, float oz, float p) {
+#pragma clang fp contract(off)
+  const float c = z * oz;
+  return c + p;
+}
+
 // Grid position of a sphere at oz on its link's z axis ...
 __device__ __forceinline__ void axis_pos(const LinkGrid& g, float oz, float* u) {
 #pragma unroll
@@ -567,106 +575,6 @@ __device__ __forceinline__ void project(const Twists& tw, int l, const float* FM
   }
 }
 
-// Self-collision share of this lane (App. A.6 C_self): every pair of spheres
-// on links at least two apart, hinge on D = |c_a - c_b| - r_a - r_b; the
-// pairs of each link pair are split over the W*L copies.  The sweep keeps
-// the seven link frames; forces go into per-link wrenches that are projected
-// on the joint axes at the end.
-template <int MODE>
-__device__ __attribute__((noinline)) void self_collision(const RobotDev* __restrict__ rb,
-                                                         const ParamsDev& P, const float* q,
-                                                         int cp, int LW, float& selfsum,
-                                                         float& clr, float* g) {
-  constexpr bool GRAD = (MODE == EV_GRAD);
-  float Rf[NJ][9], pf[NJ][3];
-  float R[9] = {1.f, 0.f, 0.f, 0.f, 1.f, 0.f, 0.f, 0.f, 1.f};
-  float p[3] = {0.f, 0.f, 0.f};
-#pragma unroll
-  for (int l = 0; l < NJ; ++l) {
-    const float* F = rb->F[l];
-    float A[9], pa[3];
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c)
-        A[3 * r + c] = R[3 * r] * F[c] + R[3 * r + 1] * F[4 + c] + R[3 * r + 2] * F[8 + c];
-      pa[r] = R[3 * r] * F[3] + R[3 * r + 1] * F[7] + R[3 * r + 2] * F[11] + p[r];
-    }
-    float sn, cs;
-    sincosf(q[l], &sn, &cs);
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-      float a0 = A[3 * r], a1 = A[3 * r + 1];
-      R[3 * r] = cs * a0 + sn * a1;
-      R[3 * r + 1] = cs * a1 - sn * a0;
-      R[3 * r + 2] = A[3 * r + 2];
-      p[r] = pa[r];
-    }
-#pragma unroll
-    for (int k = 0; k < 9; ++k) Rf[l][k] = R[k];
-    pf[l][0] = p[0]; pf[l][1] = p[1]; pf[l][2] = p[2];
-  }
-  float FM[NJ][6];
-#pragma unroll
-  for (int l = 0; l < NJ; ++l)
-#pragma unroll
-    for (int k = 0; k < 6; ++k) FM[l][k] = 0.f;
-#pragma unroll
-  for (int la = 0; la < NJ; ++la) {
-#pragma unroll
-    for (int lb = la + 2; lb < NJ; ++lb) {
-      const int a0 = rb->link_begin[la], na = rb->link_begin[la + 1] - a0;
-      const int b0 = rb->link_begin[lb], nb = rb->link_begin[lb + 1] - b0;
-      for (int k = cp; k < na * nb; k += LW) {
-        const int ia = k / nb, ib = k - ia * nb;
-        const float4 sa = s_sph[a0 + ia], sb = s_sph[b0 + ib];
-        float ca[3], cb[3];
-#pragma unroll
-        for (int r = 0; r < 3; ++r) {
-          ca[r] = Rf[la][3 * r] * sa.x + Rf[la][3 * r + 1] * sa.y + Rf[la][3 * r + 2] * sa.z + pf[la][r];
-          cb[r] = Rf[lb][3 * r] * sb.x + Rf[lb][3 * r + 1] * sb.y + Rf[lb][3 * r + 2] * sb.z + pf[lb][r];
-        }
-        float dx = ca[0] - cb[0], dy = ca[1] - cb[1], dz = ca[2] - cb[2];
-        float dist = sqrtf(dx * dx + dy * dy + dz * dz);
-        float D = dist - sa.w - sb.w;
-        float De = D - P.eps;
-        float phi = (D < P.eps) ? De * De * P.half_inv_eps : 0.f;
-        phi = (D < 0.f) ? 0.5f * P.eps - D : phi;
-        selfsum += phi;
-        if (MODE == EV_RESULT) clr = fminf(clr, D);
-        if (GRAD) {
-          float dphi = (D < P.eps) ? De * P.inv_eps : 0.f;
-          dphi = (D < 0.f) ? -1.f : dphi;
-          float w = (dist > 0.f) ? P.ws * dphi / dist : 0.f;
-          float fx = w * dx, fy = w * dy, fz = w * dz;
-          FM[la][0] += fx; FM[la][1] += fy; FM[la][2] += fz;
-          FM[la][3] += ca[1] * fz - ca[2] * fy;
-          FM[la][4] += ca[2] * fx - ca[0] * fz;
-          FM[la][5] += ca[0] * fy - ca[1] * fx;
-          FM[lb][0] -= fx; FM[lb][1] -= fy; FM[lb][2] -= fz;
-          FM[lb][3] -= cb[1] * fz - cb[2] * fy;
-          FM[lb][4] -= cb[2] * fx - cb[0] * fz;
-          FM[lb][5] -= cb[0] * fy - cb[1] * fx;
-        }
-      }
-    }
-  }
-  if (GRAD) {
-#pragma unroll
-    for (int l = 0; l < NJ; ++l) {
-#pragma unroll
-      for (int i = 0; i <= l; ++i) {
-        const float zi[3] = {Rf[i][2], Rf[i][5], Rf[i][8]};
-        const float* oi = pf[i];
-        float tx = FM[l][3] - (oi[1] * FM[l][2] - oi[2] * FM[l][1]);
-        float ty = FM[l][4] - (oi[2] * FM[l][0] - oi[0] * FM[l][2]);
-        float tz = FM[l][5] - (oi[0] * FM[l][1] - oi[1] * FM[l][0]);
-        g[i] += zi[0] * tx + zi[1] * ty + zi[2] * tz;
-      }
-    }
-  }
-}
-
 // Sines and cosines of N joint angles.  Below 2^17 the library's sincosf is a
 // short straight line; above it reduces the argument by a long one, and with
 // both in the code every call is two branches around it, which cost about as
@@ -776,6 +684,132 @@ __device__ __forceinline__ void team_frame(const Team& tm, const Twists& tw, int
     R[3 * r + 2] = tw.z[l][r];
     p[r] = tw.o[l][r];
   }
+}
+
+// Self-collision share of this lane (App. A.6 C_self): every pair of spheres
+// on links at least two apart, hinge on D = |c_a - c_b| - r_a - r_b; the
+// pairs of each link pair are split over the W*L copies.  Forces go into
+// per-link wrenches that are projected on the joint axes at the end.
+// Inlined, with the frames of the sweep before it: as a function of its own it
+// formed them again and, taking the parameters by reference, put the whole
+// tile context in scratch memory, where every gather of the sweep read its
+// descriptor lane by lane.  A call is bound by latency and instruction fetch:
+// 64 trajectories of 47 waypoints with 56 spheres and two swept samples, with
+// gradient: 92 us as that function, 39 us here.
+// Spheres on their links' axes (AXIS) need the twists only; else xy[l] holds
+// the first two columns of R of link l, by rows.
+// A pair's distance is compared squared first, with a margin well above its
+// rounding: pairs out of reach in the whole wavefront (they add zeros) take
+// neither the root nor the rest.  (The negated test lets NaN through.)
+template <int MODE, bool AXIS>
+__device__ __forceinline__ void self_pairs(const ParamsDev& P, const Links& ln, const Twists& tw,
+                                           const float (*xy)[6], int cp, int LW, bool active,
+                                           float& selfsum, float& clr, float* g) {
+  constexpr bool GRAD = (MODE == EV_GRAD);
+  constexpr float MARGIN = 1.00001f;
+  float FM[NJ][6];
+#pragma unroll
+  for (int l = 0; l < NJ; ++l)
+#pragma unroll
+    for (int k = 0; k < 6; ++k) FM[l][k] = 0.f;
+  auto centre = [&](int l, float4 sp, float* c) {
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      if constexpr (AXIS)
+        c[r] = axis_centre(tw.z[l][r], sp.z, tw.o[l][r]);
+      else
+        c[r] = xy[l][2 * r] * sp.x + xy[l][2 * r + 1] * sp.y + tw.z[l][r] * sp.z + tw.o[l][r];
+    }
+  };
+#pragma unroll
+  for (int la = 0; la < NJ; ++la) {
+#pragma unroll
+    for (int lb = la + 2; lb < NJ; ++lb) {
+      const int a0 = ln.begin(la), na = ln.begin(la + 1) - a0;
+      const int b0 = ln.begin(lb), nb = ln.begin(lb + 1) - b0;
+      // k / nb below: exact, the quotient being under 256 and k + 1/2 at
+      // least 1/(2 nb) of a step away from the next whole number
+      const float inb = __builtin_amdgcn_rcpf((float)nb);
+      for (int k0 = 0; k0 < na * nb; k0 += LW) {
+        const int k = min(k0 + cp, na * nb - 1);
+        const int ia = (int)(((float)k + 0.5f) * inb), ib = k - ia * nb;
+        const float4 sa = s_sph[a0 + ia], sb = s_sph[b0 + ib];
+        float ca[3], cb[3];
+        centre(la, sa, ca);
+        centre(lb, sb, cb);
+        float dx = ca[0] - cb[0], dy = ca[1] - cb[1], dz = ca[2] - cb[2];
+        const float d2 = dx * dx + dy * dy + dz * dz;
+        const float reach = sa.w + sb.w + P.eps;
+        const bool mine = active & (k0 + cp < na * nb);
+        const bool near = mine & (MODE == EV_RESULT || !(d2 >= reach * reach * MARGIN));
+        if (!__any(near)) continue;
+        if (near) {
+          float dist = sqrtf(d2);
+          float D = dist - sa.w - sb.w;
+          float De = D - P.eps;
+          float phi = (D < P.eps) ? De * De * P.half_inv_eps : 0.f;
+          phi = (D < 0.f) ? 0.5f * P.eps - D : phi;
+          selfsum += phi;
+          if (MODE == EV_RESULT) clr = fminf(clr, D);
+          if (GRAD) {
+            float dphi = (D < P.eps) ? De * P.inv_eps : 0.f;
+            dphi = (D < 0.f) ? -1.f : dphi;
+            float w = (dist > 0.f) ? P.ws * dphi / dist : 0.f;
+            float fx = w * dx, fy = w * dy, fz = w * dz;
+            FM[la][0] += fx; FM[la][1] += fy; FM[la][2] += fz;
+            FM[la][3] += ca[1] * fz - ca[2] * fy;
+            FM[la][4] += ca[2] * fx - ca[0] * fz;
+            FM[la][5] += ca[0] * fy - ca[1] * fx;
+            FM[lb][0] -= fx; FM[lb][1] -= fy; FM[lb][2] -= fz;
+            FM[lb][3] -= cb[1] * fz - cb[2] * fy;
+            FM[lb][4] -= cb[2] * fx - cb[0] * fz;
+            FM[lb][5] -= cb[0] * fy - cb[1] * fx;
+          }
+        }
+      }
+    }
+  }
+  if (GRAD) {
+#pragma unroll
+    for (int l = 0; l < NJ; ++l) project(tw, l, FM[l], g);
+  }
+}
+
+// ... with the frames of q: the team's rows, or the whole chain again where
+// some sphere lies off its link's axis.
+template <int MODE, bool KIN>
+__device__ __forceinline__ void self_collision(const ParamsDev& P, const Links& ln, const Team& tm,
+                                               const float* q, const Twists& tw, int cp, int LW,
+                                               bool active, float& selfsum, float& clr, float* g) {
+  if (ln.all_axis()) {
+    self_pairs<MODE, true>(P, ln, tw, nullptr, cp, LW, active, selfsum, clr, g);
+    return;
+  }
+  float xy[NJ][6];
+  if constexpr (KIN) {
+    const DS_LDS float* kin = lds(tm.kin) + (threadIdx.x & (WAVE - 1));
+#pragma unroll
+    for (int l = 0; l < NJ; ++l)
+#pragma unroll
+      for (int k = 0; k < 6; ++k) xy[l][k] = kin[(KIN_XY + 6 * l + k) * WAVE];
+  } else {
+    float sn[NJ], cs[NJ];
+    sincos_n<NJ>(q, sn, cs);
+    float R[9] = {1.f, 0.f, 0.f, 0.f, 1.f, 0.f, 0.f, 0.f, 1.f}, p[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+    for (int l = 0; l < NJ; ++l) {
+      float F[12];
+#pragma unroll
+      for (int r = 0; r < 3; ++r) *reinterpret_cast<float4*>(F + 4 * r) = s_frame[3 * l + r];
+#pragma unroll
+      for (int r = 0; r < 3; ++r) {
+        frame_row(F, sn[l], cs[l], R + 3 * r, p[r]);
+        xy[l][2 * r] = R[3 * r];
+        xy[l][2 * r + 1] = R[3 * r + 1];
+      }
+    }
+  }
+  self_pairs<MODE, false>(P, ln, tw, xy, cp, LW, active, selfsum, clr, g);
 }
 
 // A sample's coarse minimum.
@@ -990,47 +1024,6 @@ __device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
 #pragma unroll
   for (int j = 0; j < NJ; ++j) o.g[j] = 0.f;
   float phisum = 0.f, clr = FLT_MAX;
-  if (EXT && P.nsub > 0) {
-    // swept collision: q + tau (q_next - q), tau = i / (nsub + 1); the
-    // gradient splits (1 - tau) here and tau onto the next waypoint
-    float qn[NJ], gsh[NJ];
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      qn[j] = __shfl_down(q[j], 1);
-      gsh[j] = 0.f;
-    }
-    const bool seg = active && t <= T - 2;
-    for (int i = 1; i <= P.nsub; ++i) {
-      const float tau = (float)i / (float)(P.nsub + 1);
-      float qi[NJ], gi[NJ], Rs[9], ps[3];
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        qi[j] = q[j] + tau * (qn[j] - q[j]);
-        gi[j] = 0.f;
-      }
-      Twists tws;
-      float ph = 0.f, cl = FLT_MAX;
-      if constexpr (KIN) team_kinematics(rb, tm, qi, tws, []() {});
-      sweep<MODE, PIPE, KIN>(P, S, qi, cp, LW, tm, tws, Rs, ps, ph, cl, gi, o.ng, seg);
-      if constexpr (KIN) tm.sync();   // the frames are read before the next ones are formed
-      if (seg) {
-        phisum += ph;
-        clr = fminf(clr, cl);
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-          o.g[j] += (1.f - tau) * gi[j];
-          gsh[j] += tau * gi[j];
-        }
-      }
-    }
-    if (GRAD) {
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        float up = __shfl_up(gsh[j], 1);
-        o.g[j] += (t >= 1) ? up : 0.f;
-      }
-    }
-  }
   // goal pose, joint limits and smoothness: the same for every copy of the
   // waypoint, so one wavefront of the team computes each and only its first
   // copy adds them to its share before the sums below -- the goal on the
@@ -1051,22 +1044,77 @@ __device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
   float extra_g = 0.f, extra_l = 0.f;
   float R[9], p[3];
   Twists tw;
-  if constexpr (KIN) {
-    static_assert(MODE != EV_RESULT, "the result pass keeps its terms on one wavefront");
-    // the limits and the smoothness on their own wavefronts while the frames
-    // are formed
-    team_kinematics(rb, tm, q, tw, [&]() {
-      if (tm.w == xl) extra_l = limits<GRAD>(rb, P, q, ge);
-      if (tm.w == xs) extra_l += smoothness<GRAD>(P, q, t, T, ge);
-    });
+  static_assert(!KIN || MODE != EV_RESULT, "the result pass keeps its terms on one wavefront");
+  // the limits and the smoothness of a full team on their own wavefronts while
+  // the frames are formed
+  auto own_terms = [&]() {
+    if (tm.w == xl) extra_l = limits<GRAD>(rb, P, q, ge);
+    if (tm.w == xs) extra_l += smoothness<GRAD>(P, q, t, T, ge);
+  };
+  if constexpr (!EXT) {
+    if constexpr (KIN) team_kinematics(rb, tm, q, tw, own_terms);
+    sweep<MODE, PIPE, KIN>(P, S, q, cp, LW, tm, tw, R, p, phisum, clr, o.g, o.ng, active);
+  } else {
+    // swept collision: q + tau (q_next - q), tau = i / (nsub + 1), i = 1 ..
+    // nsub; the gradient splits (1 - tau) here and tau onto the next
+    // waypoint.  Then the waypoint itself, by the same code (a second copy of
+    // it would not fit the instruction cache beside the first).
+    float qn[NJ], gsh[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      qn[j] = __shfl_down(q[j], 1);
+      gsh[j] = 0.f;
+    }
+    const bool seg = active && t <= T - 2;
+#pragma unroll 1
+    for (int i = 1;; ++i) {
+      const bool own = i > P.nsub;
+      const float tau = (float)i / (float)(P.nsub + 1);
+      float qi[NJ], gi[NJ];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        qi[j] = own ? q[j] : q[j] + tau * (qn[j] - q[j]);
+        gi[j] = own ? o.g[j] : 0.f;
+      }
+      float ph = own ? phisum : 0.f, cl = own ? clr : FLT_MAX;
+      if constexpr (KIN) {
+        team_kinematics(rb, tm, qi, tw, [&]() {
+          if (own) own_terms();
+        });
+      }
+      sweep<MODE, PIPE, KIN>(P, S, qi, cp, LW, tm, tw, R, p, ph, cl, gi, o.ng, own ? active : seg);
+      if (own) {
+        phisum = ph;
+        clr = cl;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) o.g[j] = gi[j];
+        break;
+      }
+      if constexpr (KIN) tm.sync();   // the frames are read before the next ones are formed
+      if (seg) {
+        phisum += ph;
+        clr = fminf(clr, cl);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          o.g[j] += (1.f - tau) * gi[j];
+          gsh[j] += tau * gi[j];
+        }
+      }
+      if (GRAD && i == P.nsub) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          float up = __shfl_up(gsh[j], 1);
+          o.g[j] += (t >= 1) ? up : 0.f;
+        }
+      }
+    }
   }
-  sweep<MODE, PIPE, KIN>(P, S, q, cp, LW, tm, tw, R, p, phisum, clr, o.g, o.ng, active);
   // collision cost share: world hinge sum, plus the self-collision pairs
   // when that term is on
   float coll = P.wc * phisum;
   if (EXT && P.ws != 0.f) {
     float selfsum = 0.f;
-    self_collision<MODE>(rb, P, q, cp, LW, selfsum, clr, o.g);
+    self_collision<MODE, KIN>(P, S.ln, tm, q, tw, cp, LW, active, selfsum, clr, o.g);
     coll += P.ws * selfsum;
   }
   if (tm.w == wg || tm.w == xl || tm.w == xs) {
