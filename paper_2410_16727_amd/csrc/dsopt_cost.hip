@@ -9,14 +9,16 @@ namespace {
 
 // Seed of this wavefront in k_cost / k_guide: W = 1, one seed per
 // wavefront (WAVES_PER_BLOCK per workgroup); W > 1, one seed per workgroup
-// of W wavefronts (a team, for batches too small to fill the chip).
+// of W wavefronts (a team, for batches too small to fill the chip; FULL: one
+// of MAX_TEAM).
+template <bool FULL>
 __device__ __forceinline__ int seed_of(int W, float* team_lds, Team& tm) {
   tm.buf = 0;
-  if (W > 1) {
+  if (FULL || W > 1) {
     tm.W = W;
     tm.w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
     tm.lds = team_lds;
-    tm.kin = W == MAX_TEAM ? team_lds + 2 * W * PART * WAVE : nullptr;
+    tm.kin = FULL ? team_lds + 2 * W * PART * WAVE : nullptr;
     return blockIdx.x;
   }
   tm.W = 1;
@@ -39,7 +41,7 @@ __device__ __forceinline__ void load_waypoint(const float* __restrict__ X, int s
 // memory costs a copy ahead of the kernel and an event behind it.
 // Objective (and gradient) of arbitrary trajectories: one wavefront (or a
 // team) per seed group of G lanes (G = smallest of 16/32/64 holding T).
-template <bool EXT>
+template <bool EXT, bool FULL>
 __global__ void __launch_bounds__(MAX_TEAM * WAVE)
 k_cost(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp, const ProbDev pb,
        const float* __restrict__ X, int S, int T, int G, const float* __restrict__ dJ,
@@ -48,7 +50,7 @@ k_cost(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp, const 
   __shared__ __attribute__((aligned(16))) uint8_t s_cm[COARSE_BYTES];
   const int lane = threadIdx.x & (WAVE - 1);
   Team tm;
-  const int seed = seed_of(W, s_team, tm);
+  const int seed = seed_of<FULL>(W, s_team, tm);
   const int t = lane & (G - 1);
   const bool owner = tm.w == 0 && lane < G;
   const bool active = t < T;
@@ -63,7 +65,7 @@ k_cost(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp, const 
   put_goal(pb);
   float J;
   if (with_grad) {
-    EvalOut e = eval_any<EV_GRAD, EXT>(use_pipe(rb, tm, G), rb, P, Sm, x, t, T, G, active, tm);
+    EvalOut e = eval_any<EV_GRAD, EXT, FULL>(use_pipe(rb, tm, G), rb, P, Sm, x, t, T, G, active, tm);
     J = grp_sum(e.cost, G);
     float w = dJ ? dJ[seed] : 1.f;
     if (active && owner) {
@@ -71,7 +73,7 @@ k_cost(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp, const 
       for (int j = 0; j < NJ; ++j) dX[((size_t)seed * T + t) * NJ + j] = w * e.g[j];
     }
   } else {
-    EvalOut e = eval_any<EV_COST, EXT>(use_pipe(rb, tm, G), rb, P, Sm, x, t, T, G, active, tm);
+    EvalOut e = eval_any<EV_COST, EXT, FULL>(use_pipe(rb, tm, G), rb, P, Sm, x, t, T, G, active, tm);
     J = grp_sum(e.cost, G);
   }
   if (J_out && tm.w == 0 && lane == 0) J_out[seed] = J;
@@ -79,7 +81,7 @@ k_cost(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp, const 
 
 // Guidance: n gradient steps x <- x - alpha * g on every trajectory, one
 // wavefront (or a team) per seed (same evaluation as the optimiser).
-template <bool EXT>
+template <bool EXT, bool FULL>
 __global__ void __launch_bounds__(MAX_TEAM * WAVE)
 k_guide(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp, const ProbDev pb,
         float* __restrict__ X, int S, int T, int G, float alpha, int n_steps,
@@ -88,7 +90,7 @@ k_guide(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp, const
   __shared__ __attribute__((aligned(16))) uint8_t s_cm[COARSE_BYTES];
   const int lane = threadIdx.x & (WAVE - 1);
   Team tm;
-  const int seed = seed_of(W, s_team, tm);
+  const int seed = seed_of<FULL>(W, s_team, tm);
   const int t = lane & (G - 1);
   const bool owner = tm.w == 0 && lane < G;
   const bool active = t < T;
@@ -103,12 +105,12 @@ k_guide(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp, const
   put_goal(pb);
   const bool pipe = use_pipe(rb, tm, G);
   for (int k = 0; k < n_steps; ++k) {
-    EvalOut e = eval_any<EV_GRAD, EXT>(pipe, rb, P, Sm, x, t, T, G, active, tm);
+    EvalOut e = eval_any<EV_GRAD, EXT, FULL>(pipe, rb, P, Sm, x, t, T, G, active, tm);
 #pragma unroll
     for (int j = 0; j < NJ; ++j) x[j] -= alpha * e.g[j];
   }
   if (J_out) {
-    EvalOut e = eval_any<EV_COST, EXT>(pipe, rb, P, Sm, x, t, T, G, active, tm);
+    EvalOut e = eval_any<EV_COST, EXT, FULL>(pipe, rb, P, Sm, x, t, T, G, active, tm);
     float J = grp_sum(e.cost, G);
     if (tm.w == 0 && lane == 0) J_out[seed] = J;
   }
@@ -176,8 +178,10 @@ hipError_t launch_cost(const RobotDev* rb, const ParamsDev* pp, const ProbDev& p
   const int W = cost_team(S, cu_count);
   const int blocks = W > 1 ? S : (S + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK;
   const size_t lds_bytes = eval_lds(W);
-  hipLaunchKernelGGL(ext ? k_cost<true> : k_cost<false>, dim3(blocks), dim3(W > 1 ? W * WAVE : BLOCK),
-                     lds_bytes, s, rb, pp, prob, X, S, T, G, dJ, J_out, dX, with_grad, W);
+  const auto kernel = W == MAX_TEAM ? (ext ? k_cost<true, true> : k_cost<false, true>)
+                                    : (ext ? k_cost<true, false> : k_cost<false, false>);
+  hipLaunchKernelGGL(kernel, dim3(blocks), dim3(W > 1 ? W * WAVE : BLOCK), lds_bytes, s, rb, pp,
+                     prob, X, S, T, G, dJ, J_out, dX, with_grad, W);
   return hipGetLastError();
 }
 
@@ -188,8 +192,10 @@ hipError_t launch_guide(const RobotDev* rb, const ParamsDev* pp, const ProbDev& 
   const int W = cost_team(S, cu_count);
   const int blocks = W > 1 ? S : (S + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK;
   const size_t lds_bytes = eval_lds(W);
-  hipLaunchKernelGGL(ext ? k_guide<true> : k_guide<false>, dim3(blocks), dim3(W > 1 ? W * WAVE : BLOCK),
-                     lds_bytes, s, rb, pp, prob, X, S, T, G, alpha, n_steps, J_out, W);
+  const auto kernel = W == MAX_TEAM ? (ext ? k_guide<true, true> : k_guide<false, true>)
+                                    : (ext ? k_guide<true, false> : k_guide<false, false>);
+  hipLaunchKernelGGL(kernel, dim3(blocks), dim3(W > 1 ? W * WAVE : BLOCK), lds_bytes, s, rb, pp,
+                     prob, X, S, T, G, alpha, n_steps, J_out, W);
   return hipGetLastError();
 }
 

@@ -1299,20 +1299,18 @@ __device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
 }
 
 // The evaluation form for this team: PIPE when every lane holds at most one
-// sphere per link; shared kinematics for a full team.
-template <int MODE, bool EXT>
+// sphere per link; shared kinematics for a full team (FULL: MAX_TEAM
+// wavefronts).  Full teams have kernels of their own: a kernel with both forms
+// pays for both in registers and in instruction fetch (one with 100 iterations
+// of 32 seeds in teams of eight: 1060 us, 1000 us with the full team's alone).
+template <int MODE, bool EXT, bool FULL>
 __device__ __forceinline__ EvalOut eval_any(bool pipe, const RobotDev* __restrict__ rb,
                                             const ParamsDev& P, const Sampler& S, const float* q,
                                             int t, int T, int G, bool active,
                                             Team& tm) {
-  if constexpr (MODE != EV_RESULT) {
-    if (tm.kin) {
-      if (pipe) return evaluate<MODE, true, EXT, true>(rb, P, S, q, t, T, G, active, tm);
-      return evaluate<MODE, false, EXT, true>(rb, P, S, q, t, T, G, active, tm);
-    }
-  }
-  if (pipe) return evaluate<MODE, true, EXT, false>(rb, P, S, q, t, T, G, active, tm);
-  return evaluate<MODE, false, EXT, false>(rb, P, S, q, t, T, G, active, tm);
+  constexpr bool KIN = FULL && MODE != EV_RESULT;
+  if (pipe) return evaluate<MODE, true, EXT, KIN>(rb, P, S, q, t, T, G, active, tm);
+  return evaluate<MODE, false, EXT, KIN>(rb, P, S, q, t, T, G, active, tm);
 }
 
 __device__ __forceinline__ bool use_pipe(const RobotDev* __restrict__ rb, const Team& tm, int G) {

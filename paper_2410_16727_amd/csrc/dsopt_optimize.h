@@ -369,9 +369,9 @@ __device__ __forceinline__ void trace_scalar(float* buf, const TileCtx& c, int k
 }
 
 // Final per-seed results and output trajectory.
-template <bool EXT>
+template <bool EXT, bool FULL>
 __device__ __forceinline__ int finalize(const TileCtx& c, const float* x, Team& tm) {
-  EvalOut r = eval_any<EV_RESULT, EXT>(c.pipe, c.rb, c.P, c.S, x, c.t, c.T, c.G, c.active, tm);
+  EvalOut r = eval_any<EV_RESULT, EXT, FULL>(c.pipe, c.rb, c.P, c.S, x, c.t, c.T, c.G, c.active, tm);
   float Jr = grp_sum(r.cost, c.G);
   float clr = grp_min(c.active ? r.clr : FLT_MAX, c.G);
   float perr = grp_sum((c.t == c.T - 1) ? r.perr : 0.f, c.G);
@@ -451,7 +451,7 @@ enum { PH_INIT = 0, PH_DIR = 1, PH_TRIAL = 2, PH_ACCEPT = 3 };
 //          cost-only candidates while a seed of the tile has no Armijo step;
 //          if a seed accepted alpha < 1, evaluate there (ACCEPT), else update;
 //   ACCEPT take the accepted point's cost and gradient, update.
-template <bool LDS_HIST, bool EXT>
+template <bool LDS_HIST, bool EXT, bool FULL>
 __device__ __forceinline__ void run_tile(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp,
                          const ProbDev* __restrict__ probs, const TileDev& td, int max_iters,
                          Team& tm, float* hist_lds, uint8_t* coarse_lds, float* dir_lds) {
@@ -556,7 +556,7 @@ __device__ __forceinline__ void run_tile(const RobotDev* __restrict__ rb, const 
       phase = PH_TRIAL;
     }
     // the one cost+gradient evaluation of this pass
-    EvalOut e = eval_any<EV_GRAD, EXT>(c.pipe, rb, c.P, c.S, xe, c.t, c.T, c.G, c.active, tm);
+    EvalOut e = eval_any<EV_GRAD, EXT, FULL>(c.pipe, rb, c.P, c.S, xe, c.t, c.T, c.G, c.active, tm);
     ++evg;
     ngath += e.ng;
     const float Je = grp_sum(e.cost, c.G);
@@ -582,8 +582,8 @@ __device__ __forceinline__ void run_tile(const RobotDev* __restrict__ rb, const 
         float xk[NJ];
 #pragma unroll
         for (int j = 0; j < NJ; ++j) xk[j] = x[j] + al * d[j];
-        EvalOut ek = eval_any<EV_COST, EXT>(c.pipe, rb, c.P, c.S, xk, c.t, c.T, c.G, c.active,
-                                       tm);
+        EvalOut ek = eval_any<EV_COST, EXT, FULL>(c.pipe, rb, c.P, c.S, xk, c.t, c.T, c.G,
+                                                  c.active, tm);
         ++evc;
         ngath += ek.ng;
         float Jk = grp_sum(ek.cost, c.G);
@@ -663,7 +663,7 @@ __device__ __forceinline__ void run_tile(const RobotDev* __restrict__ rb, const 
     trace_row(pb.tr_x, c, iter, x);
     trace_row(pb.tr_g, c, iter, g);
     trace_scalar(pb.tr_J, c, iter, J);
-    ngath += finalize<EXT>(c, x, tm);
+    ngath += finalize<EXT, FULL>(c, x, tm);
   }
   // this launch's gathers into the seed's counter: every lane adds its own
   // count.  No lane-dependent branch here -- one at the end of the tile body
@@ -700,10 +700,10 @@ __device__ __forceinline__ int next_tile(int* counter, const int* __restrict__ x
 // (next_tile) until the table is exhausted (tile_list, if given, indirects
 // the table; n_tiles_dev, if given, overrides n_tiles).  Every member of a
 // team sees the same tile sequence and the same decisions, so all of them
-// reach every barrier.  Variants: TEAM (W > 1, history ring in LDS) and EXT
-// (self-collision and swept terms compiled in); the plain variant carries
-// no code for the optional terms.
-template <bool TEAM, bool EXT>
+// reach every barrier.  Variants: TEAM (W > 1, history ring in LDS), FULL
+// (W = 8, shared kinematics) and EXT (self-collision and swept terms compiled
+// in); the plain variant carries no code for the optional terms.
+template <bool TEAM, bool EXT, bool FULL>
 __global__ void __launch_bounds__(TEAM ? MAX_TEAM * WAVE : BLOCK, TEAM ? 1 : 2)
 k_optimize(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp,
            const ProbDev* __restrict__ probs, const TileDev* __restrict__ tiles,
@@ -721,9 +721,7 @@ k_optimize(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp,
   // wave-uniform (scalar) index, so loops over a wavefront's share stay scalar
   tm.w = TEAM ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE)) : 0;
   tm.lds = s_dyn;
-  tm.kin = TEAM && tm.W == MAX_TEAM
-               ? s_dyn + 2 * tm.W * PART * WAVE + H_FLOATS + COARSE_FLOATS + DL_FLOATS
-               : nullptr;
+  tm.kin = FULL ? s_dyn + 2 * tm.W * PART * WAVE + H_FLOATS + COARSE_FLOATS + DL_FLOATS : nullptr;
   tm.buf = 0;
   for (;;) {
     int mine = 0;
@@ -743,15 +741,15 @@ k_optimize(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp,
     const int ti = tile_list ? tile_list[mine] : mine;
     TileDev td = tiles[ti];
     if constexpr (TEAM) {
-      run_tile<true, EXT>(rb, pp, probs, td, max_iters, tm, s_dyn + 2 * tm.W * PART * WAVE,
-                          reinterpret_cast<uint8_t*>(s_dyn + 2 * tm.W * PART * WAVE + H_FLOATS),
-                          s_dyn + 2 * tm.W * PART * WAVE + H_FLOATS + COARSE_FLOATS);
+      run_tile<true, EXT, FULL>(rb, pp, probs, td, max_iters, tm, s_dyn + 2 * tm.W * PART * WAVE,
+                                reinterpret_cast<uint8_t*>(s_dyn + 2 * tm.W * PART * WAVE + H_FLOATS),
+                                s_dyn + 2 * tm.W * PART * WAVE + H_FLOATS + COARSE_FLOATS);
       __syncthreads();   // the LDS ring is free for the next tile
     } else {
       // this wavefront's coarse table (uniform)
       const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
-      run_tile<false, EXT>(rb, pp, probs, td, max_iters, tm, nullptr,
-                           reinterpret_cast<uint8_t*>(s_dyn + wv * COARSE_FLOATS), nullptr);
+      run_tile<false, EXT, FULL>(rb, pp, probs, td, max_iters, tm, nullptr,
+                                 reinterpret_cast<uint8_t*>(s_dyn + wv * COARSE_FLOATS), nullptr);
     }
   }
 }
@@ -761,7 +759,8 @@ using OptKernel = void (*)(const RobotDev*, const ParamsDev*, const ProbDev*, co
 
 template <bool EXT>
 OptKernel optimize_variant(int W) {
-  return W > 1 ? k_optimize<true, EXT> : k_optimize<false, EXT>;
+  if (W == MAX_TEAM) return k_optimize<true, EXT, true>;
+  return W > 1 ? k_optimize<true, EXT, false> : k_optimize<false, EXT, false>;
 }
 
 }  // namespace
