@@ -104,24 +104,36 @@ __device__ __forceinline__ void steepest(const TileCtx& c, const float* g, float
   for (int j = 0; j < NJ; ++j) d[j] = -g[j] * sc;
 }
 
-// A direction's descent test, restart and infinity-norm cap (the seed's
-// values are the same in every lane, so the tests are taken wave-uniformly).
-__device__ __forceinline__ void restart_and_cap(const TileCtx& c, const float* g, int& cnt,
-                                                float* d) {
-  const float gtd = grp_sum(dot7(g, d), c.G);
-  if (!__builtin_amdgcn_readfirstlane(gtd < 0.f ? 1 : 0)) {
-    cnt = 0;
-    steepest(c, g, d);
-  }
+// The largest |d| of the seed.
+__device__ __forceinline__ float largest(const TileCtx& c, const float* d) {
   float dn = 0.f;
 #pragma unroll
   for (int j = 0; j < NJ; ++j) dn = fmaxf(dn, fabsf(d[j]));
-  dn = grp_max(dn, c.G);
-  if (dn > c.P.dmax) {
+  return grp_max(dn, c.G);
+}
+
+// A direction's descent test, restart and infinity-norm cap; returns g . d of
+// the direction as it is then (formed again only where d was changed).  The
+// seed's values are the same in every lane, so the tests are taken
+// wave-uniformly, and both reductions run side by side.
+__device__ __forceinline__ float restart_and_cap(const TileCtx& c, const float* g, int& cnt,
+                                                 float* d) {
+  float gtd = grp_sum(dot7(g, d), c.G), dn = largest(c, d);
+  bool changed = false;
+  if (!__builtin_amdgcn_readfirstlane(gtd < 0.f ? 1 : 0)) {
+    cnt = 0;
+    steepest(c, g, d);
+    dn = largest(c, d);
+    changed = true;
+  }
+  if (__builtin_amdgcn_readfirstlane(dn > c.P.dmax ? 1 : 0)) {
     const float f = c.P.dmax / dn;
 #pragma unroll
     for (int j = 0; j < NJ; ++j) d[j] *= f;
+    changed = true;
   }
+  if (changed) gtd = grp_sum(dot7(g, d), c.G);
+  return gtd;
 }
 
 // Ring slot of the entry of a given age (0 = newest), 0 <= head < m and
@@ -132,10 +144,11 @@ __device__ __forceinline__ int ring_slot(int head, int age, int m) {
 }
 
 // L-BFGS direction (two-loop recursion over the history ring),
-// steepest-descent restart and infinity-norm cap.  cnt/head are the seed's
-// history count and ring head (the same in every lane of the wavefront).
+// steepest-descent restart and infinity-norm cap; returns g . d.  cnt/head are
+// the seed's history count and ring head (the same in every lane of the
+// wavefront).
 template <class H>
-__device__ __forceinline__ void direction(const TileCtx& c, const H& hist, const float* g, int& cnt,
+__device__ __forceinline__ float direction(const TileCtx& c, const H& hist, const float* g, int& cnt,
                                           int head, float* d) {
   const int m = c.P.m;
   // one seed per wavefront: count and head are wave-uniform
@@ -190,7 +203,7 @@ __device__ __forceinline__ void direction(const TileCtx& c, const H& hist, const
   } else {
     steepest(c, g, d);
   }
-  restart_and_cap(c, g, cnt, d);
+  return restart_and_cap(c, g, cnt, d);
 }
 
 // A team's direction block in LDS: the columns of d, the 2m dot products
@@ -213,9 +226,9 @@ constexpr int DL_D = 0, DL_AB = NJ * WAVE, DL_SY = DL_AB + 2 * DS_MAX_HISTORY,
 // (lane i < cnt holds row i) and forms the columns j = w mod W of d.  Every
 // wavefront ends with bitwise the same d and cnt.
 template <class H>
-__device__ __forceinline__ void team_direction(const TileCtx& c, const H& hist, const Team& tm,
-                                               const float* g, int& cnt, int head, float* d,
-                                               DS_LDS float* dl) {
+__device__ __forceinline__ float team_direction(const TileCtx& c, const H& hist, const Team& tm,
+                                                const float* g, int& cnt, int head, float* d,
+                                                DS_LDS float* dl) {
   const int m = c.P.m;
   const int cu = __builtin_amdgcn_readfirstlane(cnt);
   const int hd = __builtin_amdgcn_readfirstlane(head);
@@ -321,7 +334,7 @@ __device__ __forceinline__ void team_direction(const TileCtx& c, const H& hist, 
   } else {
     steepest(c, g, d);
   }
-  restart_and_cap(c, g, cnt, d);
+  return restart_and_cap(c, g, cnt, d);
 }
 
 // The slot matrices of the cnt valid ring entries, formed from the ring
@@ -545,12 +558,11 @@ __device__ __forceinline__ void run_tile(const RobotDev* __restrict__ rb, const 
         trace_scalar(pb.tr_J, c, iter, J);
       }
       if constexpr (LDS_HIST) {
-        team_direction(c, hist, tm, g, cnt, head, d, lds(dir_lds));
+        gtd = team_direction(c, hist, tm, g, cnt, head, d, lds(dir_lds));
       } else {
-        direction(c, hist, g, cnt, head, d);
+        gtd = direction(c, hist, g, cnt, head, d);
       }
       if (tracing) trace_row(pb.tr_d, c, iter, d);
-      gtd = grp_sum(dot7(g, d), c.G);
 #pragma unroll
       for (int j = 0; j < NJ; ++j) xe[j] = x[j] + d[j];
       phase = PH_TRIAL;
@@ -611,21 +623,21 @@ __device__ __forceinline__ void run_tile(const RobotDev* __restrict__ rb, const 
     if (!update_now) continue;
     // history update and step
     if (tracing) trace_scalar(pb.tr_a, c, iter, alpha);
-    const bool accept = chosen >= 0;
-    float s[NJ], y[NJ];
+    if (__builtin_amdgcn_readfirstlane(chosen) >= 0) {
+      float s[NJ], y[NJ];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      float xn = x[j] + alpha * d[j];
-      s[j] = accept ? xn - x[j] : 0.f;
-      y[j] = accept ? gt[j] - g[j] : 0.f;
-    }
-    float sy = grp_sum(dot7(s, y), c.G);
-    float ss = grp_sum(dot7(s, s), c.G);
-    float yy = grp_sum(dot7(y, y), c.G);
-    if (accept) {
-      if (sy > 1e-10f * sqrtf(ss) * sqrtf(yy)) {
+      for (int j = 0; j < NJ; ++j) {
+        float xn = x[j] + alpha * d[j];
+        s[j] = xn - x[j];
+        y[j] = gt[j] - g[j];
+        asm("" : "+v"(y[j]));   // a rounded difference, whatever is formed from it
+      }
+      float sy = grp_sum(dot7(s, y), c.G);
+      float ss = grp_sum(dot7(s, s), c.G);
+      float yy = grp_sum(dot7(y, y), c.G);
+      if (__builtin_amdgcn_readfirstlane(sy > 1e-10f * sqrtf(ss) * sqrtf(yy) ? 1 : 0)) {
         if (writer) hist.push(head, s, y, 1.f / sy, yy);
-        head = (head + 1) % c.P.m;
+        head = head + 1 == c.P.m ? 0 : head + 1;
         cnt = min(cnt + 1, c.P.m);
       }
 #pragma unroll
