@@ -837,7 +837,7 @@ __device__ __forceinline__ float coarse_min(const Sampler& S, const float* u) {
 // are in flight together, where a branch per sample made each of them wait
 // for its own two (lanes without a sample go through the motions with the
 // last sphere of the table at the most).
-template <int MODE, bool PIPE, bool KIN>
+template <int MODE, bool PIPE, bool KIN, bool SMALL>
 __device__ __forceinline__ void sweep(const ParamsDev& P, const Sampler& S, const float* q, int cp,
                                       int LW, const Team& tm, Twists& tw, float* R, float* p,
                                       float& phisum, float& clr, float* g, int& ng, bool active) {
@@ -925,6 +925,12 @@ __device__ __forceinline__ void sweep(const ParamsDev& P, const Sampler& S, cons
     }
   } else {
     constexpr int C = KIN ? 2 : CH;   // (a full team has eight copies at least)
+    // SMALL: a team's later wavefronts run out of a link's spheres before its
+    // first one does, and make fewer tests: what counts is left from their own
+    // first copy on.  (50 iterations of 10 seeds with nine spheres on some
+    // links: W = 2 908 us, 887 us so; W = 4 718 and 704 us.  One wavefront per
+    // seed has nothing to gain and loses 3 % to the longer code.)
+    const int cp0 = SMALL ? __builtin_amdgcn_readfirstlane(cp) : 0;
     if constexpr (!KIN) advance(0);
 #pragma unroll
     for (int l = 0; l < NJ; ++l) {
@@ -961,12 +967,17 @@ __device__ __forceinline__ void sweep(const ParamsDev& P, const Sampler& S, cons
 #pragma unroll
           for (int k = 0; k < N; ++k) use[k] &= !(SKIP & (cm[k] >= r[k] + P.far));
         };
-        if (C == 2 || s + 2 * LW < s1) {
+        if (C == 2 || s + 2 * LW < s1 - cp0) {
           test(std::integral_constant<int, C>());
-        } else {   // at most two spheres per lane are left
+        } else if (!SMALL || s + LW < s1 - cp0) {   // at most two spheres per lane are left
 #pragma unroll
           for (int k = 2; k < C; ++k) use[k] = false;
           test(std::integral_constant<int, 2>());
+        } else {
+          use[1] = false;
+#pragma unroll
+          for (int k = 2; k < C; ++k) use[k] = false;
+          test(std::integral_constant<int, 1>());
         }
 #pragma unroll
         for (int k = 0; k < C; ++k) {
@@ -1006,7 +1017,7 @@ __device__ __forceinline__ void sweep(const ParamsDev& P, const Sampler& S, cons
 // One evaluation of the objective at this lane's configuration q (its
 // waypoint) and, with swept sub-samples, at the configurations interpolated
 // towards the next waypoint.
-template <int MODE, bool PIPE, bool EXT, bool KIN>
+template <int MODE, bool PIPE, bool EXT, bool KIN, bool SMALL>
 __device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
                                             const ParamsDev& P, const Sampler& S, const float* q,
                                             int t, int T, int G, bool active,
@@ -1053,7 +1064,7 @@ __device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
   };
   if constexpr (!EXT) {
     if constexpr (KIN) team_kinematics(rb, tm, q, tw, own_terms);
-    sweep<MODE, PIPE, KIN>(P, S, q, cp, LW, tm, tw, R, p, phisum, clr, o.g, o.ng, active);
+    sweep<MODE, PIPE, KIN, SMALL>(P, S, q, cp, LW, tm, tw, R, p, phisum, clr, o.g, o.ng, active);
   } else {
     // swept collision: q + tau (q_next - q), tau = i / (nsub + 1), i = 1 ..
     // nsub; the gradient splits (1 - tau) here and tau onto the next
@@ -1082,7 +1093,7 @@ __device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
           if (own) own_terms();
         });
       }
-      sweep<MODE, PIPE, KIN>(P, S, qi, cp, LW, tm, tw, R, p, ph, cl, gi, o.ng, own ? active : seg);
+      sweep<MODE, PIPE, KIN, SMALL>(P, S, qi, cp, LW, tm, tw, R, p, ph, cl, gi, o.ng, own ? active : seg);
       if (own) {
         phisum = ph;
         clr = cl;
@@ -1300,17 +1311,18 @@ __device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
 
 // The evaluation form for this team: PIPE when every lane holds at most one
 // sphere per link; shared kinematics for a full team (FULL: MAX_TEAM
-// wavefronts).  Full teams have kernels of their own: a kernel with both forms
-// pays for both in registers and in instruction fetch (one with 100 iterations
-// of 32 seeds in teams of eight: 1060 us, 1000 us with the full team's alone).
-template <int MODE, bool EXT, bool FULL>
+// wavefronts; SMALL: the optimiser's smaller ones).  Full teams have kernels
+// of their own: a kernel with both forms pays for both in registers and in
+// instruction fetch (100 iterations of 32 seeds in teams of eight: 1060 us,
+// 1000 us with the full team's alone).
+template <int MODE, bool EXT, bool FULL, bool SMALL = false>
 __device__ __forceinline__ EvalOut eval_any(bool pipe, const RobotDev* __restrict__ rb,
                                             const ParamsDev& P, const Sampler& S, const float* q,
                                             int t, int T, int G, bool active,
                                             Team& tm) {
   constexpr bool KIN = FULL && MODE != EV_RESULT;
-  if (pipe) return evaluate<MODE, true, EXT, KIN>(rb, P, S, q, t, T, G, active, tm);
-  return evaluate<MODE, false, EXT, KIN>(rb, P, S, q, t, T, G, active, tm);
+  if (pipe) return evaluate<MODE, true, EXT, KIN, SMALL>(rb, P, S, q, t, T, G, active, tm);
+  return evaluate<MODE, false, EXT, KIN, SMALL>(rb, P, S, q, t, T, G, active, tm);
 }
 
 __device__ __forceinline__ bool use_pipe(const RobotDev* __restrict__ rb, const Team& tm, int G) {

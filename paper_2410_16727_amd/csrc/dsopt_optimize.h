@@ -468,6 +468,7 @@ template <bool LDS_HIST, bool EXT, bool FULL>
 __device__ __forceinline__ void run_tile(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp,
                          const ProbDev* __restrict__ probs, const TileDev& td, int max_iters,
                          Team& tm, float* hist_lds, uint8_t* coarse_lds, float* dir_lds) {
+  constexpr bool SMALL = LDS_HIST && !FULL;   // a team of less than MAX_TEAM
   TileCtx c;
   c.rb = rb;
   c.P = *pp;
@@ -568,7 +569,8 @@ __device__ __forceinline__ void run_tile(const RobotDev* __restrict__ rb, const 
       phase = PH_TRIAL;
     }
     // the one cost+gradient evaluation of this pass
-    EvalOut e = eval_any<EV_GRAD, EXT, FULL>(c.pipe, rb, c.P, c.S, xe, c.t, c.T, c.G, c.active, tm);
+    EvalOut e = eval_any<EV_GRAD, EXT, FULL, SMALL>(c.pipe, rb, c.P, c.S, xe, c.t, c.T, c.G,
+                                                    c.active, tm);
     ++evg;
     ngath += e.ng;
     const float Je = grp_sum(e.cost, c.G);
@@ -594,8 +596,8 @@ __device__ __forceinline__ void run_tile(const RobotDev* __restrict__ rb, const 
         float xk[NJ];
 #pragma unroll
         for (int j = 0; j < NJ; ++j) xk[j] = x[j] + al * d[j];
-        EvalOut ek = eval_any<EV_COST, EXT, FULL>(c.pipe, rb, c.P, c.S, xk, c.t, c.T, c.G,
-                                                  c.active, tm);
+        EvalOut ek = eval_any<EV_COST, EXT, FULL, SMALL>(c.pipe, rb, c.P, c.S, xk, c.t, c.T, c.G,
+                                                         c.active, tm);
         ++evc;
         ngath += ek.ng;
         float Jk = grp_sum(ek.cost, c.G);
