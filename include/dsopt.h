@@ -224,9 +224,10 @@ int ds_esdf_release(ds_plan* plan, int32_t scene_id);
  * no occupied (no free) voxel yields values >= 1e9 * voxel in magnitude.
  * The field becomes scene `scene_id` exactly as with ds_esdf_upload;
  * `out_vals` (device, nx*ny*nz floats, may be NULL) receives a copy of the
- * signed distances.  Temporary space (nx*ny*nz floats, as many again without
- * out_vals, and a bit per voxel) comes from the arena.  Errors:
- * DS_ERR_INVALID (dims < 2 or > 1024, voxel <= 0), DS_ERR_NOMEM. */
+ * signed distances, also where only the scene's part of the call fails; the
+ * scene is built from the library's own field.  Temporary space (nx*ny*nz
+ * floats and a bit per voxel) comes from the arena.  Errors: DS_ERR_INVALID
+ * (dims < 2 or > 1024, voxel <= 0), DS_ERR_NOMEM. */
 int ds_esdf_from_occupancy(ds_plan* plan, int32_t scene_id, const uint8_t* occ, int nx, int ny,
                            int nz, float voxel, const float origin[3], float* out_vals,
                            void* stream);

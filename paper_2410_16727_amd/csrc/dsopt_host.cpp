@@ -439,6 +439,21 @@ bool on_device(const void* ptr) {
   return dev;
 }
 
+// Whether a kernel of this plan may write `bytes` at ptr: device memory of the
+// plan's GPU, aligned for floats, the whole range inside one allocation.
+bool writable_here(const ds_plan* p, void* ptr, size_t bytes) {
+  hipPointerAttribute_t attr;
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  const bool ok = reinterpret_cast<uintptr_t>(ptr) % sizeof(float) == 0 &&
+                  hipPointerGetAttributes(&attr, ptr) == hipSuccess &&
+                  attr.type == hipMemoryTypeDevice && attr.device == p->device &&
+                  hipMemGetAddressRange(&base, &size, ptr) == hipSuccess &&
+                  static_cast<uint8_t*>(ptr) + bytes <= static_cast<uint8_t*>(base) + size;
+  (void)hipGetLastError();
+  return ok;
+}
+
 }  // namespace dsh
 
 using namespace dsh;
@@ -599,10 +614,10 @@ int ds_esdf_from_occupancy(ds_plan* p, int32_t scene_id, const uint8_t* occ, int
   poll_deferred(p, false);
   const size_t n = (size_t)nx * ny * nz;
   const size_t fb = n * sizeof(float);
-  // occupancy bits, the signed squared distances between the passes and,
-  // unless the caller takes them, the distances
+  // occupancy bits and the field: the scene is made from this one, never from
+  // the caller's buffer
   const size_t bits = (edt_bits_bytes(nx, ny, nz) + 255) / 256 * 256;
-  const size_t work_bytes = bits + (out_vals ? 1 : 2) * fb;
+  const size_t work_bytes = bits + fb;
   size_t occ_off = SIZE_MAX, work_off = arena_alloc(p, work_bytes);
   if (work_off == SIZE_MAX)
     return fail(DS_ERR_NOMEM, "arena full (distance transform, %zu B)", work_bytes);
@@ -616,17 +631,31 @@ int ds_esdf_from_occupancy(ds_plan* p, int32_t scene_id, const uint8_t* occ, int
     HIP_TRY(hipMemcpyAsync(p->arena.ptr(occ_off), occ, n, hipMemcpyHostToDevice, s));
     occ_dev = p->arena.ptr(occ_off);
   }
-  // the scene's place first: a scene that is replaced waits for the device,
-  // and every launch below then follows the one before it at once
-  SceneRec rec;
-  int rc = open_scene(p, scene_id, nx, ny, nz, voxel, origin, rec);
-  if (!rc) {
-    uint8_t* w = p->arena.ptr(work_off);
-    float* work = reinterpret_cast<float*>(w + bits);
-    float* dist = out_vals ? out_vals : work + n;
+  uint8_t* w = p->arena.ptr(work_off);
+  float* dist = reinterpret_cast<float*>(w + bits);
+  // memory that the kernel cannot write (host, another GPU) is the copy engine's
+  const bool direct = out_vals && writable_here(p, out_vals, fb);
+  const bool copied = out_vals && !direct;
+  auto transform = [&]() -> int {
     HIP_TRY(launch_esdf_from_occupancy(occ_dev, nx, ny, nz, voxel,
-                                       reinterpret_cast<unsigned long long*>(w), work, dist, s));
-    rc = fill_scene(p, scene_id, dist, rec, s);
+                                       reinterpret_cast<unsigned long long*>(w), dist,
+                                       direct ? out_vals : nullptr, s));
+    if (copied) HIP_TRY(hipMemcpyAsync(out_vals, dist, fb, hipMemcpyDefault, s));
+    return DS_OK;
+  };
+  // the scene's place first: a scene that is replaced waits for the device,
+  // and every launch below then follows the one before it at once.  (Not where
+  // the copy engine may refuse out_vals: the old scene stays then.)
+  int rc = copied ? transform() : DS_OK;
+  if (!rc) {
+    SceneRec rec;
+    rc = open_scene(p, scene_id, nx, ny, nz, voxel, origin, rec);
+    const bool opened = !rc;
+    // out_vals is the caller's also where the scene has no place
+    if (!copied && (opened || out_vals))
+      if (int r2 = transform()) rc = r2;
+    if (!rc) rc = fill_scene(p, scene_id, dist, rec, s);
+    if (rc && opened) p->arena.release(rec.off);
   }
   if (int r2 = defer_free(p, work_off, s)) return r2;
   if (occ_off != SIZE_MAX)

@@ -127,11 +127,11 @@ inline bool params_ext(const ParamsDev& P) { return P.ws != 0.f || P.nsub > 0; }
 hipError_t launch_esdf_pack(const float* vals, int nx, int ny, int nz, int shift, int cdx,
                             int cdy, int cdz, float cq, float4* rec, uint8_t* table,
                             hipStream_t s);
-// The signed distance field of an occupancy grid into dist (work: as many
-// floats again; bits: edt_bits_bytes) (dsopt_scene.hip).
+// The signed distance field of an occupancy grid into dist and, if not null,
+// copy (bits: edt_bits_bytes) (dsopt_scene.hip).
 size_t edt_bits_bytes(int nx, int ny, int nz);
 hipError_t launch_esdf_from_occupancy(const uint8_t* occ, int nx, int ny, int nz, float voxel,
-                                      unsigned long long* bits, float* work, float* dist,
+                                      unsigned long long* bits, float* dist, float* copy,
                                       hipStream_t s);
 // counter: N_XCD ints when xcd_ranges (N_XCD + 1 ints: the per-XCD queues'
 // bounds in the tile table) is given, else one.

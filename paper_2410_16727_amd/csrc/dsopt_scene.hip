@@ -398,10 +398,11 @@ k_edt_xy(const unsigned* __restrict__ bits, int nx, int ny, float* __restrict__ 
 }
 
 // Pass along z over EDT_X neighbouring lines, and the distance itself: the
-// root of the squared distance in metres, negative inside.
+// root of the squared distance in metres, negative inside.  In place: a
+// workgroup has its lines in LDS before it writes them.  The caller's copy, if
+// any, is written beside it, without another pass over the field.
 __global__ void __launch_bounds__(EDT_THREADS)
-k_edt_z(const float* __restrict__ f, long long plane, int nz, float voxel,
-        float* __restrict__ dist) {
+k_edt_z(float* f, long long plane, int nz, float voxel, float* copy) {
   extern __shared__ float s_line[];
   const EdtLines L(s_line, nz);
   const long long l = (long long)blockIdx.x * EDT_X + L.col;
@@ -409,7 +410,10 @@ k_edt_z(const float* __restrict__ f, long long plane, int nz, float voxel,
   for (int z = threadIdx.x / EDT_X; z < nz; z += EDT_ROWS)
     L.s[z * EDT_X + L.col] = in ? f[l + z * plane] : 1.f;
   edt_lines(L, [&](int p, float s) {
-    if (in) dist[l + p * plane] = s < 0.f ? -voxel * sqrtf(-s) : voxel * sqrtf(s);
+    if (!in) return;
+    const float d = s < 0.f ? -voxel * sqrtf(-s) : voxel * sqrtf(s);
+    f[l + p * plane] = d;
+    if (copy) copy[l + p * plane] = d;
   });
 }
 
@@ -429,7 +433,7 @@ size_t edt_bits_bytes(int nx, int ny, int nz) {
 }
 
 hipError_t launch_esdf_from_occupancy(const uint8_t* occ, int nx, int ny, int nz, float voxel,
-                                      unsigned long long* bits, float* work, float* dist,
+                                      unsigned long long* bits, float* dist, float* copy,
                                       hipStream_t s) {
   const long long plane = (long long)nx * ny;
   const int per = EDT_THREADS / WAVE * BITS_ROWS;
@@ -438,11 +442,11 @@ hipError_t launch_esdf_from_occupancy(const uint8_t* occ, int nx, int ny, int nz
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_edt_xy, dim3((nx + EDT_X - 1) / EDT_X, nz), dim3(EDT_THREADS),
-                     edt_lds(ny), s, reinterpret_cast<const unsigned*>(bits), nx, ny, work);
+                     edt_lds(ny), s, reinterpret_cast<const unsigned*>(bits), nx, ny, dist);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_edt_z, dim3((unsigned)((plane + EDT_X - 1) / EDT_X)), dim3(EDT_THREADS),
-                     edt_lds(nz), s, work, plane, nz, voxel, dist);
+                     edt_lds(nz), s, dist, plane, nz, voxel, copy);
   return hipGetLastError();
 }
 
