@@ -13,28 +13,54 @@ namespace dsk {
 namespace {
 
 // ------------------------------------------------------ records and table --
-// One workgroup makes the records of a row of up to PACK_XB coarse blocks
-// (2^shift cells per axis) and their table entries, so that the field is
-// read once for both.  A thread owns a column of cells along z inside the
-// row: it keeps the plane of four nodes it has and loads the next one (four
-// loads per record instead of eight), writes the 32-byte record, and adds
-// the column's minimum to its block's in LDS.
+// One workgroup makes the records of a run of up to PACK_BLOCKS coarse blocks
+// (2^shift cells per axis; a part of a row along x, or whole rows, or whole
+// layers: a run in the table's order in any case) and their table entries, so
+// that the field is read once for both.  A thread owns a block's column of
+// cells along z: it keeps the plane of four nodes it has and loads the next
+// one (four loads per record instead of eight), writes the 32-byte record, and
+// adds the column's minimum to its block's in LDS.
 //
 // Table entry: the minimum node value m over the block's cells (the far
 // faces included: a cell's corners), kept as the 4-bit level L = the largest
 // L <= 15 with L * cq <= m (0 for a negative m), two blocks per byte, the
 // even block (linear index bx + cdx (by + cdy bz)) in the low nibble.  The
 // workgroup that owns a byte's even block writes the byte; where the odd one
-// is not in its row it forms that block's minimum from the nodes as well, so
+// is not in its run it forms that block's minimum from the nodes as well, so
 // no byte has two writers and the table needs no clearing.
 //
 // Bound: HBM, 36 bytes a cell (4 read, 32 written).  200^3: 57 us, 4.9 TB/s
 // of the 5.2 a large copy reaches here (one thread per record and a second
 // kernel that read the field again for the table: 54 + 35 us, and 5 us to
 // clear it).  Workgroups of 256 threads: 60 us; stores past the caches: 146.
-constexpr int PACK_XB = 32;
+constexpr int PACK_BLOCKS = 32;
 constexpr int PACK_THREADS = 512;
 constexpr int PACK_Z = 4;
+
+// Blocks of a workgroup along each axis: about a column of cells per thread.
+// Of a long row a part, of an even number of blocks; of short ones as many
+// rows, and then layers, as fill the threads.  With whole rows for every
+// workgroup, grids thin in x left most threads idle (4 x 4 x 100000: 86 us a
+// call, 20 so; 3 x 700 x 700: 106 and 21), and larger ones had too few
+// workgroups, or rows cut into a long and a short part of which one half of
+// the XCDs got all the long ones (400^3: 884 us, 730 so; 300 x 250 x 200: 248
+// and 163).  Parts of four times that, 400^3: 893 us, 300 x 250 x 200: 186;
+// of half, 186 for the latter.
+struct PackTile {
+  int x, y, z;
+};
+PackTile pack_tile(int nx, int ny, int shift, int cdx, int cdy, int cdz) {
+  const int most = std::min(PACK_BLOCKS, std::max(2, PACK_THREADS >> (2 * shift)));
+  if (cdx > most) {
+    const int parts = (cdx + most - 1) / most, each = (cdx + parts - 1) / parts;
+    return {each + (each & 1), 1, 1};
+  }
+  const int columns = (nx - 1) * std::min(1 << shift, ny - 1);   // of a row of blocks
+  PackTile t{cdx, std::max(1, std::min({cdy, PACK_BLOCKS / cdx, PACK_THREADS / columns})), 1};
+  if (t.y == cdy)
+    t.z = std::max(1, std::min({cdz, PACK_BLOCKS / (cdx * cdy), PACK_THREADS / ((nx - 1) * (ny - 1))}));
+  return t;
+}
 
 // Order-preserving integer key of a float (for a minimum by LDS atomics).
 __device__ __forceinline__ int min_key(float v) {
@@ -52,25 +78,38 @@ __device__ __forceinline__ unsigned level_of(float m, float cq) {
   return L;
 }
 
+template <bool LAYERS>
 __global__ void __launch_bounds__(PACK_THREADS)
 k_esdf_pack(const float* __restrict__ v, int nx, int ny, int nz, int shift, int cdx, int cdy,
-            int cdz, float cq, float4* __restrict__ rec, uint8_t* __restrict__ table) {
-  __shared__ int s_min[PACK_XB + 1];   // the row's blocks and the one after them
+            int cdz, PackTile tile, float cq, float4* __restrict__ rec,
+            uint8_t* __restrict__ table) {
+  __shared__ int s_min[PACK_BLOCKS + 1];   // the run's blocks and the one after them
   const int cx = nx - 1, cy = ny - 1, cz = nz - 1;
-  // this workgroup's blocks: bx in [bx0, bx1) of the row (by, bz)
-  const int by = blockIdx.y % cdy, bz = blockIdx.y / cdy;
-  const int bx0 = blockIdx.x * PACK_XB, bx1 = min(bx0 + PACK_XB, cdx);
-  const int x0 = bx0 << shift, xn = min(bx1 << shift, cx) - x0;
-  const int y0 = by << shift, yn = min((by + 1) << shift, cy) - y0;
-  const int z0 = bz << shift, z1 = min((bz + 1) << shift, cz);
-  for (int i = threadIdx.x; i < PACK_XB + 1; i += PACK_THREADS) s_min[i] = min_key(FLT_MAX);
+  // this workgroup's blocks: [bx0, bx0 + bxn) x [by0, by0 + byn) x [bz0, bz0 + bzn)
+  // (a row's parts begin at even indices of the table, but for the first; the
+  // last, shorter ones of the rows are dealt to the XCDs in turn)
+  const int by0 = blockIdx.y * tile.y, byn = min(tile.y, cdy - by0);
+  const int bz0 = LAYERS ? blockIdx.z * tile.z : blockIdx.z, bzn = LAYERS ? min(tile.z, cdz - bz0) : 1;
+  int bx0 = 0, bxn = cdx;
+  if (gridDim.x > 1) {
+    const int part = (blockIdx.x + blockIdx.y + blockIdx.z) % gridDim.x;
+    const int odd = (cdx * (by0 + cdy * bz0)) & 1;
+    bx0 = max(part * tile.x - odd, 0);
+    bxn = min((part + 1) * tile.x - odd, cdx) - bx0;
+    if (bxn <= 0) return;
+  }
+  const int x0 = bx0 << shift, xn = min((bx0 + bxn) << shift, cx) - x0;
+  const int y0 = by0 << shift, yn = min((by0 + byn) << shift, cy) - y0;
+  for (int i = threadIdx.x; i < PACK_BLOCKS + 1; i += PACK_THREADS) s_min[i] = min_key(FLT_MAX);
   __syncthreads();
   const size_t row = nx, plane = (size_t)nx * ny;
-  for (int c = threadIdx.x; c < xn * yn; c += PACK_THREADS) {
-    const int yi = c / xn, x = x0 + (c - yi * xn), y = y0 + yi;
+  for (int c = threadIdx.x; c < xn * yn * bzn; c += PACK_THREADS) {
+    const int q = c / xn, xi = c - q * xn, zi = LAYERS ? q / yn : 0, yi = q - zi * yn;
+    const int x = x0 + xi, y = y0 + yi;
+    const int z0 = (bz0 + zi) << shift, z1 = min((bz0 + zi + 1) << shift, cz);
     const float* p = v + x + row * y + plane * z0;
     float a0 = p[0], a1 = p[1], a2 = p[row], a3 = p[row + 1];
-    float m = fminf(FLT_MAX, fminf(fminf(a0, a1), fminf(a2, a3)));   // drops NaN nodes
+    float m = FLT_MAX;   // (fminf drops NaN nodes)
     float4* r = rec + 2 * ((size_t)x + (size_t)cx * ((size_t)y + (size_t)cy * z0));
     const size_t step = 2 * (size_t)cx * cy;
     for (int z = z0; z < z1; z += PACK_Z) {
@@ -87,14 +126,15 @@ k_esdf_pack(const float* __restrict__ v, int nx, int ny, int nz, int shift, int 
           r[0] = make_float4(a0, a1, a2, a3);
           r[1] = make_float4(b[k][0], b[k][1], b[k][2], b[k][3]);
         }
-        a0 = b[k][0]; a1 = b[k][1]; a2 = b[k][2]; a3 = b[k][3];
         m = fminf(m, fminf(fminf(a0, a1), fminf(a2, a3)));
+        a0 = b[k][0]; a1 = b[k][1]; a2 = b[k][2]; a3 = b[k][3];
       }
     }
-    atomicMin(&s_min[(x - x0) >> shift], min_key(m));
+    m = fminf(m, fminf(fminf(a0, a1), fminf(a2, a3)));
+    atomicMin(&s_min[(xi >> shift) + bxn * ((yi >> shift) + byn * zi)], min_key(m));
   }
   // the odd block after this workgroup's last one, if that byte is its own
-  const int first = bx0 + cdx * (by + cdy * bz), last = first + (bx1 - bx0);
+  const int first = bx0 + cdx * (by0 + cdy * bz0), last = first + bxn * byn * bzn;
   if ((last & 1) && last < cdx * cdy * cdz) {
     const int ex = last % cdx, ey = (last / cdx) % cdy, ez = last / (cdx * cdy);
     const int ex0 = ex << shift, ey0 = ey << shift, ez0 = ez << shift;
@@ -422,8 +462,13 @@ k_edt_z(float* f, long long plane, int nz, float voxel, float* copy) {
 hipError_t launch_esdf_pack(const float* vals, int nx, int ny, int nz, int shift, int cdx,
                             int cdy, int cdz, float cq, float4* rec, uint8_t* table,
                             hipStream_t s) {
-  hipLaunchKernelGGL(k_esdf_pack, dim3((cdx + PACK_XB - 1) / PACK_XB, cdy * cdz),
-                     dim3(PACK_THREADS), 0, s, vals, nx, ny, nz, shift, cdx, cdy, cdz, cq, rec,
+  const PackTile t = pack_tile(nx, ny, shift, cdx, cdy, cdz);
+  // (in odd rows of an odd length the parts begin one block earlier)
+  const int parts = t.x == cdx ? 1 : (cdx + (cdx & 1) + t.x - 1) / t.x;
+  const auto kernel = t.z > 1 ? k_esdf_pack<true> : k_esdf_pack<false>;
+  hipLaunchKernelGGL(kernel,
+                     dim3(parts, (cdy + t.y - 1) / t.y, (cdz + t.z - 1) / t.z),
+                     dim3(PACK_THREADS), 0, s, vals, nx, ny, nz, shift, cdx, cdy, cdz, t, cq, rec,
                      table);
   return hipGetLastError();
 }
