@@ -56,6 +56,7 @@ __device__ __forceinline__ DS_LDS T* lds(T* p) {
 #define DSOPT_CH 4
 #endif
 constexpr int CH = DSOPT_CH;                     // sphere gathers in flight per lane
+static_assert(CH >= 2, "a chunk's short form has two");
 // s_waitcnt operand: vector memory count 0, the export and LDS/scalar
 // counts at their maxima (not waited on)
 constexpr int WAIT_VMEM_ALL = 0x0F70;
@@ -206,7 +207,7 @@ struct Sampler {
   __amdgpu_buffer_rsrc_t rsrc;
   float ox, oy, oz, inv_h, h, nxm1, nym1, nzm1;
   float fxm2, fym2, fzm2;          // last cell index per axis, as floats
-  int nxm2, nym2, nzm2, cx, cy;    // cells along x and y
+  int cx, cy;                      // cells along x and y
   const DS_LDS uint8_t* cm;        // the scene's coarse table (4-bit levels), staged in LDS
   float cq;                        // distance of one level
   int cshift, cdx, cdy;
@@ -218,8 +219,7 @@ __device__ __forceinline__ Sampler make_sampler(const SceneDev& sc, const RobotD
   s.rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)sc.rec, (short)0, (int)sc.bytes, RSRC_DWORD3);
   s.ox = sc.ox; s.oy = sc.oy; s.oz = sc.oz; s.inv_h = sc.inv_h; s.h = 1.f / sc.inv_h;
   s.nxm1 = (float)(sc.nx - 1); s.nym1 = (float)(sc.ny - 1); s.nzm1 = (float)(sc.nz - 1);
-  s.nxm2 = sc.nx - 2; s.nym2 = sc.ny - 2; s.nzm2 = sc.nz - 2;
-  s.fxm2 = (float)s.nxm2; s.fym2 = (float)s.nym2; s.fzm2 = (float)s.nzm2;
+  s.fxm2 = (float)(sc.nx - 2); s.fym2 = (float)(sc.ny - 2); s.fzm2 = (float)(sc.nz - 2);
   s.cx = sc.nx - 1;
   s.cy = sc.ny - 1;
   s.cm = nullptr;
@@ -635,8 +635,8 @@ __device__ __forceinline__ void frame_row(const float* F, float sn, float cs, fl
 // the frames' rows in tm.kin.  `between` runs while three wavefronts form the
 // frames (work of the others that needs no frame).  Every wavefront calls it.
 template <class Between>
-__device__ __forceinline__ void team_kinematics(const RobotDev* __restrict__ rb, const Team& tm,
-                                                const float* q, Twists& tw, Between between) {
+__device__ __forceinline__ void team_kinematics(const Team& tm, const float* q, Twists& tw,
+                                                Between between) {
   const int lane = threadIdx.x & (WAVE - 1);
   DS_LDS float* kin = lds(tm.kin) + lane;
   // rows on wavefronts 4..6: three different SIMDs, beside wavefronts that
@@ -1063,7 +1063,7 @@ __device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
     if (tm.w == xs) extra_l += smoothness<GRAD>(P, q, t, T, ge);
   };
   if constexpr (!EXT) {
-    if constexpr (KIN) team_kinematics(rb, tm, q, tw, own_terms);
+    if constexpr (KIN) team_kinematics(tm, q, tw, own_terms);
     sweep<MODE, PIPE, KIN, SMALL>(P, S, q, cp, LW, tm, tw, R, p, phisum, clr, o.g, o.ng, active);
   } else {
     // swept collision: q + tau (q_next - q), tau = i / (nsub + 1), i = 1 ..
@@ -1089,7 +1089,7 @@ __device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
       }
       float ph = own ? phisum : 0.f, cl = own ? clr : FLT_MAX;
       if constexpr (KIN) {
-        team_kinematics(rb, tm, qi, tw, [&]() {
+        team_kinematics(tm, qi, tw, [&]() {
           if (own) own_terms();
         });
       }

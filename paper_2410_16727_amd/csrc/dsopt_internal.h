@@ -45,8 +45,10 @@ struct ParamsDev {
 // Coarse table: for each block of 2^cshift cells per axis (x fastest, at
 // most COARSE_MAX blocks), a 4-bit level L bounding the minimum node
 // distance m over the block's nodes from below: the largest L <= 15 with
-// L * cq <= m in float arithmetic (0 when m is negative or NaN); two blocks
-// per byte, the even block in the low nibble (16 KB).
+// L * cq <= m in float arithmetic (0 when m is negative); two blocks per
+// byte, the even block in the low nibble (16 KB).  NaN nodes are left out of
+// m (a block of nothing else has level 15): samples that lie next to one may
+// be skipped, where gathering them gives NaN.
 constexpr int COARSE_MAX = 32768;
 constexpr int COARSE_BYTES = COARSE_MAX / 2;
 constexpr int COARSE_FLOATS = COARSE_BYTES / 4;   // the table's size in 4-byte words

@@ -395,11 +395,12 @@ k_edt_xy(const unsigned* __restrict__ bits, int nx, int ny, float* __restrict__ 
   const int x0 = blockIdx.x * EDT_X, w0 = blockIdx.x;
   const int words = 2 * ((nx + WAVE - 1) / WAVE);
   // the tile's word and the four positions of each row, where the block
-  // minima and minimisers will be (16 bytes a row: as many as the minimisers)
+  // minima and minimisers will be (the minimisers alone take 16 bytes a row)
   struct Row {
     unsigned own;
     short po, pf, no, nf;
   };
+  static_assert(sizeof(Row) <= 16, "the rows fit where the minimisers will be");
   Row* rows = reinterpret_cast<Row*>(L.blk);
   for (int y = threadIdx.x; y < ny; y += EDT_THREADS) {
     const unsigned* w = bits + ((size_t)blockIdx.y * ny + y) * words;
