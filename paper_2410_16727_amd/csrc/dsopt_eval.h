@@ -1077,8 +1077,15 @@ __device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
       gsh[j] = 0.f;
     }
     const bool seg = active && t <= T - 2;
+    // The tables in LDS are read again in every round: without the statement
+    // the compiler reads the frames (84 registers) and the lane's spheres ahead
+    // of the loop and, being short of registers, keeps them in scratch memory
+    // instead (k_cost for smaller teams: 336 bytes per lane, 140 so; 600
+    // trajectories of 12 waypoints, 28 spheres, eight swept samples, with
+    // gradient: 142 us, 87 us so).
 #pragma unroll 1
     for (int i = 1;; ++i) {
+      asm volatile("" ::: "memory");
       const bool own = i > P.nsub;
       const float tau = (float)i / (float)(P.nsub + 1);
       float qi[NJ], gi[NJ];

@@ -50,7 +50,8 @@ def repeats(a):
 
 @pytest.mark.parametrize("S", [3, 600, 1100, 2101])
 @pytest.mark.parametrize("T", [13, 32, 47])
-@pytest.mark.parametrize("off_axis,w_self,swept", [(False, 50.0, 2), (True, 50.0, 1), (False, 50.0, 0), (True, 0.0, 2)])
+@pytest.mark.parametrize("off_axis,w_self,swept", [(False, 50.0, 2), (True, 50.0, 1), (False, 50.0, 0), (True, 0.0, 2),
+                                                  (False, 0.0, 8)])
 def test_cost_grad(off_axis, w_self, swept, T, S):
     say(f"optional terms off-axis={off_axis} w_self={w_self} swept={swept} T={T} S={S}")
     su = Terms(off_axis, w_self, swept)
