@@ -639,7 +639,7 @@ int ds_esdf_from_occupancy(ds_plan* p, int32_t scene_id, const uint8_t* occ, int
   auto transform = [&]() -> int {
     HIP_TRY(launch_esdf_from_occupancy(occ_dev, nx, ny, nz, voxel,
                                        reinterpret_cast<unsigned long long*>(w), dist,
-                                       direct ? out_vals : nullptr, s));
+                                       direct ? out_vals : nullptr, p->cu_count, s));
     if (copied) HIP_TRY(hipMemcpyAsync(out_vals, dist, fb, hipMemcpyDefault, s));
     return DS_OK;
   };

@@ -134,7 +134,7 @@ hipError_t launch_esdf_pack(const float* vals, int nx, int ny, int nz, int shift
 size_t edt_bits_bytes(int nx, int ny, int nz);
 hipError_t launch_esdf_from_occupancy(const uint8_t* occ, int nx, int ny, int nz, float voxel,
                                       unsigned long long* bits, float* dist, float* copy,
-                                      hipStream_t s);
+                                      int cu_count, hipStream_t s);
 // counter: N_XCD ints when xcd_ranges (N_XCD + 1 ints: the per-XCD queues'
 // bounds in the tile table) is given, else one.
 // tile_list (optional): the queue order, a permutation of 0..n_tiles-1.

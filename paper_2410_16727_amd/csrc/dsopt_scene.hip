@@ -188,32 +188,53 @@ k_esdf_pack(const float* __restrict__ v, int nx, int ny, int nz, int shift, int 
 // outward from every voxel, six passes of 27 to 428 us (829 together) and
 // 50 us of kernels around them.
 constexpr float EDT_NONE = 1e20f;
-constexpr int EDT_X = 32;          // lines of a workgroup, side by side along x
-constexpr int EDT_THREADS = 256;
-constexpr int EDT_ROWS = EDT_THREADS / EDT_X;
+// Lines of a workgroup, side by side along x, and its threads.
+constexpr int EDT_X = 32, EDT_THREADS = 256;
+// ... where such workgroups would be fewer than a quarter of the CUs: the time
+// is then that of one workgroup, whose threads take the positions of their
+// lines in turn.  A quarter of the lines and four times the threads, and still
+// no more than one workgroup per CU.  8 x 8 x 1024, half of the voxels
+// occupied: z pass 159 us, 27 so (256 threads with 8 lines: 48; 1024 with 32:
+// 73); 2 x 200 x 200: 39 and 18.  With more workgroups the narrow ones lose
+// what their short rows cost in memory and in barriers (100^3, 313 workgroups
+// of 32 lines: 29 us, 52 narrow; 1024 x 1024 x 16: 146 and 1660).
+constexpr int EDT_XN = 8, EDT_THREADSN = 1024;
+bool edt_narrow(long long workgroups, int cu_count) { return 4 * workgroups <= cu_count; }
 
 // Candidates per block: the block minima fit into LDS beside a line of 1024.
 __host__ __device__ inline int edt_block_shift(int n) { return n <= 512 ? 3 : 4; }
 
-// In LDS, element [i * EDT_X + column]: the candidates s[q], q < n; the
-// minimum of each block of 2^bs of them, signed like them (0 where the block
-// holds both kinds: a zero of either field); the minimisers of the positions
-// that are multiples of four.
+// In LDS, X lines side by side, element [i * X + column]: the candidates s[q],
+// q < n; the minimum of each block of 2^bs of them, signed like them (0 where
+// the block holds both kinds: a zero of either field); the minimisers of the
+// positions that are multiples of four.
+template <int X_>
 struct EdtLines {
+  static constexpr int X = X_;
   float *s, *blk;
   unsigned short* opt;
   int n, bs, col;
   __device__ __forceinline__ EdtLines(float* lds, int n_)
-      : s(lds), n(n_), bs(edt_block_shift(n_)), col((int)threadIdx.x % EDT_X) {
-    blk = s + n * EDT_X;
-    opt = reinterpret_cast<unsigned short*>(blk + (((n - 1) >> bs) + 1) * EDT_X);
+      : s(lds), n(n_), bs(edt_block_shift(n_)), col((int)threadIdx.x % X) {
+    blk = s + n * X;
+    opt = reinterpret_cast<unsigned short*>(blk + (((n - 1) >> bs) + 1) * X);
   }
-  __device__ __forceinline__ float at(int q) const { return s[q * EDT_X + col]; }
+  __device__ __forceinline__ float at(int q) const { return s[q * X + col]; }
 };
 
-size_t edt_lds(int n) {
-  return (size_t)EDT_X * ((n + ((n - 1) >> edt_block_shift(n)) + 1) * sizeof(float) +
-                          (n + 3) / 4 * sizeof(unsigned short));
+size_t edt_lds(int n, int x) {
+  return (size_t)x * ((n + ((n - 1) >> edt_block_shift(n)) + 1) * sizeof(float) +
+                      (n + 3) / 4 * sizeof(unsigned short));
+}
+
+// A row of a tile of k_edt_xy: its word, and the nearest occupied and free
+// position before and after that word.
+struct EdtRow {
+  unsigned own;
+  short po, pf, no, nf;
+};
+size_t edt_xy_lds(int ny, int x) {
+  return std::max(edt_lds(ny, x), (size_t)ny * (x * sizeof(float) + sizeof(EdtRow)));
 }
 
 // N positions p0 + i step of one field (sg > 0: that of the free voxels):
@@ -232,7 +253,8 @@ struct EdtBest {
       arg[i] = 0;
     }
   }
-  __device__ __forceinline__ void take(const EdtLines& L, int q) {
+  template <class Lines>
+  __device__ __forceinline__ void take(const Lines& L, int q) {
     const float d = (float)q - p0, c0 = fmaf(d, d, fmaxf(sg * L.at(q), 0.f));
 #pragma unroll
     for (int i = 0; i < N; ++i) {
@@ -248,13 +270,14 @@ struct EdtBest {
   // place to the positions is no less than the largest sum so far.  All of
   // them, eight reads in flight, also where only some were asked for: more
   // candidates never change a minimum.
-  __device__ __forceinline__ void block(const EdtLines& L, int b) {
+  template <class Lines>
+  __device__ __forceinline__ void block(const Lines& L, int b) {
     const float q0 = (float)(b << L.bs), q1 = q0 + (float)((1 << L.bs) - 1);
     const float d = fmaxf(fmaxf(q0 - (p0 + (N - 1) * step), p0 - q1), 0.f);
     float most = best[0];
 #pragma unroll
     for (int i = 1; i < N; ++i) most = fmaxf(most, sum(i));
-    if (fmaf(d, d, fmaxf(sg * L.blk[b * EDT_X + L.col], 0.f)) >= most) return;
+    if (fmaf(d, d, fmaxf(sg * L.blk[b * Lines::X + L.col], 0.f)) >= most) return;
     for (int q = b << L.bs; q < (b + 1) << L.bs; q += 8) {
 #pragma unroll
       for (int k = 0; k < 8; ++k) take(L, min(q + k, L.n - 1));
@@ -266,14 +289,14 @@ struct EdtBest {
 // of each in the field its own kind needs, over the candidates between the
 // minimisers of a and b (b past the end: the end of the line).  An a or b of
 // the other kind is a zero of that field, and so its own minimiser.
-template <int N, bool ARG, class Put>
-__device__ __forceinline__ void edt_gap(const EdtLines& L, int a, int b, int p0, int step,
+template <int N, bool ARG, class Lines, class Put>
+__device__ __forceinline__ void edt_gap(const Lines& L, int a, int b, int p0, int step,
                                         Put put) {
   const bool past = b >= L.n;
   const int be = past ? L.n - 1 : b;
   const bool fa = L.at(a) > 0.f, fb = past || L.at(be) > 0.f;
-  const int oa = L.opt[(a >> 2) * EDT_X + L.col];
-  const int ob = past ? be : L.opt[(be >> 2) * EDT_X + L.col];
+  const int oa = L.opt[(a >> 2) * Lines::X + L.col];
+  const int ob = past ? be : L.opt[(be >> 2) * Lines::X + L.col];
   bool fr[N], some = false, other = false;
 #pragma unroll
   for (int i = 0; i < N; ++i) {
@@ -300,11 +323,12 @@ __device__ __forceinline__ void edt_gap(const EdtLines& L, int a, int b, int p0,
 
 // All lines of the workgroup: put(p, signed minimum) for every position.
 // Every thread must call it, after s is filled.
-template <class Put>
-__device__ __forceinline__ void edt_lines(const EdtLines& L, Put put) {
-  const int n = L.n, g0 = threadIdx.x / EDT_X, nb = ((n - 1) >> L.bs) + 1;
+template <int THREADS, class Lines, class Put>
+__device__ __forceinline__ void edt_lines(const Lines& L, Put put) {
+  constexpr int X = Lines::X, ROWS = THREADS / X;
+  const int n = L.n, g0 = threadIdx.x / X, nb = ((n - 1) >> L.bs) + 1;
   __syncthreads();
-  for (int b = g0; b < nb; b += EDT_ROWS) {
+  for (int b = g0; b < nb; b += ROWS) {
     const int q1 = min(n, (b + 1) << L.bs);
     float mo = EDT_NONE, mf = EDT_NONE;   // minima of the two fields
     for (int q = b << L.bs; q < q1; ++q) {
@@ -312,11 +336,11 @@ __device__ __forceinline__ void edt_lines(const EdtLines& L, Put put) {
       mo = fminf(mo, fmaxf(v, 0.f));
       mf = fminf(mf, fmaxf(-v, 0.f));
     }
-    L.blk[b * EDT_X + L.col] = mo - mf;   // one of them is zero
+    L.blk[b * X + L.col] = mo - mf;   // one of them is zero
   }
   __syncthreads();
   // every 64th position: its block, then outward while a block is near enough
-  for (int p = g0 * 64; p < n; p += EDT_ROWS * 64) {
+  for (int p = g0 * 64; p < n; p += ROWS * 64) {
     const float v = L.at(p);
     EdtBest<1, true> r(p, 0, v > 0.f ? 1.f : -1.f);
     r.best[0] = fabsf(v);
@@ -329,18 +353,18 @@ __device__ __forceinline__ void edt_lines(const EdtLines& L, Put put) {
       if (b0 - k >= 0) r.block(L, b0 - k);
       if (b0 + k < nb) r.block(L, b0 + k);
     }
-    L.opt[(p >> 2) * EDT_X + L.col] = (unsigned short)r.arg[0];
+    L.opt[(p >> 2) * X + L.col] = (unsigned short)r.arg[0];
   }
   __syncthreads();
   for (int S = 16; S >= 4; S >>= 2) {
-    for (int a = g0 * 4 * S; a + S < n; a += EDT_ROWS * 4 * S) {
+    for (int a = g0 * 4 * S; a + S < n; a += ROWS * 4 * S) {
       edt_gap<3, true>(L, a, a + 4 * S, a + S, S, [&](int i, float, int arg) {
-        L.opt[((a + (i + 1) * S) >> 2) * EDT_X + L.col] = (unsigned short)arg;
+        L.opt[((a + (i + 1) * S) >> 2) * X + L.col] = (unsigned short)arg;
       });
     }
     __syncthreads();
   }
-  for (int a = g0 * 4; a < n; a += EDT_ROWS * 4) {
+  for (int a = g0 * 4; a < n; a += ROWS * 4) {
     edt_gap<4, false>(L, a, a + 4, a, 1, [&](int i, float f, int) { put(a + i, f); });
   }
 }
@@ -383,28 +407,24 @@ k_edt_bits(const uint8_t* __restrict__ occ, int nx, int rows, unsigned* __restri
   }
 }
 
-// Passes along x and y: one workgroup per tile of EDT_X columns of one z
-// plane.  The tile is one word of each row's bits, so the nearest opposite
-// voxel on the row is in that word or is one of four positions that the
-// whole row of the tile shares (the nearest occupied and free one before
-// and after it), found by one thread per row.
-__global__ void __launch_bounds__(EDT_THREADS)
+// Passes along x and y: one workgroup per tile of X columns of one z plane.
+// The tile is in one word of each row's bits, so the nearest opposite voxel on
+// the row is in that word or is one of four positions that the whole row of
+// the tile shares (the nearest occupied and free one before and after the
+// word), found by one thread per row.
+template <int THREADS, int X>
+__global__ void __launch_bounds__(THREADS)
 k_edt_xy(const unsigned* __restrict__ bits, int nx, int ny, float* __restrict__ out) {
   extern __shared__ float s_line[];
-  const EdtLines L(s_line, ny);
-  const int x0 = blockIdx.x * EDT_X, w0 = blockIdx.x;
+  const EdtLines<X> L(s_line, ny);
+  const int x = blockIdx.x * X + L.col, w0 = blockIdx.x * X / 32;
+  const int x0 = w0 * 32, bit = x - x0;   // the tile is in one word of each row
   const int words = 2 * ((nx + WAVE - 1) / WAVE);
-  // the tile's word and the four positions of each row, where the block
-  // minima and minimisers will be (the minimisers alone take 16 bytes a row)
-  struct Row {
-    unsigned own;
-    short po, pf, no, nf;
-  };
-  static_assert(sizeof(Row) <= 16, "the rows fit where the minimisers will be");
-  Row* rows = reinterpret_cast<Row*>(L.blk);
-  for (int y = threadIdx.x; y < ny; y += EDT_THREADS) {
+  // (the rows are where the block minima and minimisers will be)
+  EdtRow* rows = reinterpret_cast<EdtRow*>(L.blk);
+  for (int y = threadIdx.x; y < ny; y += THREADS) {
     const unsigned* w = bits + ((size_t)blockIdx.y * ny + y) * words;
-    Row r = {w[w0], -2048, -2048, 4096, 4096};
+    EdtRow r = {w[w0], -2048, -2048, 4096, 4096};
     for (int k = 0; k < w0; ++k) {
       const unsigned o = w[k], f = ~o;
       if (o) r.po = (short)(k * 32 + 31 - __builtin_clz(o));
@@ -418,11 +438,10 @@ k_edt_xy(const unsigned* __restrict__ bits, int nx, int ny, float* __restrict__ 
     rows[y] = r;
   }
   __syncthreads();
-  const int x = x0 + L.col;
-  const unsigned valid = 0xFFFFFFFFu >> max(0, x0 + 32 - nx), below = (1u << L.col) - 1u;
-  for (int y = threadIdx.x / EDT_X; y < ny; y += EDT_ROWS) {
-    const Row r = rows[y];
-    const bool is_occ = (r.own >> L.col) & 1;
+  const unsigned valid = 0xFFFFFFFFu >> max(0, x0 + 32 - nx), below = (1u << bit) - 1u;
+  for (int y = threadIdx.x / X; y < ny; y += THREADS / X) {
+    const EdtRow r = rows[y];
+    const bool is_occ = (r.own >> bit) & 1;
     const unsigned opp = is_occ ? valid & ~r.own : r.own;
     const unsigned lo = opp & below, hi = opp & ~below;
     const int before = lo ? x0 + 31 - __builtin_clz(lo) : (is_occ ? r.pf : r.po);
@@ -430,27 +449,28 @@ k_edt_xy(const unsigned* __restrict__ bits, int nx, int ny, float* __restrict__ 
     const int d = min(x - before, after - x);
     // (columns past the row's end get a value that is not used)
     const float v = d < 1024 ? (float)(d * d) : EDT_NONE;
-    L.s[y * EDT_X + L.col] = is_occ ? -v : v;
+    L.s[y * X + L.col] = is_occ ? -v : v;
   }
   float* o = out + ((size_t)blockIdx.y * ny) * nx + x;
-  edt_lines(L, [&](int p, float f) {
+  edt_lines<THREADS>(L, [&](int p, float f) {
     if (x < nx) o[(size_t)p * nx] = f;
   });
 }
 
-// Pass along z over EDT_X neighbouring lines, and the distance itself: the
+// Pass along z over X neighbouring lines, and the distance itself: the
 // root of the squared distance in metres, negative inside.  In place: a
 // workgroup has its lines in LDS before it writes them.  The caller's copy, if
 // any, is written beside it, without another pass over the field.
-__global__ void __launch_bounds__(EDT_THREADS)
+template <int THREADS, int X>
+__global__ void __launch_bounds__(THREADS)
 k_edt_z(float* f, long long plane, int nz, float voxel, float* copy) {
   extern __shared__ float s_line[];
-  const EdtLines L(s_line, nz);
-  const long long l = (long long)blockIdx.x * EDT_X + L.col;
+  const EdtLines<X> L(s_line, nz);
+  const long long l = (long long)blockIdx.x * X + L.col;
   const bool in = l < plane;
-  for (int z = threadIdx.x / EDT_X; z < nz; z += EDT_ROWS)
-    L.s[z * EDT_X + L.col] = in ? f[l + z * plane] : 1.f;
-  edt_lines(L, [&](int p, float s) {
+  for (int z = threadIdx.x / X; z < nz; z += THREADS / X)
+    L.s[z * X + L.col] = in ? f[l + z * plane] : 1.f;
+  edt_lines<THREADS>(L, [&](int p, float s) {
     if (!in) return;
     const float d = s < 0.f ? -voxel * sqrtf(-s) : voxel * sqrtf(s);
     f[l + p * plane] = d;
@@ -480,19 +500,30 @@ size_t edt_bits_bytes(int nx, int ny, int nz) {
 
 hipError_t launch_esdf_from_occupancy(const uint8_t* occ, int nx, int ny, int nz, float voxel,
                                       unsigned long long* bits, float* dist, float* copy,
-                                      hipStream_t s) {
+                                      int cu_count, hipStream_t s) {
   const long long plane = (long long)nx * ny;
   const int per = EDT_THREADS / WAVE * BITS_ROWS;
+  unsigned* words = reinterpret_cast<unsigned*>(bits);
   hipLaunchKernelGGL(k_edt_bits, dim3((ny * nz + per - 1) / per), dim3(EDT_THREADS), 0, s, occ, nx,
-                     ny * nz, reinterpret_cast<unsigned*>(bits));
+                     ny * nz, words);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_edt_xy, dim3((nx + EDT_X - 1) / EDT_X, nz), dim3(EDT_THREADS),
-                     edt_lds(ny), s, reinterpret_cast<const unsigned*>(bits), nx, ny, dist);
+  const dim3 xy((nx + EDT_X - 1) / EDT_X, nz), xyn((nx + EDT_XN - 1) / EDT_XN, nz);
+  if (edt_narrow((long long)xy.x * nz, cu_count))
+    hipLaunchKernelGGL((k_edt_xy<EDT_THREADSN, EDT_XN>), xyn, dim3(EDT_THREADSN),
+                       edt_xy_lds(ny, EDT_XN), s, words, nx, ny, dist);
+  else
+    hipLaunchKernelGGL((k_edt_xy<EDT_THREADS, EDT_X>), xy, dim3(EDT_THREADS),
+                       edt_xy_lds(ny, EDT_X), s, words, nx, ny, dist);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_edt_z, dim3((unsigned)((plane + EDT_X - 1) / EDT_X)), dim3(EDT_THREADS),
-                     edt_lds(nz), s, dist, plane, nz, voxel, copy);
+  const long long z = (plane + EDT_X - 1) / EDT_X, zn = (plane + EDT_XN - 1) / EDT_XN;
+  if (edt_narrow(z, cu_count))
+    hipLaunchKernelGGL((k_edt_z<EDT_THREADSN, EDT_XN>), dim3((unsigned)zn), dim3(EDT_THREADSN),
+                       edt_lds(nz, EDT_XN), s, dist, plane, nz, voxel, copy);
+  else
+    hipLaunchKernelGGL((k_edt_z<EDT_THREADS, EDT_X>), dim3((unsigned)z), dim3(EDT_THREADS),
+                       edt_lds(nz, EDT_X), s, dist, plane, nz, voxel, copy);
   return hipGetLastError();
 }
 
