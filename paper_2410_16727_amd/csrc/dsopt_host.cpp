@@ -426,7 +426,8 @@ int fill_scene(ds_plan* p, int32_t scene_id, const float* vals, const SceneRec& 
                hipStream_t s) {
   const SceneDev& d = rec.dev;
   HIP_TRY(launch_esdf_pack(vals, d.nx, d.ny, d.nz, d.cshift, d.cdx, d.cdy, d.cdz, d.cq,
-                           const_cast<float4*>(d.rec), const_cast<uint8_t*>(d.coarse), s));
+                           const_cast<float4*>(d.rec), const_cast<uint8_t*>(d.coarse), p->cu_count,
+                           s));
   p->scenes[scene_id] = rec;
   return DS_OK;
 }

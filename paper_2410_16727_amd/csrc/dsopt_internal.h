@@ -128,7 +128,7 @@ inline bool params_ext(const ParamsDev& P) { return P.ws != 0.f || P.nsub > 0; }
 // A field's cell records and its coarse table (COARSE_BYTES) (dsopt_scene.hip).
 hipError_t launch_esdf_pack(const float* vals, int nx, int ny, int nz, int shift, int cdx,
                             int cdy, int cdz, float cq, float4* rec, uint8_t* table,
-                            hipStream_t s);
+                            int cu_count, hipStream_t s);
 // The signed distance field of an occupancy grid into dist and, if not null,
 // copy (bits: edt_bits_bytes) (dsopt_scene.hip).
 size_t edt_bits_bytes(int nx, int ny, int nz);

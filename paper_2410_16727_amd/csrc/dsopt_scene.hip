@@ -29,13 +29,19 @@ namespace {
 // is not in its run it forms that block's minimum from the nodes as well, so
 // no byte has two writers and the table needs no clearing.
 //
-// Bound: HBM, 36 bytes a cell (4 read, 32 written).  200^3: 57 us, 4.9 TB/s
-// of the 5.2 a large copy reaches here (one thread per record and a second
-// kernel that read the field again for the table: 54 + 35 us, and 5 us to
-// clear it).  Workgroups of 256 threads: 60 us; stores past the caches: 146.
+// Bound: HBM, 36 bytes a cell (4 read, 32 written).  200^3, behind the kernel
+// that wrote the field: 56 us, 5.1 TB/s of the 5.2 a large copy reaches here
+// (one thread per record and a second kernel that read the field again for the
+// table: 54 + 33 us, and 5 us to clear it).  Stores past the caches: 146.
 constexpr int PACK_BLOCKS = 32;
 constexpr int PACK_THREADS = 512;
 constexpr int PACK_Z = 4;
+
+// Records that the memory-side cache does not hold are written to memory in the
+// order of the workgroups.
+bool past_cache(int nx, int ny, int nz) {
+  return (long long)(nx - 1) * (ny - 1) * (nz - 1) * 32 > 256 << 20;
+}
 
 // Blocks of a workgroup along each axis: about a column of cells per thread.
 // Of a long row a part, of an even number of blocks; of short ones as many
@@ -45,13 +51,18 @@ constexpr int PACK_Z = 4;
 // workgroups, or rows cut into a long and a short part of which one half of
 // the XCDs got all the long ones (400^3: 884 us, 730 so; 300 x 250 x 200: 248
 // and 163).  Parts of four times that, 400^3: 893 us, 300 x 250 x 200: 186;
-// of half, 186 for the latter.
+// of half, 186 for the latter.  A whole row where one per workgroup comes to
+// about the same number for every CU and the records stay in the cache
+// (196 x 185 x 154, 460 rows: 35 us of the kernel, 43 in parts; 155 x 137 x 147,
+// 342 rows: 25 and 24; 256^3, 1024 rows: 188 and 158).
 struct PackTile {
   int x, y, z;
 };
-PackTile pack_tile(int nx, int ny, int shift, int cdx, int cdy, int cdz) {
+PackTile pack_tile(int nx, int ny, int nz, int shift, int cdx, int cdy, int cdz, int cu_count) {
   const int most = std::min(PACK_BLOCKS, std::max(2, PACK_THREADS >> (2 * shift)));
   if (cdx > most) {
+    const int rows = cdy * cdz, slots = (rows + cu_count - 1) / cu_count * cu_count;
+    if (cdx <= PACK_BLOCKS && !past_cache(nx, ny, nz) && rows >= 0.85 * slots) return {cdx, 1, 1};
     const int parts = (cdx + most - 1) / most, each = (cdx + parts - 1) / parts;
     return {each + (each & 1), 1, 1};
   }
@@ -60,6 +71,35 @@ PackTile pack_tile(int nx, int ny, int shift, int cdx, int cdy, int cdz) {
   if (t.y == cdy)
     t.z = std::max(1, std::min({cdz, PACK_BLOCKS / (cdx * cdy), PACK_THREADS / ((nx - 1) * (ny - 1))}));
   return t;
+}
+
+// Whether the records and the table get a kernel each.  Past the cache the
+// records are best written in their own order, at the price of a second reading
+// of the field:
+// 40 x 600 x 700 230 us in one pass, 126 + 38 in two; 204^3 84, 53 + 14;
+// 700 x 600 x 40 185, 137 + 23.  Not where the one pass keeps its lanes busy,
+// by the columns of its tiles and the last round of its workgroups (256^3 148,
+// 140 + 23; 400^3 701, 637 + 90; equal at about 0.85 of the lanes), or where
+// every row of records begins at a cache line, which no two workgroups then
+// share (741 x 377 x 140 380, 379 + 54).  Below 256 MB: 215 x 85 x 416 54,
+// 51 + 14; 128^3 16, 15 + 5.
+bool pack_apart(int nx, int ny, int nz, int shift, const PackTile& t, int parts, int cdy, int cdz,
+                int cu_count) {
+  const int cx = nx - 1, cy = ny - 1;
+  if (!past_cache(nx, ny, nz) || cx % 4 == 0 || t.z > 1) return false;
+  // lanes that the workgroups have, and those with a column
+  const int rows = (cdy + t.y - 1) / t.y;
+  const int w = parts > 1 ? t.x << shift : cx, wl = cx - (parts - 1) * w;
+  const int h = rows > 1 ? t.y << shift : cy, hl = cy - (rows - 1) * h;
+  auto lanes = [](long long a, long long b) {
+    return (a * b + PACK_THREADS - 1) / PACK_THREADS * PACK_THREADS;
+  };
+  const long long all = (parts - 1) * ((rows - 1) * lanes(w, h) + lanes(w, hl)) +
+                        (rows - 1) * lanes(std::max(wl, 0), h) + lanes(std::max(wl, 0), hl);
+  const long long slots = 2048 / PACK_THREADS * (long long)cu_count;
+  const long long wgs = (long long)parts * rows * cdz;
+  const double busy = (double)cx * cy / all * wgs / ((wgs + slots - 1) / slots * slots);
+  return busy < 0.86;
 }
 
 // Order-preserving integer key of a float (for a minimum by LDS atomics).
@@ -78,35 +118,85 @@ __device__ __forceinline__ unsigned level_of(float m, float cq) {
   return L;
 }
 
+// The blocks of a workgroup, [bx0, bx0 + bxn) x [by0, by0 + byn) x
+// [bz0, bz0 + bzn): [first, last) in the table's order.  (A row's parts begin at
+// even indices of the table, but for the first; the last, shorter ones of the
+// rows are dealt to the XCDs in turn.)
+struct PackRun {
+  int bx0, by0, bz0, bxn, byn, bzn, first, last;
+};
+template <bool LAYERS>
+__device__ __forceinline__ PackRun pack_run(const PackTile& tile, int cdx, int cdy, int cdz) {
+  PackRun r;
+  r.by0 = blockIdx.y * tile.y;
+  r.byn = min(tile.y, cdy - r.by0);
+  r.bz0 = LAYERS ? blockIdx.z * tile.z : blockIdx.z;
+  r.bzn = LAYERS ? min(tile.z, cdz - r.bz0) : 1;
+  r.bx0 = 0;
+  r.bxn = cdx;
+  if (gridDim.x > 1) {
+    const int part = (blockIdx.x + blockIdx.y + blockIdx.z) % gridDim.x;
+    const int odd = (cdx * (r.by0 + cdy * r.bz0)) & 1;
+    r.bx0 = max(part * tile.x - odd, 0);
+    r.bxn = min((part + 1) * tile.x - odd, cdx) - r.bx0;
+  }
+  r.first = r.bx0 + cdx * (r.by0 + cdy * r.bz0);
+  r.last = r.first + r.bxn * r.byn * r.bzn;
+  return r;
+}
+
+// The minima of a run's blocks and of the one after them.
+__shared__ int s_min[PACK_BLOCKS + 1];
+__device__ __forceinline__ void clear_minima() {
+  for (int i = threadIdx.x; i < PACK_BLOCKS + 1; i += PACK_THREADS) s_min[i] = min_key(FLT_MAX);
+  __syncthreads();
+}
+
+// The bytes whose even block is one of this workgroup's, once its threads have
+// added their columns.
+__device__ __forceinline__ void put_levels(const PackRun& r, const float* __restrict__ v, int nx,
+                                           int ny, int nz, int shift, int cdx, int cdy, int cdz,
+                                           float cq, uint8_t* __restrict__ table) {
+  // the odd block after the run, if that byte is its own
+  if ((r.last & 1) && r.last < cdx * cdy * cdz) {
+    const int ex = r.last % cdx, ey = (r.last / cdx) % cdy, ez = r.last / (cdx * cdy);
+    const int ex0 = ex << shift, ey0 = ey << shift, ez0 = ez << shift;
+    const int lx = min((ex + 1) << shift, nx - 1) - ex0 + 1,
+              ly = min((ey + 1) << shift, ny - 1) - ey0 + 1,
+              lz = min((ez + 1) << shift, nz - 1) - ez0 + 1;
+    float m = FLT_MAX;
+    for (int e = threadIdx.x; e < lx * ly * lz; e += PACK_THREADS) {
+      const int i = e % lx, j = (e / lx) % ly, k = e / (lx * ly);
+      m = fminf(m, v[(size_t)(ex0 + i) + (size_t)nx * (ey0 + j) + (size_t)nx * ny * (ez0 + k)]);
+    }
+    for (int off = 1; off < WAVE; off <<= 1) m = fminf(m, __shfl_xor(m, off));
+    if ((threadIdx.x & (WAVE - 1)) == 0) atomicMin(&s_min[r.last - r.first], min_key(m));
+  }
+  __syncthreads();
+  for (int b = (r.first + 1) / 2 + threadIdx.x; 2 * b < r.last; b += PACK_THREADS) {
+    const int e = 2 * b - r.first;
+    const unsigned lo = level_of(key_value(s_min[e]), cq);
+    const unsigned hi = 2 * b + 1 < cdx * cdy * cdz ? level_of(key_value(s_min[e + 1]), cq) : 0u;
+    table[b] = (uint8_t)(lo | (hi << 4));
+  }
+}
+
 template <bool LAYERS>
 __global__ void __launch_bounds__(PACK_THREADS)
 k_esdf_pack(const float* __restrict__ v, int nx, int ny, int nz, int shift, int cdx, int cdy,
             int cdz, PackTile tile, float cq, float4* __restrict__ rec,
             uint8_t* __restrict__ table) {
-  __shared__ int s_min[PACK_BLOCKS + 1];   // the run's blocks and the one after them
   const int cx = nx - 1, cy = ny - 1, cz = nz - 1;
-  // this workgroup's blocks: [bx0, bx0 + bxn) x [by0, by0 + byn) x [bz0, bz0 + bzn)
-  // (a row's parts begin at even indices of the table, but for the first; the
-  // last, shorter ones of the rows are dealt to the XCDs in turn)
-  const int by0 = blockIdx.y * tile.y, byn = min(tile.y, cdy - by0);
-  const int bz0 = LAYERS ? blockIdx.z * tile.z : blockIdx.z, bzn = LAYERS ? min(tile.z, cdz - bz0) : 1;
-  int bx0 = 0, bxn = cdx;
-  if (gridDim.x > 1) {
-    const int part = (blockIdx.x + blockIdx.y + blockIdx.z) % gridDim.x;
-    const int odd = (cdx * (by0 + cdy * bz0)) & 1;
-    bx0 = max(part * tile.x - odd, 0);
-    bxn = min((part + 1) * tile.x - odd, cdx) - bx0;
-    if (bxn <= 0) return;
-  }
-  const int x0 = bx0 << shift, xn = min((bx0 + bxn) << shift, cx) - x0;
-  const int y0 = by0 << shift, yn = min((by0 + byn) << shift, cy) - y0;
-  for (int i = threadIdx.x; i < PACK_BLOCKS + 1; i += PACK_THREADS) s_min[i] = min_key(FLT_MAX);
-  __syncthreads();
+  const PackRun run = pack_run<LAYERS>(tile, cdx, cdy, cdz);
+  if (run.bxn <= 0) return;
+  const int x0 = run.bx0 << shift, xn = min((run.bx0 + run.bxn) << shift, cx) - x0;
+  const int y0 = run.by0 << shift, yn = min((run.by0 + run.byn) << shift, cy) - y0;
+  clear_minima();
   const size_t row = nx, plane = (size_t)nx * ny;
-  for (int c = threadIdx.x; c < xn * yn * bzn; c += PACK_THREADS) {
+  for (int c = threadIdx.x; c < xn * yn * run.bzn; c += PACK_THREADS) {
     const int q = c / xn, xi = c - q * xn, zi = LAYERS ? q / yn : 0, yi = q - zi * yn;
     const int x = x0 + xi, y = y0 + yi;
-    const int z0 = (bz0 + zi) << shift, z1 = min((bz0 + zi + 1) << shift, cz);
+    const int z0 = (run.bz0 + zi) << shift, z1 = min((run.bz0 + zi + 1) << shift, cz);
     const float* p = v + x + row * y + plane * z0;
     float a0 = p[0], a1 = p[1], a2 = p[row], a3 = p[row + 1];
     float m = FLT_MAX;   // (fminf drops NaN nodes)
@@ -131,31 +221,61 @@ k_esdf_pack(const float* __restrict__ v, int nx, int ny, int nz, int shift, int 
       }
     }
     m = fminf(m, fminf(fminf(a0, a1), fminf(a2, a3)));
-    atomicMin(&s_min[(xi >> shift) + bxn * ((yi >> shift) + byn * zi)], min_key(m));
+    atomicMin(&s_min[(xi >> shift) + run.bxn * ((yi >> shift) + run.byn * zi)], min_key(m));
   }
-  // the odd block after this workgroup's last one, if that byte is its own
-  const int first = bx0 + cdx * (by0 + cdy * bz0), last = first + bxn * byn * bzn;
-  if ((last & 1) && last < cdx * cdy * cdz) {
-    const int ex = last % cdx, ey = (last / cdx) % cdy, ez = last / (cdx * cdy);
-    const int ex0 = ex << shift, ey0 = ey << shift, ez0 = ez << shift;
-    const int lx = min((ex + 1) << shift, cx) - ex0 + 1, ly = min((ey + 1) << shift, cy) - ey0 + 1,
-              lz = min((ez + 1) << shift, cz) - ez0 + 1;
+  put_levels(run, v, nx, ny, nz, shift, cdx, cdy, cdz, cq, table);
+}
+
+// The records alone, one per thread in their own order.  Bound: HBM
+// (40 x 600 x 700, 588 MB: 126 us, 4.7 TB/s).
+constexpr int RECORD_THREADS = 256;
+__global__ void __launch_bounds__(RECORD_THREADS)
+k_esdf_records(const float* __restrict__ v, int nx, int ny, unsigned cells, float4* __restrict__ rec) {
+  const unsigned r = blockIdx.x * RECORD_THREADS + threadIdx.x;   // (below 2^26)
+  if (r >= cells) return;
+  const unsigned cx = nx - 1, cy = ny - 1;
+  const unsigned q = r / cx, x = r - q * cx, z = q / cy, y = q - z * cy;
+  const size_t row = nx, plane = (size_t)nx * ny;
+  const float *p = v + x + row * y + plane * z, *n = p + plane;
+  rec[2 * (size_t)r] = make_float4(p[0], p[1], p[row], p[row + 1]);
+  rec[2 * (size_t)r + 1] = make_float4(n[0], n[1], n[row], n[row + 1]);
+}
+
+// The table alone: a thread per column of nodes, which adds its minimum to
+// every block that has it (two along an axis on their common face).  Bound:
+// latency of one column's loads (40 x 600 x 700, 67 MB: 38 us; a workgroup per
+// block and a thread per node took 44, and 5 to clear the table).
+__global__ void __launch_bounds__(PACK_THREADS)
+k_esdf_table(const float* __restrict__ v, int nx, int ny, int nz, int shift, int cdx, int cdy,
+             int cdz, PackTile tile, float cq, uint8_t* __restrict__ table) {
+  const PackRun run = pack_run<false>(tile, cdx, cdy, cdz);
+  if (run.bxn <= 0) return;
+  const int x0 = run.bx0 << shift, xn = min((run.bx0 + run.bxn) << shift, nx - 1) - x0 + 1;
+  const int y0 = run.by0 << shift, yn = min((run.by0 + run.byn) << shift, ny - 1) - y0 + 1;
+  const int z0 = run.bz0 << shift, zn = min((run.bz0 + 1) << shift, nz - 1) - z0 + 1;
+  clear_minima();
+  const size_t row = nx, plane = (size_t)nx * ny;
+  const int in_block = (1 << shift) - 1;
+  for (int c = threadIdx.x; c < xn * yn; c += PACK_THREADS) {
+    const int yi = c / xn, xi = c - yi * xn;
+    const float* p = v + (x0 + xi) + row * (y0 + yi) + plane * z0;
     float m = FLT_MAX;
-    for (int e = threadIdx.x; e < lx * ly * lz; e += PACK_THREADS) {
-      const int i = e % lx, j = (e / lx) % ly, k = e / (lx * ly);
-      m = fminf(m, v[(size_t)(ex0 + i) + row * (ey0 + j) + plane * (ez0 + k)]);
+    for (int z = 0; z < zn; z += 8) {
+      float b[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) b[k] = p[plane * min(z + k, zn - 1)];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) m = fminf(m, b[k]);
     }
-    for (int off = 1; off < WAVE; off <<= 1) m = fminf(m, __shfl_xor(m, off));
-    if ((threadIdx.x & (WAVE - 1)) == 0) atomicMin(&s_min[last - first], min_key(m));
+    const int bx = xi >> shift, by = yi >> shift;
+    const bool lx = (xi & in_block) == 0 && xi > 0, ly = (yi & in_block) == 0 && yi > 0;
+    const bool hx = bx < run.bxn, hy = by < run.byn;
+    if (hx && hy) atomicMin(&s_min[bx + run.bxn * by], min_key(m));
+    if (lx && hy) atomicMin(&s_min[bx - 1 + run.bxn * by], min_key(m));
+    if (hx && ly) atomicMin(&s_min[bx + run.bxn * (by - 1)], min_key(m));
+    if (lx && ly) atomicMin(&s_min[bx - 1 + run.bxn * (by - 1)], min_key(m));
   }
-  __syncthreads();
-  // bytes whose even block is one of this workgroup's
-  for (int b = (first + 1) / 2 + threadIdx.x; 2 * b < last; b += PACK_THREADS) {
-    const int e = 2 * b - first;
-    const unsigned lo = level_of(key_value(s_min[e]), cq);
-    const unsigned hi = 2 * b + 1 < cdx * cdy * cdz ? level_of(key_value(s_min[e + 1]), cq) : 0u;
-    table[b] = (uint8_t)(lo | (hi << 4));
-  }
+  put_levels(run, v, nx, ny, nz, shift, cdx, cdy, cdz, cq, table);
 }
 
 // ---------------------------------------------- ESDF from an occupancy grid --
@@ -482,14 +602,21 @@ k_edt_z(float* f, long long plane, int nz, float voxel, float* copy) {
 
 hipError_t launch_esdf_pack(const float* vals, int nx, int ny, int nz, int shift, int cdx,
                             int cdy, int cdz, float cq, float4* rec, uint8_t* table,
-                            hipStream_t s) {
-  const PackTile t = pack_tile(nx, ny, shift, cdx, cdy, cdz);
+                            int cu_count, hipStream_t s) {
+  const PackTile t = pack_tile(nx, ny, nz, shift, cdx, cdy, cdz, cu_count);
   // (in odd rows of an odd length the parts begin one block earlier)
   const int parts = t.x == cdx ? 1 : (cdx + (cdx & 1) + t.x - 1) / t.x;
-  const auto kernel = t.z > 1 ? k_esdf_pack<true> : k_esdf_pack<false>;
-  hipLaunchKernelGGL(kernel,
-                     dim3(parts, (cdy + t.y - 1) / t.y, (cdz + t.z - 1) / t.z),
-                     dim3(PACK_THREADS), 0, s, vals, nx, ny, nz, shift, cdx, cdy, cdz, t, cq, rec,
+  const dim3 grid(parts, (cdy + t.y - 1) / t.y, (cdz + t.z - 1) / t.z), block(PACK_THREADS);
+  if (!pack_apart(nx, ny, nz, shift, t, parts, cdy, cdz, cu_count)) {
+    hipLaunchKernelGGL(t.z > 1 ? k_esdf_pack<true> : k_esdf_pack<false>, grid, block, 0, s, vals,
+                       nx, ny, nz, shift, cdx, cdy, cdz, t, cq, rec, table);
+    return hipGetLastError();
+  }
+  const unsigned cells = (unsigned)(nx - 1) * (ny - 1) * (nz - 1);
+  hipLaunchKernelGGL(k_esdf_records, dim3((cells + RECORD_THREADS - 1) / RECORD_THREADS),
+                     dim3(RECORD_THREADS), 0, s, vals, nx, ny, cells, rec);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_esdf_table, grid, block, 0, s, vals, nx, ny, nz, shift, cdx, cdy, cdz, t, cq,
                      table);
   return hipGetLastError();
 }

@@ -1,6 +1,6 @@
 """Records and coarse table of grids whose rows of blocks are cut into parts
-(rows of even and odd length, blocks of 4, 8 and 16 cells) or joined, by rows
-and by layers: every record and every level against numpy, exactly."""
+(rows of even and odd length, blocks of 4, 8 and 16 cells), whole where one per
+workgroup fills the CUs evenly, or joined, by rows and by layers: every record and every level against numpy, exactly."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -16,7 +16,8 @@ import test_gpu_scene_build as build  # noqa: E402
     (2, 2, 700), (3, 5, 90), (5, 4, 66), (9, 6, 139),                      # layers joined
     (2, 300, 7), (5, 70, 41), (12, 90, 10), (61, 23, 9), (129, 30, 6),     # rows joined
     (130, 7, 6), (134, 70, 5), (300, 130, 120), (290, 131, 121),           # parts, 4 and 8 cells
-    (1470, 1460, 2), (1450, 1470, 2)])                                     # parts, 16 cells
+    (1470, 1460, 2), (1450, 1470, 2),                                      # parts, 16 cells
+    (148, 145, 111), (158, 145, 111)])                                     # whole rows, odd and even
 def test_records_and_table(dims):
     print(f"grid {dims}", flush=True)
     build.test_records_and_table(dims)
