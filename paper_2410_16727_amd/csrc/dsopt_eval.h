@@ -848,13 +848,19 @@ __device__ __forceinline__ void sweep(const ParamsDev& P, const Sampler& S, cons
   const Links ln = S.ln;
   float sn[NJ], cs[NJ];
   // the frame of link l from that of its predecessor
-  auto advance = [&](int l) {
-    float F[12];
+  auto fixed = [&](int l, float* F) {
 #pragma unroll
     for (int r = 0; r < 3; ++r) *reinterpret_cast<float4*>(F + 4 * r) = s_frame[3 * l + r];
+  };
+  auto advance_by = [&](int l, const float* F) {
 #pragma unroll
     for (int r = 0; r < 3; ++r) frame_row(F, sn[l], cs[l], R + 3 * r, p[r]);
     tw.put(l, R, p);
+  };
+  auto advance = [&](int l) {
+    float F[12];
+    fixed(l, F);
+    advance_by(l, F);
   };
   if constexpr (!KIN) {
     sincos_n<NJ>(q, sn, cs);
@@ -925,22 +931,32 @@ __device__ __forceinline__ void sweep(const ParamsDev& P, const Sampler& S, cons
     }
   } else {
     constexpr int C = KIN ? 2 : CH;   // (a full team has eight copies at least)
-    // SMALL: a team's later wavefronts run out of a link's spheres before its
-    // first one does, and make fewer tests: what counts is left from their own
-    // first copy on.  (50 iterations of 10 seeds with nine spheres on some
-    // links: W = 2 908 us, 887 us so; W = 4 718 and 704 us.  One wavefront per
-    // seed has nothing to gain and loses 3 % to the longer code.)
+    // SMALL (teams of 2 and 4, and robots with bare links): a team's later
+    // wavefronts run out of a link's spheres before its first one does, and make
+    // fewer tests: what counts is left from their own first copy on; where
+    // nothing is, or on a link without spheres, the next frame is formed at
+    // once, its fixed transform being read ahead.  (50 iterations of 10 seeds
+    // with nine spheres on some links: W = 2 893 us with a branch per sample,
+    // 908 with the tests in straight lines, 887 from the first copy on; W = 4
+    // 700, 718 and 704.  30 iterations of 300 seeds of 32 waypoints, 0, 1, 17,
+    // 3, 0, 9 and 0 spheres on the links: W = 1 718, 765 and 699, W = 2 657,
+    // 710 and 642, W = 4 557, 622 and 554, W = 8 750, 766 and 642.  One
+    // wavefront per seed of a robot with spheres on every link has nothing to
+    // gain and loses 1 to 4 % to the longer code, a full team 1 to 2 %.)
     const int cp0 = SMALL ? __builtin_amdgcn_readfirstlane(cp) : 0;
     if constexpr (!KIN) advance(0);
 #pragma unroll
     for (int l = 0; l < NJ; ++l) {
       const int s1 = ln.begin(l + 1);
+      if (KIN && SMALL && ln.begin(l) >= s1) continue;
       const LinkGrid lg = link_grid(S, tw.z[l], tw.o[l]);
       if (KIN && !ln.axis(l)) team_frame(tm, tw, l, R, p);
       float FM[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
       bool forced = false;   // some sample of this link added a force
       // this lane takes every (W*L)-th sphere of the link
       int s = ln.begin(l);
+      float Fn[12];
+      if (SMALL && !KIN && l + 1 < NJ) fixed(l + 1, Fn);
       do {
         int sk[C];
         float oz[C], r[C], u[C][3], cm[C];
@@ -967,33 +983,36 @@ __device__ __forceinline__ void sweep(const ParamsDev& P, const Sampler& S, cons
 #pragma unroll
           for (int k = 0; k < N; ++k) use[k] &= !(SKIP & (cm[k] >= r[k] + P.far));
         };
-        if (C == 2 || s + 2 * LW < s1 - cp0) {
-          test(std::integral_constant<int, C>());
-        } else if (!SMALL || s + LW < s1 - cp0) {   // at most two spheres per lane are left
 #pragma unroll
-          for (int k = 2; k < C; ++k) use[k] = false;
-          test(std::integral_constant<int, 2>());
-        } else {
-          use[1] = false;
+        for (int k = 0; k < C; ++k) use[k] = false;
+        if (!SMALL || s < s1 - cp0) {   // (else no sphere for this wavefront)
+          if (C == 2 || s + 2 * LW < s1 - cp0)
+            test(std::integral_constant<int, C>());
+          else if (!SMALL || s + LW < s1 - cp0)   // at most two spheres per lane are left
+            test(std::integral_constant<int, 2>());
+          else
+            test(std::integral_constant<int, 1>());
 #pragma unroll
-          for (int k = 2; k < C; ++k) use[k] = false;
-          test(std::integral_constant<int, 1>());
-        }
-#pragma unroll
-        for (int k = 0; k < C; ++k) {
-          some |= use[k];
-          if (use[k]) {
-            int ci[3];
-            cell_of(S, u[k], ci);
-            const int off = record_offset(S, ci);
-            ra[k] = load_rec(S, off);
-            rz[k] = load_rec(S, off + 16);
-            ++ng;
+          for (int k = 0; k < C; ++k) {
+            some |= use[k];
+            if (use[k]) {
+              int ci[3];
+              cell_of(S, u[k], ci);
+              const int off = record_offset(S, ci);
+              ra[k] = load_rec(S, off);
+              rz[k] = load_rec(S, off + 16);
+              ++ng;
+            }
           }
         }
         s += LW * C;
         if constexpr (!KIN)
-          if (l + 1 < NJ && s >= s1) advance(l + 1);
+          if (l + 1 < NJ && s >= s1) {
+            if constexpr (SMALL)
+              advance_by(l + 1, Fn);
+            else
+              advance(l + 1);
+          }
         if (__any(some)) {
 #pragma unroll
           for (int k = 0; k < C; ++k)
@@ -1318,7 +1337,8 @@ __device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
 
 // The evaluation form for this team: PIPE when every lane holds at most one
 // sphere per link; shared kinematics for a full team (FULL: MAX_TEAM
-// wavefronts; SMALL: the optimiser's smaller ones).  Full teams have kernels
+// wavefronts; SMALL: the optimiser's smaller ones, and any with bare links).
+// Full teams have kernels
 // of their own: a kernel with both forms pays for both in registers and in
 // instruction fetch (100 iterations of 32 seeds in teams of eight: 1060 us,
 // 1000 us with the full team's alone).

@@ -342,14 +342,14 @@ int run_optimize(ds_plan* p, const ds_problem* probs, int n, hipStream_t s, floa
   if (int rc = timed_launch(p, s, [&]() {
         if (ordered) {
           hipError_t e = launch_optimize(p->robot_dev, p->params_dev, pd_dev, td_dev, total_tiles,
-                                         counter, blocks, 0, W, params_ext(p->params), s,
+                                         counter, blocks, 0, opt_form(p->params, p->robot), s,
                                          ranges_dev);
           if (e != hipSuccess) return e;
           e = launch_queue_order(td_dev, ranges_dev, list_dev, counter, s);
           if (e != hipSuccess) return e;
         }
         return launch_optimize(p->robot_dev, p->params_dev, pd_dev, td_dev, total_tiles, counter,
-                               blocks, p->params.n_iters, W, params_ext(p->params), s,
+                               blocks, p->params.n_iters, opt_form(p->params, p->robot), s,
                                ranges_dev, ordered ? list_dev : nullptr);
       }))
     return rc;
@@ -545,7 +545,7 @@ int ds_plan_create(const ds_robot* robot, const ds_params* prm, void* arena_dev,
   P.skip = prm->exact_gathers ? 0 : 1;
   P.drain = prm->serve_drain ? 1 : 0;
   P.vlim = prm->v_limit; P.alim = prm->a_limit; P.jlim = prm->j_limit;
-  p->blocks_per_cu = optimize_blocks_per_cu(P.waves, params_ext(P));
+  p->blocks_per_cu = optimize_blocks_per_cu(opt_form(P, rb));
   // the allocation-free call's device array, resolved once per device
   if (int rc = noalloc_init(p->device)) return rc;
 

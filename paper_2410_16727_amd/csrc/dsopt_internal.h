@@ -125,6 +125,17 @@ bool ds_serve_uses_scene(const ds_plan* plan, int32_t scene_id);
 // with the optional terms (self-collision, swept sub-samples) compiled in.
 namespace dsk {
 inline bool params_ext(const ParamsDev& P) { return P.ws != 0.f || P.nsub > 0; }
+// What the optimiser's kernel is chosen by (bare: two or more links have no
+// spheres).
+struct OptForm {
+  int waves;
+  bool ext, bare;
+};
+inline OptForm opt_form(const ParamsDev& P, const RobotDev& R) {
+  int none = 0;
+  for (int l = 0; l < NJ; ++l) none += R.link_begin[l] == R.link_begin[l + 1];
+  return {P.waves, params_ext(P), none >= 2};
+}
 // A field's cell records and its coarse table (COARSE_BYTES) (dsopt_scene.hip).
 hipError_t launch_esdf_pack(const float* vals, int nx, int ny, int nz, int shift, int cdx,
                             int cdy, int cdz, float cq, float4* rec, uint8_t* table,
@@ -140,7 +151,7 @@ hipError_t launch_esdf_from_occupancy(const uint8_t* occ, int nx, int ny, int nz
 // tile_list (optional): the queue order, a permutation of 0..n_tiles-1.
 hipError_t launch_optimize(const RobotDev* rb, const ParamsDev* pp, const ProbDev* probs,
                            const TileDev* tiles, int n_tiles, int* counter, int grid_blocks,
-                           int max_iters, int waves, bool ext, hipStream_t s,
+                           int max_iters, const OptForm& form, hipStream_t s,
                            const int* xcd_ranges = nullptr, const int* tile_list = nullptr);
 // Order each per-XCD queue (xcd_ranges: N_XCD + 1 ints) longest expected
 // tile first -- larger lane groups first, then higher cost at the seed (the
@@ -165,10 +176,10 @@ hipError_t launch_tile_reset(const TileDev* tiles, const ProbDev* probs, int n_t
                              hipStream_t s);
 hipError_t launch_serve_step(const RobotDev* rb, const ParamsDev* pp, const ProbDev* probs,
                              const TileDev* tiles, const int* tile_list, int* counter,
-                             int max_tiles, int grid_blocks, const int* max_iters_dev, int waves,
-                             bool ext, hipStream_t s);
+                             int max_tiles, int grid_blocks, const int* max_iters_dev,
+                             const OptForm& form, hipStream_t s);
 int team_block(int waves);
-int optimize_blocks_per_cu(int waves, bool ext);
+int optimize_blocks_per_cu(const OptForm& form);
 // Resolve the allocation-free call's device array on the current device
 // (dsopt_noalloc.hip); DS_OK or a DS_ERR_* code.
 int noalloc_init(int device);

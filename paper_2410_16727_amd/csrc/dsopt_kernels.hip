@@ -164,17 +164,21 @@ size_t team_lds(int W) {
 
 const void* optimize_kernel_ext(int W);   // dsopt_optimize_ext.hip
 
-static OptKernel optimize_kernel(int W, bool ext) {
-  if (ext) return reinterpret_cast<OptKernel>(const_cast<void*>(optimize_kernel_ext(W)));
-  return optimize_variant<false>(W);
+// (With one bare link in seven the plain kernels are as fast or faster; with
+// the optional terms the sweeps are a smaller part.)
+static OptKernel optimize_kernel(const OptForm& f) {
+  if (f.ext) return reinterpret_cast<OptKernel>(const_cast<void*>(optimize_kernel_ext(f.waves)));
+  if (f.bare && f.waves == 1) return k_optimize<false, false, false, true>;
+  if (f.bare && f.waves == MAX_TEAM) return k_optimize<true, false, true, true>;
+  return optimize_variant<false>(f.waves);
 }
 
 hipError_t launch_optimize(const RobotDev* rb, const ParamsDev* pp, const ProbDev* probs,
                            const TileDev* tiles, int n_tiles, int* counter, int grid_blocks,
-                           int max_iters, int W, bool ext, hipStream_t s,
+                           int max_iters, const OptForm& form, hipStream_t s,
                            const int* xcd_ranges, const int* tile_list) {
-  hipLaunchKernelGGL(optimize_kernel(W, ext), dim3(grid_blocks), dim3(team_block(W)),
-                     team_lds(W), s, rb, pp, probs, tiles, tile_list, (const int*)nullptr,
+  hipLaunchKernelGGL(optimize_kernel(form), dim3(grid_blocks), dim3(team_block(form.waves)),
+                     team_lds(form.waves), s, rb, pp, probs, tiles, tile_list, (const int*)nullptr,
                      n_tiles, counter, max_iters, (const int*)nullptr, xcd_ranges);
   return hipGetLastError();
 }
@@ -188,20 +192,20 @@ hipError_t launch_queue_order(const TileDev* tiles, const int* xcd_ranges, int* 
 
 hipError_t launch_serve_step(const RobotDev* rb, const ParamsDev* pp, const ProbDev* probs,
                              const TileDev* tiles, const int* tile_list, int* counter,
-                             int max_tiles, int grid_blocks, const int* max_iters_dev, int W,
-                             bool ext, hipStream_t s) {
+                             int max_tiles, int grid_blocks, const int* max_iters_dev,
+                             const OptForm& form, hipStream_t s) {
   // tile_list[0] holds the number of listed tiles, the indices follow; the
   // iterations of this replay are read from max_iters_dev
-  hipLaunchKernelGGL(optimize_kernel(W, ext), dim3(grid_blocks), dim3(team_block(W)),
-                     team_lds(W), s, rb, pp, probs, tiles, tile_list + 1, tile_list, max_tiles,
+  hipLaunchKernelGGL(optimize_kernel(form), dim3(grid_blocks), dim3(team_block(form.waves)),
+                     team_lds(form.waves), s, rb, pp, probs, tiles, tile_list + 1, tile_list, max_tiles,
                      counter, 0, max_iters_dev, (const int*)nullptr);
   return hipGetLastError();
 }
 
-int optimize_blocks_per_cu(int W, bool ext) {
+int optimize_blocks_per_cu(const OptForm& f) {
   int n = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, optimize_kernel(W, ext), team_block(W),
-                                                   team_lds(W)) != hipSuccess)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, optimize_kernel(f), team_block(f.waves),
+                                                   team_lds(f.waves)) != hipSuccess)
     return 1;
   return n > 0 ? n : 1;
 }

@@ -116,7 +116,7 @@ extern "C" int ds_optimize_noalloc(ds_plan* p, const ds_problem* prob,
   int blocks = (S + per_block - 1) / per_block;
   blocks = std::max(1, std::min(blocks, p->cu_count * p->blocks_per_cu));
   HIP_TRY(launch_optimize(p->robot_dev, p->params_dev, pd_dev, td_dev, S, counter, blocks,
-                          p->params.n_iters, W, params_ext(p->params), s));
+                          p->params.n_iters, opt_form(p->params, p->robot), s));
   HIP_TRY(launch_best(pd_dev, 1, nullptr, s));
   return DS_OK;
 }

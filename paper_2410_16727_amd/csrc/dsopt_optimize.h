@@ -505,11 +505,10 @@ enum { PH_INIT = 0, PH_DIR = 1, PH_TRIAL = 2, PH_ACCEPT = 3 };
 //          cost-only candidates while a seed of the tile has no Armijo step;
 //          if a seed accepted alpha < 1, evaluate there (ACCEPT), else update;
 //   ACCEPT take the accepted point's cost and gradient, update.
-template <bool LDS_HIST, bool EXT, bool FULL>
+template <bool LDS_HIST, bool EXT, bool FULL, bool SMALL>
 __device__ __forceinline__ void run_tile(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp,
                          const ProbDev* __restrict__ probs, const TileDev& td, int max_iters,
                          Team& tm, float* hist_lds, uint8_t* coarse_lds, float* dir_lds) {
-  constexpr bool SMALL = LDS_HIST && !FULL;   // a team of less than MAX_TEAM
   TileCtx c;
   c.rb = rb;
   c.P = *pp;
@@ -756,9 +755,10 @@ __device__ __forceinline__ int next_tile(int* counter, const int* __restrict__ x
 // the table; n_tiles_dev, if given, overrides n_tiles).  Every member of a
 // team sees the same tile sequence and the same decisions, so all of them
 // reach every barrier.  Variants: TEAM (W > 1, history ring in LDS), FULL
-// (W = 8, shared kinematics) and EXT (self-collision and swept terms compiled
-// in); the plain variant carries no code for the optional terms.
-template <bool TEAM, bool EXT, bool FULL>
+// (W = 8, shared kinematics), SMALL (see the sweep) and EXT (self-collision and
+// swept terms compiled in); the plain variant carries no code for the optional
+// terms.
+template <bool TEAM, bool EXT, bool FULL, bool SMALL>
 __global__ void __launch_bounds__(TEAM ? MAX_TEAM * WAVE : BLOCK, TEAM ? 1 : 2)
 k_optimize(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp,
            const ProbDev* __restrict__ probs, const TileDev* __restrict__ tiles,
@@ -796,14 +796,14 @@ k_optimize(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp,
     const int ti = tile_list ? tile_list[mine] : mine;
     TileDev td = tiles[ti];
     if constexpr (TEAM) {
-      run_tile<true, EXT, FULL>(rb, pp, probs, td, max_iters, tm, s_dyn + 2 * tm.W * PART * WAVE,
+      run_tile<true, EXT, FULL, SMALL>(rb, pp, probs, td, max_iters, tm, s_dyn + 2 * tm.W * PART * WAVE,
                                 reinterpret_cast<uint8_t*>(s_dyn + 2 * tm.W * PART * WAVE + H_FLOATS),
                                 s_dyn + 2 * tm.W * PART * WAVE + H_FLOATS + COARSE_FLOATS);
       __syncthreads();   // the LDS ring is free for the next tile
     } else {
       // this wavefront's coarse table (uniform)
       const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
-      run_tile<false, EXT, FULL>(rb, pp, probs, td, max_iters, tm, nullptr,
+      run_tile<false, EXT, FULL, SMALL>(rb, pp, probs, td, max_iters, tm, nullptr,
                                  reinterpret_cast<uint8_t*>(s_dyn + wv * COARSE_FLOATS), nullptr);
     }
   }
@@ -814,8 +814,8 @@ using OptKernel = void (*)(const RobotDev*, const ParamsDev*, const ProbDev*, co
 
 template <bool EXT>
 OptKernel optimize_variant(int W) {
-  if (W == MAX_TEAM) return k_optimize<true, EXT, true>;
-  return W > 1 ? k_optimize<true, EXT, false> : k_optimize<false, EXT, false>;
+  if (W == MAX_TEAM) return k_optimize<true, EXT, true, false>;
+  return W > 1 ? k_optimize<true, EXT, false, true> : k_optimize<false, EXT, false, false>;
 }
 
 }  // namespace
