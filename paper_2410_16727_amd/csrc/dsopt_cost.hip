@@ -160,12 +160,13 @@ __global__ void k_spheres(const RobotDev* __restrict__ rb, const float* __restri
 
 }  // namespace
 
-// Team size for k_cost / k_guide: one wavefront per seed when the seeds
-// give at least WAVES_PER_BLOCK wavefronts per CU, else teams of up to
-// WAVES_PER_BLOCK wavefronts per seed.
+// Team size for k_cost / k_guide: wavefronts per seed, doubled while all the
+// seeds' wavefronts are fewer than eight per CU (two per SIMD, which is what
+// the registers allow), up to MAX_TEAM.  The last doubling may go past that:
+// 257 to 511 seeds in teams of eight and 513 to 1023 in teams of four take two
+// rounds (gradient of 48 waypoints, 60 spheres: 256 seeds 12.7 us, 257 18.4,
+// 511 19.2, 512 14.3, 513 22.2, 1023 25.1, 1024 18.8, 2048 26.8).
 static int cost_team(int S, int cu_count) {
-  // up to 8 wavefronts per seed while the seeds alone would leave the CUs
-  // below two wavefronts per SIMD
   int W = 1;
   while (W < MAX_TEAM && (long long)S * W < (long long)2 * WAVES_PER_BLOCK * cu_count) W *= 2;
   return W;

@@ -166,8 +166,9 @@ __device__ __forceinline__ float direction(const TileCtx& c, const H& hist, cons
   // one seed per wavefront: count and head are wave-uniform
   const int cmax = __builtin_amdgcn_readfirstlane(cnt);
   const int hd = __builtin_amdgcn_readfirstlane(head);
-  // A full history (all = true, every iteration but the first few) has no
-  // branches on the count of ages (100 iterations of 32 seeds of one wavefront
+  // A history of all eight entries (all = true, every iteration but the first
+  // few; a plan with a shorter memory takes the other form) has no branches on
+  // the count of ages (100 iterations of 32 seeds of one wavefront
   // each: 1580 us, 1520 us so).  The products that stay rounded by themselves
   // are stated, so that both forms give the same bits.
   float q[NJ];
@@ -295,8 +296,9 @@ __device__ __forceinline__ float team_direction(const TileCtx& c, const H& hist,
 
   // lane i < cnt holds age i: row i of SY and YY, column i of SY.  Every
   // operand is loaded unconditionally (valid LDS addresses) and entries of
-  // ages >= cnt are replaced by zeros, so no stale value reaches a sum.  A full
-  // history (all = true, every iteration but the first few) has none, and the
+  // ages >= cnt are replaced by zeros, so no stale value reaches a sum.  A
+  // history of all eight entries (all = true, every iteration but the first
+  // few; a plan with a shorter memory takes the other form) has none, and the
   // lanes past it are not read: no selects, 60 instructions less of a phase
   // bound by issue (100 iterations of 32 seeds in teams of eight: 868 us, 840
   // us so).
