@@ -304,7 +304,7 @@ k_esdf_table(const float* __restrict__ v, int nx, int ny, int nz, int shift, int
 //
 // Bound: VALU of the candidates (half of the issue slots; the rest is the
 // latency of one round of workgroups, five per CU).  200^3 shelf scene: bits
-// 6 us, x and y 54 us, z 48 us; before, with a field for each sign and a scan
+// 6 us, x and y 54 us, z 50 us; before, with a field for each sign and a scan
 // outward from every voxel, six passes of 27 to 428 us (829 together) and
 // 50 us of kernels around them.
 constexpr float EDT_NONE = 1e20f;
