@@ -827,7 +827,9 @@ __device__ __forceinline__ float coarse_min(const Sampler& S, const float* u) {
 // R, p are left alone.
 // A sample whose coarse block holds no node nearer than radius + eps (+
 // margin) has a zero hinge (a trilinear blend stays within its corners'
-// range): it loads no record.
+// range): it loads no record.  EXACT: no sample is tested (for plans that
+// gather them all; with the tests made and not used these take up to 5 %
+// longer, and a branch around the tests costs the other plans 1 to 4 %).
 // PIPE (every lane holds at most one sphere of each link, W*L >= spheres
 // per link): the tests of all links, then their record loads, then the
 // hinges, so one memory round trip covers the whole configuration.
@@ -837,14 +839,14 @@ __device__ __forceinline__ float coarse_min(const Sampler& S, const float* u) {
 // are in flight together, where a branch per sample made each of them wait
 // for its own two (lanes without a sample go through the motions with the
 // last sphere of the table at the most).
-template <int MODE, bool PIPE, bool KIN, bool SMALL>
+template <int MODE, bool PIPE, bool KIN, bool SMALL, bool EXACT>
 __device__ __forceinline__ void sweep(const ParamsDev& P, const Sampler& S, const float* q, int cp,
                                       int LW, const Team& tm, Twists& tw, float* R, float* p,
                                       float& phisum, float& clr, float* g, int& ng, bool active) {
   constexpr bool GRAD = (MODE == EV_GRAD);
   // the result pass gathers every sample: the clearance is a minimum over
   // all of them
-  const bool SKIP = MODE != EV_RESULT && P.skip;
+  const bool SKIP = MODE != EV_RESULT && !EXACT && P.skip;
   const Links ln = S.ln;
   float sn[NJ], cs[NJ];
   // the frame of link l from that of its predecessor
@@ -1036,7 +1038,7 @@ __device__ __forceinline__ void sweep(const ParamsDev& P, const Sampler& S, cons
 // One evaluation of the objective at this lane's configuration q (its
 // waypoint) and, with swept sub-samples, at the configurations interpolated
 // towards the next waypoint.
-template <int MODE, bool PIPE, bool EXT, bool KIN, bool SMALL>
+template <int MODE, bool PIPE, bool EXT, bool KIN, bool SMALL, bool EXACT>
 __device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
                                             const ParamsDev& P, const Sampler& S, const float* q,
                                             int t, int T, int G, bool active,
@@ -1083,7 +1085,7 @@ __device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
   };
   if constexpr (!EXT) {
     if constexpr (KIN) team_kinematics(tm, q, tw, own_terms);
-    sweep<MODE, PIPE, KIN, SMALL>(P, S, q, cp, LW, tm, tw, R, p, phisum, clr, o.g, o.ng, active);
+    sweep<MODE, PIPE, KIN, SMALL, EXACT>(P, S, q, cp, LW, tm, tw, R, p, phisum, clr, o.g, o.ng, active);
   } else {
     // swept collision: q + tau (q_next - q), tau = i / (nsub + 1), i = 1 ..
     // nsub; the gradient splits (1 - tau) here and tau onto the next
@@ -1119,7 +1121,7 @@ __device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
           if (own) own_terms();
         });
       }
-      sweep<MODE, PIPE, KIN, SMALL>(P, S, qi, cp, LW, tm, tw, R, p, ph, cl, gi, o.ng, own ? active : seg);
+      sweep<MODE, PIPE, KIN, SMALL, EXACT>(P, S, qi, cp, LW, tm, tw, R, p, ph, cl, gi, o.ng, own ? active : seg);
       if (own) {
         phisum = ph;
         clr = cl;
@@ -1342,14 +1344,14 @@ __device__ __forceinline__ EvalOut evaluate(const RobotDev* __restrict__ rb,
 // of their own: a kernel with both forms pays for both in registers and in
 // instruction fetch (100 iterations of 32 seeds in teams of eight: 1060 us,
 // 1000 us with the full team's alone).
-template <int MODE, bool EXT, bool FULL, bool SMALL = false>
+template <int MODE, bool EXT, bool FULL, bool SMALL = false, bool EXACT = false>
 __device__ __forceinline__ EvalOut eval_any(bool pipe, const RobotDev* __restrict__ rb,
                                             const ParamsDev& P, const Sampler& S, const float* q,
                                             int t, int T, int G, bool active,
                                             Team& tm) {
   constexpr bool KIN = FULL && MODE != EV_RESULT;
-  if (pipe) return evaluate<MODE, true, EXT, KIN, SMALL>(rb, P, S, q, t, T, G, active, tm);
-  return evaluate<MODE, false, EXT, KIN, SMALL>(rb, P, S, q, t, T, G, active, tm);
+  if (pipe) return evaluate<MODE, true, EXT, KIN, SMALL, EXACT>(rb, P, S, q, t, T, G, active, tm);
+  return evaluate<MODE, false, EXT, KIN, SMALL, EXACT>(rb, P, S, q, t, T, G, active, tm);
 }
 
 __device__ __forceinline__ bool use_pipe(const RobotDev* __restrict__ rb, const Team& tm, int G) {

@@ -126,15 +126,15 @@ bool ds_serve_uses_scene(const ds_plan* plan, int32_t scene_id);
 namespace dsk {
 inline bool params_ext(const ParamsDev& P) { return P.ws != 0.f || P.nsub > 0; }
 // What the optimiser's kernel is chosen by (bare: two or more links have no
-// spheres).
+// spheres; exact: every sample is gathered).
 struct OptForm {
   int waves;
-  bool ext, bare;
+  bool ext, bare, exact;
 };
 inline OptForm opt_form(const ParamsDev& P, const RobotDev& R) {
   int none = 0;
   for (int l = 0; l < NJ; ++l) none += R.link_begin[l] == R.link_begin[l + 1];
-  return {P.waves, params_ext(P), none >= 2};
+  return {P.waves, params_ext(P), none >= 2, !P.skip};
 }
 // A field's cell records and its coarse table (COARSE_BYTES) (dsopt_scene.hip).
 hipError_t launch_esdf_pack(const float* vals, int nx, int ny, int nz, int shift, int cdx,

@@ -164,10 +164,13 @@ size_t team_lds(int W) {
 
 const void* optimize_kernel_ext(int W);   // dsopt_optimize_ext.hip
 
-// (With one bare link in seven the plain kernels are as fast or faster; with
-// the optional terms the sweeps are a smaller part.)
+// (With one bare link in seven the plain kernels are as fast or faster; a full
+// team's tests cost nothing beside its kinematics; with the optional terms the
+// sweeps are a smaller part.)
 static OptKernel optimize_kernel(const OptForm& f) {
   if (f.ext) return reinterpret_cast<OptKernel>(const_cast<void*>(optimize_kernel_ext(f.waves)));
+  if (f.exact && f.waves == 1) return k_optimize<false, false, false, false, true>;
+  if (f.exact && f.waves < MAX_TEAM) return k_optimize<true, false, false, true, true>;
   if (f.bare && f.waves == 1) return k_optimize<false, false, false, true>;
   if (f.bare && f.waves == MAX_TEAM) return k_optimize<true, false, true, true>;
   return optimize_variant<false>(f.waves);

@@ -507,7 +507,7 @@ enum { PH_INIT = 0, PH_DIR = 1, PH_TRIAL = 2, PH_ACCEPT = 3 };
 //          cost-only candidates while a seed of the tile has no Armijo step;
 //          if a seed accepted alpha < 1, evaluate there (ACCEPT), else update;
 //   ACCEPT take the accepted point's cost and gradient, update.
-template <bool LDS_HIST, bool EXT, bool FULL, bool SMALL>
+template <bool LDS_HIST, bool EXT, bool FULL, bool SMALL, bool EXACT>
 __device__ __forceinline__ void run_tile(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp,
                          const ProbDev* __restrict__ probs, const TileDev& td, int max_iters,
                          Team& tm, float* hist_lds, uint8_t* coarse_lds, float* dir_lds) {
@@ -611,7 +611,7 @@ __device__ __forceinline__ void run_tile(const RobotDev* __restrict__ rb, const 
       phase = PH_TRIAL;
     }
     // the one cost+gradient evaluation of this pass
-    EvalOut e = eval_any<EV_GRAD, EXT, FULL, SMALL>(c.pipe, rb, c.P, c.S, xe, c.t, c.T, c.G,
+    EvalOut e = eval_any<EV_GRAD, EXT, FULL, SMALL, EXACT>(c.pipe, rb, c.P, c.S, xe, c.t, c.T, c.G,
                                                     c.active, tm);
     ++evg;
     ngath += e.ng;
@@ -638,7 +638,7 @@ __device__ __forceinline__ void run_tile(const RobotDev* __restrict__ rb, const 
         float xk[NJ];
 #pragma unroll
         for (int j = 0; j < NJ; ++j) xk[j] = x[j] + al * d[j];
-        EvalOut ek = eval_any<EV_COST, EXT, FULL, SMALL>(c.pipe, rb, c.P, c.S, xk, c.t, c.T, c.G,
+        EvalOut ek = eval_any<EV_COST, EXT, FULL, SMALL, EXACT>(c.pipe, rb, c.P, c.S, xk, c.t, c.T, c.G,
                                                          c.active, tm);
         ++evc;
         ngath += ek.ng;
@@ -757,10 +757,10 @@ __device__ __forceinline__ int next_tile(int* counter, const int* __restrict__ x
 // the table; n_tiles_dev, if given, overrides n_tiles).  Every member of a
 // team sees the same tile sequence and the same decisions, so all of them
 // reach every barrier.  Variants: TEAM (W > 1, history ring in LDS), FULL
-// (W = 8, shared kinematics), SMALL (see the sweep) and EXT (self-collision and
-// swept terms compiled in); the plain variant carries no code for the optional
-// terms.
-template <bool TEAM, bool EXT, bool FULL, bool SMALL>
+// (W = 8, shared kinematics), SMALL and EXACT (see the sweep) and EXT
+// (self-collision and swept terms compiled in); the plain variant carries no
+// code for the optional terms.
+template <bool TEAM, bool EXT, bool FULL, bool SMALL, bool EXACT = false>
 __global__ void __launch_bounds__(TEAM ? MAX_TEAM * WAVE : BLOCK, TEAM ? 1 : 2)
 k_optimize(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp,
            const ProbDev* __restrict__ probs, const TileDev* __restrict__ tiles,
@@ -798,14 +798,14 @@ k_optimize(const RobotDev* __restrict__ rb, const ParamsDev* __restrict__ pp,
     const int ti = tile_list ? tile_list[mine] : mine;
     TileDev td = tiles[ti];
     if constexpr (TEAM) {
-      run_tile<true, EXT, FULL, SMALL>(rb, pp, probs, td, max_iters, tm, s_dyn + 2 * tm.W * PART * WAVE,
+      run_tile<true, EXT, FULL, SMALL, EXACT>(rb, pp, probs, td, max_iters, tm, s_dyn + 2 * tm.W * PART * WAVE,
                                 reinterpret_cast<uint8_t*>(s_dyn + 2 * tm.W * PART * WAVE + H_FLOATS),
                                 s_dyn + 2 * tm.W * PART * WAVE + H_FLOATS + COARSE_FLOATS);
       __syncthreads();   // the LDS ring is free for the next tile
     } else {
       // this wavefront's coarse table (uniform)
       const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
-      run_tile<false, EXT, FULL, SMALL>(rb, pp, probs, td, max_iters, tm, nullptr,
+      run_tile<false, EXT, FULL, SMALL, EXACT>(rb, pp, probs, td, max_iters, tm, nullptr,
                                  reinterpret_cast<uint8_t*>(s_dyn + wv * COARSE_FLOATS), nullptr);
     }
   }
