@@ -281,6 +281,12 @@ class Plan:
         else:
             src = occ.to(torch.uint8).contiguous()
         nz, ny, nx = src.shape
+        if out is not None:
+            # the library writes nx * ny * nz floats from out's first element on
+            room = out.untyped_storage().nbytes() - out.storage_offset() * out.element_size()
+            if room < 4 * nx * ny * nz:
+                raise DsError(DS_ERR_INVALID, f"out has room for {room} bytes, the distances take "
+                                              f"{4 * nx * ny * nz}")
         o = (C.c_float * 3)(*[float(v) for v in origin])
         check(self.lib.ds_esdf_from_occupancy(self.h, int(scene_id), C.c_void_p(src.data_ptr()),
                                               nx, ny, nz, float(voxel), o, _ptr(out),

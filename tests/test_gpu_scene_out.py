@@ -99,3 +99,23 @@ def test_distances_without_a_place_for_the_scene(host):
     pl.scene_from_occupancy(0, occ, VOXEL, ORIGIN)
     torch.cuda.synchronize()
     pl.close()
+
+
+@pytest.mark.parametrize("short", ["plain", "view", "host"])
+def test_buffer_without_room_is_refused(short):
+    """Before anything is launched: the buffer keeps its values, and the scene
+    of that id its own."""
+    occ = occupancy(5)
+    pl = make_plan()
+    pl.scene_from_occupancy(0, occupancy(6), VOXEL, ORIGIN)
+    before = score(pl, 0)
+    n = occ.numel()
+    buf = torch.full((n + 8,), 7.0, dtype=torch.float32, device="cpu" if short == "host" else "cuda")
+    out = buf[9:] if short == "view" else buf[:n - 1].clone()
+    with pytest.raises(dsopt.DsError) as e:
+        pl.scene_from_occupancy(0, occ, VOXEL, ORIGIN, out=out)
+    assert e.value.code == dsopt.DS_ERR_INVALID
+    torch.cuda.synchronize()
+    assert bool((buf == 7.0).all()) and bool((out == 7.0).all())
+    assert bool((score(pl, 0) == before).all())
+    pl.close()
