@@ -51,7 +51,9 @@ bool past_cache(int nx, int ny, int nz) {
 // workgroups, or rows cut into a long and a short part of which one half of
 // the XCDs got all the long ones (400^3: 884 us, 730 so; 300 x 250 x 200: 248
 // and 163).  Parts of four times that, 400^3: 893 us, 300 x 250 x 200: 186;
-// of half, 186 for the latter.  A whole row where one per workgroup comes to
+// of half, 186 for the latter; of blocks thin in y as many as fill the threads
+// (500000 x 2 x 9: 56 us a call with two blocks of 32 cells, 39 so).  A whole
+// row where one per workgroup comes to
 // about the same number for every CU and the records stay in the cache
 // (196 x 185 x 154, 460 rows: 35 us of the kernel, 43 in parts; 155 x 137 x 147,
 // 342 rows: 25 and 24; 256^3, 1024 rows: 188 and 158).
@@ -59,14 +61,15 @@ struct PackTile {
   int x, y, z;
 };
 PackTile pack_tile(int nx, int ny, int nz, int shift, int cdx, int cdy, int cdz, int cu_count) {
-  const int most = std::min(PACK_BLOCKS, std::max(2, PACK_THREADS >> (2 * shift)));
+  const int b = 1 << shift;
+  const int most = std::clamp(PACK_THREADS / (b * std::min(b, ny - 1)), 2, PACK_BLOCKS);
   if (cdx > most) {
     const int rows = cdy * cdz, slots = (rows + cu_count - 1) / cu_count * cu_count;
     if (cdx <= PACK_BLOCKS && !past_cache(nx, ny, nz) && rows >= 0.85 * slots) return {cdx, 1, 1};
     const int parts = (cdx + most - 1) / most, each = (cdx + parts - 1) / parts;
     return {each + (each & 1), 1, 1};
   }
-  const int columns = (nx - 1) * std::min(1 << shift, ny - 1);   // of a row of blocks
+  const int columns = (nx - 1) * std::min(b, ny - 1);   // of a row of blocks
   PackTile t{cdx, std::max(1, std::min({cdy, PACK_BLOCKS / cdx, PACK_THREADS / columns})), 1};
   if (t.y == cdy)
     t.z = std::max(1, std::min({cdz, PACK_BLOCKS / (cdx * cdy), PACK_THREADS / ((nx - 1) * (ny - 1))}));
