@@ -53,10 +53,10 @@ bool past_cache(int nx, int ny, int nz) {
 // and 163).  Parts of four times that, 400^3: 893 us, 300 x 250 x 200: 186;
 // of half, 186 for the latter; of blocks thin in y as many as fill the threads
 // (500000 x 2 x 9: 56 us a call with two blocks of 32 cells, 39 so).  A whole
-// row where one per workgroup comes to
-// about the same number for every CU and the records stay in the cache
-// (196 x 185 x 154, 460 rows: 35 us of the kernel, 43 in parts; 155 x 137 x 147,
-// 342 rows: 25 and 24; 256^3, 1024 rows: 188 and 158).
+// row where one per workgroup comes to about the same number for every CU and
+// the records stay in the cache (196 x 185 x 154, 460 rows: 35 us of the
+// kernel, 43 in parts; 155 x 137 x 147, 342 rows: 25 and 24; 256^3, 1024 rows:
+// 188 and 158).
 struct PackTile {
   int x, y, z;
 };
