@@ -313,16 +313,19 @@ k_esdf_table(const float* __restrict__ v, int nx, int ny, int nz, int shift, int
 constexpr float EDT_NONE = 1e20f;
 // Lines of a workgroup, side by side along x, and its threads.
 constexpr int EDT_X = 32, EDT_THREADS = 256;
-// ... where such workgroups would be fewer than a quarter of the CUs: the time
-// is then that of one workgroup, whose threads take the positions of their
-// lines in turn.  A quarter of the lines and four times the threads, and still
-// no more than one workgroup per CU.  8 x 8 x 1024, half of the voxels
+// ... where such workgroups would be a quarter of the CUs or fewer, and a thread
+// of them would have more than one gap of four positions: the time is then that
+// of one workgroup, whose threads take the gaps in turn.  A quarter of the
+// lines and four times the threads, and still no more than one workgroup per
+// CU.  8 x 8 x 1024, half of the voxels
 // occupied: z pass 159 us, 27 so (256 threads with 8 lines: 48; 1024 with 32:
 // 73); 2 x 200 x 200: 39 and 18.  With more workgroups the narrow ones lose
 // what their short rows cost in memory and in barriers (100^3, 313 workgroups
 // of 32 lines: 29 us, 52 narrow; 1024 x 1024 x 16: 146 and 1660).
 constexpr int EDT_XN = 8, EDT_THREADSN = 1024;
-bool edt_narrow(long long workgroups, int cu_count) { return 4 * workgroups <= cu_count; }
+bool edt_narrow(int n, long long workgroups, int cu_count) {
+  return n > 4 * (EDT_THREADS / EDT_X) && 4 * workgroups <= cu_count;
+}
 
 // Candidates per block: the block minima fit into LDS beside a line of 1024.
 __host__ __device__ inline int edt_block_shift(int n) { return n <= 512 ? 3 : 4; }
@@ -639,7 +642,7 @@ hipError_t launch_esdf_from_occupancy(const uint8_t* occ, int nx, int ny, int nz
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const dim3 xy((nx + EDT_X - 1) / EDT_X, nz), xyn((nx + EDT_XN - 1) / EDT_XN, nz);
-  if (edt_narrow((long long)xy.x * nz, cu_count))
+  if (edt_narrow(ny, (long long)xy.x * nz, cu_count))
     hipLaunchKernelGGL((k_edt_xy<EDT_THREADSN, EDT_XN>), xyn, dim3(EDT_THREADSN),
                        edt_xy_lds(ny, EDT_XN), s, words, nx, ny, dist);
   else
@@ -648,7 +651,7 @@ hipError_t launch_esdf_from_occupancy(const uint8_t* occ, int nx, int ny, int nz
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   const long long z = (plane + EDT_X - 1) / EDT_X, zn = (plane + EDT_XN - 1) / EDT_XN;
-  if (edt_narrow(z, cu_count))
+  if (edt_narrow(nz, z, cu_count))
     hipLaunchKernelGGL((k_edt_z<EDT_THREADSN, EDT_XN>), dim3((unsigned)zn), dim3(EDT_THREADSN),
                        edt_lds(nz, EDT_XN), s, dist, plane, nz, voxel, copy);
   else
